@@ -64,6 +64,14 @@ enum GettKind {
 template <typename R>
 void launch_gett(const Gett<R>& g, int kind, hipStream_t s);
 
+// FP64 products on the INT8 matrix cores (modgemm.hip): true when the product was launched,
+// false when it is not worth it or has no room in the thread's workspace.
+void set_mod_workspace(void* p, size_t bytes);
+bool mod_gemm_pays(int64_t M, int64_t N, int64_t K);
+int64_t mod_plane_bytes(int64_t rows, int64_t K);  // residues of a rows x K operand
+int64_t mod_out_bytes(int64_t M, int64_t N);       // residues of an M x N product
+bool mod_gemm(const Gett<double>& g, hipStream_t s);
+
 // BF16x3 on pre-split operands (layout in gett.hip): K rounded up to the split
 // width; split `rows` rows of K complex FP32 values (row r at src +
 // (r / group) * group_stride + (r % group) * row_stride complex elements) into

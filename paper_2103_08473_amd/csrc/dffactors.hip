@@ -130,6 +130,7 @@ struct PlannerState {
   ~PlannerState() {
     set_alloc_registry(nullptr, 0);
     set_gett_workspace(nullptr, 0);
+    set_mod_workspace(nullptr, 0);
   }
 };
 

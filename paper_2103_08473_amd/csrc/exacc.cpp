@@ -62,7 +62,22 @@ struct Plan {
   // the defect-corrected phase also covers the ring (its reference arrays are planned in)
   bool ring_dc = false;
   size_t bytes_peak_no_ring_dc = 0;
+  // residue workspace of the large FP64 products (modgemm.hip), on top of bytes_peak; it is
+  // given up before anything else is refused
+  size_t bytes_mod = 0;
 };
+
+// Residue workspace: the largest products are the rings (o v)^3 and the ladder's, with both
+// operands' residues resident where kModCap allows (products run in chunks otherwise).
+// Nothing where no product is large enough to gain.
+static size_t mod_workspace_bytes(const Plan& p) {
+  const int64_t ov = (int64_t)p.o * p.v;
+  constexpr int64_t kModCap = 8ll << 30, kOut = 512ll << 20;
+  if (!mod_gemm_pays(ov, ov, ov)) return 0;
+  const int64_t ring = 2 * mod_plane_bytes(ov, ov) + std::min(kOut, mod_out_bytes(ov, ov));
+  const int64_t want = ring + (16 << 20);
+  return (size_t)std::min(want, kModCap);
+}
 
 static Plan make_plan(int o, int v, int X, const exacc_ccsd_opts& op) {
   Plan p;
@@ -134,6 +149,12 @@ static Plan make_plan(int o, int v, int X, const exacc_ccsd_opts& op) {
       p.ring_dc = true;
       p.bytes_peak = with;
     }
+  }
+  p.bytes_mod = mod_workspace_bytes(p);
+  if (op.hbm_budget_bytes) {  // what the budget leaves, if that is of use
+    const size_t left = op.hbm_budget_bytes > p.bytes_peak ? op.hbm_budget_bytes - p.bytes_peak : 0;
+    p.bytes_mod = std::min(p.bytes_mod, left / 256 * 256);
+    if (p.bytes_mod < ((size_t)64 << 20)) p.bytes_mod = 0;
   }
   return p;
 }
@@ -243,9 +264,23 @@ struct Handle {
   }
   void* ws = nullptr;  // split-K scratch
   size_t ws_bytes = 0;
+  void* mod_ws = nullptr;  // residue workspace (plan.bytes_mod, or none)
   void use() {
     set_alloc_registry(ranges.data(), (int)ranges.size());
     set_gett_workspace(ws, ws_bytes);
+    set_mod_workspace(mod_ws, mod_ws ? P.bytes_mod : 0);
+  }
+  // Give the residue workspace back (memory is short); recorded graphs address it.
+  bool release_mod() {
+    if (!mod_ws) return false;
+    HIPCHECK(hipStreamSynchronize(s));
+    for (auto& g : gexec)
+      if (g) {
+        (void)hipGraphExecDestroy(g);
+        g = nullptr;
+      }
+    dfree(mod_ws);
+    return true;
   }
   template <typename T>
   void dfree(T*& p) {
@@ -267,7 +302,13 @@ struct Handle {
   double* dalloc(int64_t complex_elems) {
     void* p = nullptr;
     const size_t b = (size_t)std::max<int64_t>(complex_elems, 1) * 16;
-    HIPCHECK(hipMalloc(&p, b));
+    hipError_t e = hipMalloc(&p, b);
+    if (e == hipErrorOutOfMemory && mod_ws) {
+      (void)hipGetLastError();
+      release_mod();
+      e = hipMalloc(&p, b);
+    }
+    HIPCHECK(e);
     allocs.push_back(p);
     ranges.push_back({p, b});
     set_alloc_registry(ranges.data(), (int)ranges.size());
@@ -277,11 +318,15 @@ struct Handle {
 
 // Calls after create that allocate on top of the handle (the Lambda buffers, the triples
 // temporaries) stay within opts.hbm_budget_bytes together with what the handle holds.
-static void check_budget(const Handle& h, size_t extra, const char* what) {
+static void check_budget(Handle& h, size_t extra, const char* what) {
   if (!h.op.hbm_budget_bytes) return;
-  size_t held = 0;
-  for (const AllocRange& r : h.ranges) held += r.bytes;
-  if (held + extra > h.op.hbm_budget_bytes)
+  auto held = [&] {
+    size_t b = 0;
+    for (const AllocRange& r : h.ranges) b += r.bytes;
+    return b;
+  };
+  if (held() + extra > h.op.hbm_budget_bytes) h.release_mod();
+  if (held() + extra > h.op.hbm_budget_bytes)
     raise(EXACC_ERR_NOMEM, std::string(what) + " would exceed hbm_budget_bytes");
 }
 
@@ -1361,13 +1406,14 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   const int64_t vv = (int64_t)v * v, ooo = (int64_t)o * o * o, Pv = h.P.Pv, pvv = Pv * v;
   const int nblk = triples_blocks(v);
   size_t free_b = 0, total_b = 0;
-  HIPCHECK(hipMemGetInfo(&free_b, &total_b));
   const size_t small = (size_t)(2 * ooo + 2 * (int64_t)(o - 2) * nblk + 4) * 16 + (256u << 20);
   const size_t trow = (size_t)pvv * 16;   // packed tile of one occupied i
   const size_t wrow = 2 * trow;           // We and Wm of one triple
   // occupied block size n_red: all of nocc when its tiles fit beside one W row, else the
   // largest with three blocks of tiles resident (or the requested size)
   int red = o;
+  HIPCHECK(hipMemGetInfo(&free_b, &total_b));
+  if (small + (size_t)o * (trow + wrow) > free_b && h.release_mod()) HIPCHECK(hipMemGetInfo(&free_b, &total_b));
   if (small + (size_t)o * trow + wrow > free_b) {
     if (small + 3 * trow + wrow > free_b)
       raise(EXACC_ERR_NOMEM, "triples: three <ab||ie> tile rows and one W row do not fit in free device memory");
@@ -1540,6 +1586,7 @@ static void lambda_alloc(Handle& h) {
                        h.P.Po * h.P.Po + o * o * X + X + (o + v) * (o + v);
   size_t fr = 0, tot = 0;
   HIPCHECK(hipMemGetInfo(&fr, &tot));
+  if ((size_t)need * 16 + (256u << 20) > fr && h.release_mod()) HIPCHECK(hipMemGetInfo(&fr, &tot));
   if ((size_t)need * 16 + (256u << 20) > fr) raise(EXACC_ERR_NOMEM, "Lambda buffers do not fit");
   check_budget(h, (size_t)need * 16, "Lambda buffers");
   // into a local set first: the handle records them only once every allocation succeeded;
@@ -1922,6 +1969,11 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     h->ws_bytes = (size_t)256 << 20;
     h->ws = h->dalloc((int64_t)(h->ws_bytes / 16));
     h->redout = h->dalloc(64);
+    if (P.bytes_mod) {  // optional: only where it leaves room for the whole plan
+      size_t fr = 0, tot = 0;
+      HIPCHECK(hipMemGetInfo(&fr, &tot));
+      if (P.bytes_peak + P.bytes_mod + ((size_t)1 << 30) <= fr) h->mod_ws = h->dalloc((int64_t)(P.bytes_mod / 16));
+    }
     // B: stage raw, check Hermiticity and finiteness on the device, transpose to [p][q][P]
     const double* Braw = B;
     double* Bstage = nullptr;
@@ -2046,6 +2098,7 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     if (h->s) (void)hipStreamSynchronize(h->s);
     set_alloc_registry(nullptr, 0);
     set_gett_workspace(nullptr, 0);
+    set_mod_workspace(nullptr, 0);
     delete h;
     throw;
   }
@@ -2096,7 +2149,8 @@ size_t exacc_ccsd_memory_estimate(int nocc, int nvir, int naux, const exacc_ccsd
   if (nocc < 1 || nvir < 1 || naux < 1) return 0;
   exacc_ccsd_opts d;
   exacc_ccsd_default_opts(&d);
-  return make_plan(nocc, nvir, naux, opts ? *opts : d).bytes_peak;
+  const Plan p = make_plan(nocc, nvir, naux, opts ? *opts : d);
+  return p.bytes_peak + p.bytes_mod;
 }
 
 int exacc_ccsd_create(exacc_ccsd_t* out, int nocc, int nvir, int naux, const double* eps,
@@ -2422,6 +2476,7 @@ int exacc_ccsd_destroy(exacc_ccsd_t hh) {
     if (h->s) (void)hipStreamSynchronize(h->s);
     set_alloc_registry(nullptr, 0);
     set_gett_workspace(nullptr, 0);
+    set_mod_workspace(nullptr, 0);
     delete h;
     return (int)EXACC_OK;
   });

@@ -945,6 +945,8 @@ void launch_gett(const Gett<R>& g, int kind_in, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nbatch <= 0) return;
   if ((int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) > 0x7fffffffLL)
     raise(-1, "contraction too large for one launch");
+  if constexpr (sizeof(R) == sizeof(double))
+    if (mod_gemm(g, s)) return;
   // BF16x3 kinds: only for FP32 operands that are K-contiguous in both A and B; 16-byte
   // loads of two complex values where row strides are even and bases 16-byte aligned
   const bool kcontig = g.k_in == g.K && g.a_ki == 1 && g.b_ki == 1;

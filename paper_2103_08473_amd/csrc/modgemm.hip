@@ -1,0 +1,669 @@
+// FP64 complex products on the INT8 matrix cores.
+//
+// The FP64 matrix rate of gfx950 (78.6 TFLOP/s) bounds the FP64 GETT, which already runs at
+// 0.8 to 0.95 of it on large products.  The INT8 rate is about 64 times higher, so a large
+// product is formed exactly on integers instead, in a residue number system:
+//   * every operand row a_m is scaled by a power of two to the 2-norm range (2^(S-1), 2^S]
+//     and rounded to integers (S = kS bits, more than the 53 of a double);
+//   * modulo a prime (or product of primes) p = 1 mod 4 there is j with j^2 = -1, and a
+//     complex integer x + iy is held as the pair (x + jy, x - jy) mod p: in this form a
+//     complex product is two real products (the quadratic residue number system of
+//     Leung and of Jenkins and Krogmeier), so kNP moduli give 2 kNP independent INT8 planes;
+//   * per plane one INT8 GEMM with INT32 accumulation (exact: |sum| <= K (p/2)^2 < 2^31 for
+//     K <= kMaxK), reduced mod p to one byte per output;
+//   * the Chinese remainder theorem gives the exact integer product back: by the
+//     Cauchy-Schwarz inequality |re|, |im| <= |a_m| |b_n| <= 2^(2S) < M / 2, M the product of
+//     the moduli, so value / M is the fractional part of sum_i r_i w_i / p_i, summed as an
+//     exact high part (multiples of 2^-42) and an FP64 remainder.
+// The only rounding is that of the scaled operands to integers (relative to the row's norm)
+// and of the result to FP64; sums over k are exact, so results do not depend on tiling.
+// A row with a non-finite element gives NaN outputs.
+#include <algorithm>
+#include <cstdint>
+
+#include "common.h"
+
+namespace exacc {
+namespace {
+
+constexpr int kNP = 16;
+constexpr int kPlanes = 2 * kNP;
+constexpr int kS = 58;            // 2^(2 kS) (1 + 2^-40) < M / 2
+constexpr int kMaxK = 131072;     // K (p / 2)^2 < 2^31 with p <= 241
+constexpr int kShortK = 1152;     // K (p / 2)^2 + 128 < 2^24
+constexpr int kNaN = 0x40000000;  // exponent of a row that holds a non-finite element
+
+typedef int i4v __attribute__((ext_vector_type(4)));
+typedef int i16v __attribute__((ext_vector_type(16)));
+typedef double d2v __attribute__((ext_vector_type(2)));
+typedef unsigned __int128 u128;
+
+// Pairwise coprime products of primes = 1 mod 4 (so that -1 has a square root), largest first.
+constexpr int kMods[16] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97};
+
+struct ModTab {
+  int p[kNP];
+  float pf[kNP], ipf[kNP];  // p, 1 / p
+  int w[kNP][4];  // 256^d mod p (d = 0..7, one byte each), then j 256^d mod p
+  double hr[kNP], lr[kNP], hi[kNP], li[kNP];  // CRT weights of re and im, high and low parts
+  double mhi, mlo;                            // M
+};
+
+constexpr int inv_mod(int a, int p) {
+  for (int x = 1; x < p; ++x)
+    if ((int)((int64_t)a * x % p) == 1) return x;
+  return 0;
+}
+
+ModTab make_tab() {
+  ModTab t{};
+  u128 M = 1;
+  for (int i = 0; i < kNP; ++i) M *= (u128)kMods[i];
+  for (int i = 0; i < kNP; ++i) {
+    const int p = kMods[i];
+    int j = 1;
+    while ((j * j + 1) % p) ++j;
+    if (2 * j > p) j = p - j;
+    t.p[i] = p;
+    t.pf[i] = (float)p;
+    t.ipf[i] = 1.0f / (float)p;
+    int w = 1;
+    for (int d = 0; d < 8; ++d, w = w * 256 % p) {
+      auto put = [&](int word, int x) {
+        if (2 * x > p) x -= p;
+        t.w[i][word] |= (int)((unsigned)(x & 255) << (8 * (d & 3)));
+      };
+      put(d / 4, w);
+      put(2 + d / 4, w * j % p);
+    }
+    const int mi = inv_mod((int)((M / (u128)p) % (u128)p), p);
+    // re = (u + v) / 2 and im = (u - v) / (2 j), times the CRT factor of p, in (-p/2, p/2)
+    int cr = (int)((int64_t)mi * inv_mod(2, p) % p), ci = (int)((int64_t)cr * inv_mod(j, p) % p);
+    if (2 * cr > p) cr -= p;
+    if (2 * ci > p) ci -= p;
+    auto parts = [&](int c, double& hpart, double& lpart) {
+      const int64_t num = (int64_t)c << 42;
+      const int64_t h = (num + (num < 0 ? -p / 2 : p / 2)) / p;
+      hpart = (double)h * 0x1p-42;
+      lpart = (double)(num - h * p) / (double)p * 0x1p-42;
+    };
+    parts(cr, t.hr[i], t.lr[i]);
+    parts(ci, t.hi[i], t.li[i]);
+  }
+  t.mhi = (double)M;
+  const u128 mh = (u128)t.mhi;
+  t.mlo = mh > M ? -(double)(mh - M) : (double)(M - mh);
+  return t;
+}
+
+const ModTab& tab() {
+  static const ModTab t = make_tab();
+  return t;
+}
+
+__device__ __forceinline__ int64_t cmap(int x, int in, int64_t so, int64_t si) {
+  const int q = x / in;
+  return (int64_t)q * so + (int64_t)(x - q * in) * si;
+}
+
+// One operand as rows x K of complex FP64 values with composite row and k maps.
+struct Src {
+  const double* p;
+  int row0, rows, K;  // rows [row0, rows) of the operand
+  int r_in, k_in;
+  int64_t r_so, r_si, k_so, k_si;
+  int kfast;  // consecutive k are the nearer neighbours in memory
+  int conj;
+  // planes[row / 32][k / 64][z][(k / 32) % 2][lane][16]: lane l holds row l % 32 and
+  // k 16 (l / 32) .. + 15 of its 32 x 32 block, the fragment order of the 32x32x32 INT8 MFMA;
+  // zero past rows and K.  All planes of 32 rows x 64 k are together, so that splitting writes
+  // whole 64 KiB runs (a plane-major order: 2.3 TB/s at 12363^2, this one: see mod_split_kernel)
+  signed char* planes;
+  int* exps;        // power of two each row was scaled by
+  int rb, kb;       // 32-row and 32-k blocks (kb even)
+};
+
+// Scale exponents: per row the largest |component| and the sum of squares (fixed order).
+// kfast: tpr threads per row; else 32 rows x 32 k phases per workgroup.  Bound by reading
+// the operand once.
+__global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src b, int tpr_a, int tpr_b) {
+  const bool first = (int)blockIdx.x < blocks_a;
+  const Src s = first ? a : b;
+  const int blk = first ? blockIdx.x : blockIdx.x - blocks_a;
+  const int tid = threadIdx.x;
+  __shared__ double ssum[1024], smax[1024];
+  int row, k0, kstep, stride, width;
+  if (s.kfast) {
+    const int tpr = first ? tpr_a : tpr_b;
+    row = s.row0 + blk * (1024 / tpr) + tid / tpr;
+    k0 = tid % tpr;
+    kstep = width = tpr;
+    stride = 1;
+  } else {
+    row = s.row0 + blk * 32 + (tid & 31);
+    k0 = tid >> 5;
+    kstep = width = 32;
+    stride = 32;
+  }
+  double sum = 0.0, mx = 0.0;
+  if (row < s.rows) {
+    const double* p = s.p + 2 * cmap(row, s.r_in, s.r_so, s.r_si);
+    if (s.k_in == s.K) {
+#pragma unroll 4
+      for (int k = k0; k < s.K; k += kstep) {
+        const d2v x = *reinterpret_cast<const d2v*>(p + 2 * (int64_t)k * s.k_si);
+        sum += x.x * x.x + x.y * x.y;
+        mx = fmax(mx, fmax(fabs(x.x), fabs(x.y)));
+      }
+    } else {
+#pragma unroll 4
+      for (int k = k0; k < s.K; k += kstep) {
+        const d2v x = *reinterpret_cast<const d2v*>(p + 2 * cmap(k, s.k_in, s.k_so, s.k_si));
+        sum += x.x * x.x + x.y * x.y;
+        mx = fmax(mx, fmax(fabs(x.x), fabs(x.y)));
+      }
+    }
+  }
+  ssum[tid] = sum;
+  smax[tid] = mx;
+  __syncthreads();
+  for (int w = width / 2; w > 0; w >>= 1) {
+    if (k0 < w) {
+      ssum[tid] += ssum[tid + w * stride];
+      smax[tid] = fmax(smax[tid], smax[tid + w * stride]);
+    }
+    __syncthreads();
+  }
+  if (k0 == 0 && row < s.rows) {
+    sum = ssum[tid];
+    mx = smax[tid];
+    int e = 0;
+    if (sum != sum || mx > 1.7976931348623157e308) {
+      e = kNaN;
+    } else if (mx > 0.0) {
+      int ex;
+      if (sum > 1e-280 && sum < 1e300) {  // norm < 2^(ex / 2)
+        (void)frexp(sum, &ex);
+        ex = (ex + 1) >> 1;
+      } else {  // squares out of range: norm <= max sqrt(2 K)
+        (void)frexp(mx, &ex);
+        ex += (33 - __clz(2 * s.K)) >> 1;
+      }
+      e = kS - ex;
+    }
+    s.exps[row] = e;
+  }
+}
+
+// Residue planes of 32 rows x 64 k per workgroup: the scaled, rounded values are staged in
+// LDS as 8 balanced base-256 digits (re, im), then each wave forms every second modulus of one
+// 32 x 32 block, 16 k per lane: x mod p is a dot product of the digits with 256^d mod p (two
+// 4-byte dot instructions) and one rounding step, 16 instructions per element and modulus
+// against 16 bytes read and 4 written.
+__global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src b, ModTab t) {
+  const bool first = (int)blockIdx.x < blocks_a;
+  const Src s = first ? a : b;
+  const int blk = first ? blockIdx.x : blockIdx.x - blocks_a;
+  const int kg = s.kb / 2;
+  const int rblk = blk / kg, kgrp = blk - rblk * kg;
+  const int tid = threadIdx.x;
+  __shared__ i4v sv[32][65];
+  // all loads first (rows and k past the end are clamped and zeroed below)
+  d2v xs[8];
+  int es[8];
+  const int r0 = s.kfast ? tid >> 6 : tid & 31, kk0 = s.kfast ? tid & 63 : tid >> 5;
+  const int rstep = s.kfast ? 4 : 0, kstep = s.kfast ? 0 : 8;
+  const int rowb = s.row0 + rblk * 32;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int row = min(rowb + r0 + rstep * q, s.rows - 1), k = min(kgrp * 64 + kk0 + kstep * q, s.K - 1);
+    const int64_t ro = s.r_in < s.rows ? cmap(row, s.r_in, s.r_so, s.r_si) : row * s.r_si;
+    const int64_t ko = s.k_in < s.K ? cmap(k, s.k_in, s.k_so, s.k_si) : k * s.k_si;
+    es[q] = s.exps[row];
+    xs[q] = *reinterpret_cast<const d2v*>(s.p + 2 * (ro + ko));
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int r = r0 + rstep * q, kk = kk0 + kstep * q;
+    d2v x = {0.0, 0.0};
+    if (rowb + r < s.rows && kgrp * 64 + kk < s.K && es[q] != kNaN) {
+      x.x = rint(ldexp(xs[q].x, es[q]));
+      x.y = rint(ldexp(s.conj ? -xs[q].y : xs[q].y, es[q]));
+    }
+    // digits: the bytes of x + 0x80..80, each less 128 (flipping the top bit does that)
+    constexpr uint64_t kBias = 0x8080808080808080ull;
+    const uint64_t re = ((uint64_t)(int64_t)x.x + kBias) ^ kBias, im = ((uint64_t)(int64_t)x.y + kBias) ^ kBias;
+    sv[r][kk] = i4v{(int)re, (int)(re >> 32), (int)im, (int)(im >> 32)};
+  }
+  __syncthreads();
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kblk = w & 1, half = w >> 1;
+  i4v x[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) x[q] = sv[lane & 31][kblk * 32 + (lane >> 5) * 16 + q];
+  signed char* out = s.planes + (int64_t)blk * (kPlanes * 2048) + kblk * 1024 + lane * 16;
+  for (int i = half; i < kNP; i += 2) {
+    const float pf = t.pf[i], ipf = t.ipf[i], off = -128.0f * ipf;
+    const int w0 = t.w[i][0], w1 = t.w[i][1], j0 = t.w[i][2], j1 = t.w[i][3];
+    i4v u, v;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      unsigned ub = 0, vb = 0;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const i4v y = x[4 * q + r];
+        // below 8 128 120 each in magnitude, so the sums are exact in FP32; 128 makes the
+        // rounded residues unsigned bytes
+        const int re = __builtin_amdgcn_sdot4(y.y, w1, __builtin_amdgcn_sdot4(y.x, w0, 128, false), false);
+        const int im = __builtin_amdgcn_sdot4(y.w, j1, __builtin_amdgcn_sdot4(y.z, j0, 0, false), false);
+        const float tu = (float)(re + im), tv = (float)(re - im);
+        const float ru = fmaf(-rintf(fmaf(tu, ipf, off)), pf, tu);
+        const float rv = fmaf(-rintf(fmaf(tv, ipf, off)), pf, tv);
+        ub = __builtin_amdgcn_cvt_pk_u8_f32(ru, r, ub);
+        vb = __builtin_amdgcn_cvt_pk_u8_f32(rv, r, vb);
+      }
+      u[q] = (int)(ub ^ 0x80808080u);
+      v[q] = (int)(vb ^ 0x80808080u);
+    }
+    *reinterpret_cast<i4v*>(out + (2 * i) * 2048) = u;
+    *reinterpret_cast<i4v*>(out + (2 * i + 1) * 2048) = v;
+  }
+}
+
+// Workgroup order: each XCD (own L2) takes a contiguous run of logical ids, which walk
+// groups of 4 tiles along m by all of n.
+__device__ __forceinline__ void tile_of(int id, int n, int tiles_m, int tiles_n, int& tm, int& tn) {
+  const int per = (n + 7) / 8, tall = n % 8 == 0 ? 8 : n % 8;
+  const int x = id % 8, l = id / 8;
+  const int t = x < tall ? x * per + l : tall * per + (x - tall) * (per - 1) + l;
+  const int gsz = 4 * tiles_n, g = t / gsz, gm = min(4, tiles_m - g * 4), r = t - g * gsz;
+  tm = g * 4 + r % gm;
+  tn = r / gm;
+}
+
+typedef __attribute__((address_space(3))) void lds_void;
+typedef const __attribute__((address_space(1))) void global_void;
+
+struct PlaneGemm {
+  const signed char *A, *B;
+  signed char* C;              // [mblk][nblk][z][lane][q][r]: row 8 q + 4 (lane / 32) + r, column lane % 32
+  int mb, nb, kb;              // kb even
+  int a_in, a_outer;           // A block of m-block x: (x / a_in) * a_outer + x % a_in
+  int b_in, b_outer;           // likewise B
+  int tiles_m, tiles_n;
+  int p[kNP];
+};
+
+// C[z] = A[z] B[z]^T mod p: WM x WN waves of TM x TN 32 x 32 blocks, stages of 64 k in three
+// LDS buffers filled by direct global-to-LDS loads, two stages ahead.  Operands lie in
+// fragment order, so a block is one contiguous 1 KiB copy and every LDS read is
+// conflict-free.  Bound by the power the INT8 matrix cores draw: 12363^3 x 30 planes of
+// residues run at 2217 TOP/s (256 x 256 tile), the same launch on zeros and ones at 3051;
+// two buffers of 128 k 2126, a 4-wave 256 x 256 tile 2145, 128 x 256 1891, 128 x 128 1719.
+template <int WM, int WN, int TM, int TN, int OCC, bool LONG>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g) {
+  constexpr int KB = 2, S = 3;
+  constexpr int T = 64 * WM * WN, RA = WM * TM, RB = WN * TN;
+  constexpr int NA = RA * KB * 64 / T, NB = RB * KB * 64 / T;
+  static_assert(NA * T == RA * KB * 64 && NB * T == RB * KB * 64, "whole copies per thread");
+  __shared__ i4v sm[S][(RA + RB) * KB * 64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int wm = w % WM, wn = w / WM;
+  const int z = blockIdx.y;
+  int tm, tn;
+  tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.tiles_n, tm, tn);
+  const int m0 = tm * RA, n0 = tn * RB;
+  const i4v* A = reinterpret_cast<const i4v*>(g.A + z * 2048);
+  const i4v* B = reinterpret_cast<const i4v*>(g.B + z * 2048);
+  const int64_t rs = (int64_t)g.kb / 2 * kPlanes * 128;  // 16-byte units per row block
+  const i4v* pa[NA];
+  const i4v* pb[NB];
+  // blocks past mb (nb) are clamped: they feed only outputs that are not stored
+#pragma unroll
+  for (int q = 0; q < NA; ++q) {
+    const int e = tid + T * q, m = min(m0 + e / (KB * 64), g.mb - 1), o = m / g.a_in;
+    pa[q] = A + ((int64_t)o * g.a_outer + (m - o * g.a_in)) * rs + e % (KB * 64);
+  }
+#pragma unroll
+  for (int q = 0; q < NB; ++q) {
+    const int e = tid + T * q, n = min(n0 + e / (KB * 64), g.nb - 1), o = n / g.b_in;
+    pb[q] = B + ((int64_t)o * g.b_outer + (n - o * g.b_in)) * rs + e % (KB * 64);
+  }
+  const int nk = g.kb / KB;
+  // past the last stage the last one is loaded again, into a buffer that is not read any more,
+  // so that the count of loads in flight is the same in every step
+  auto load = [&](int kt, int buf) {
+    const int64_t ko = (int64_t)min(kt, nk - 1) * (kPlanes * 128);
+#pragma unroll
+    for (int q = 0; q < NA; ++q)
+      __builtin_amdgcn_global_load_lds((global_void*)(pa[q] + ko), (lds_void*)&sm[buf][w * 64 + T * q], 16, 0, 0);
+#pragma unroll
+    for (int q = 0; q < NB; ++q)
+      __builtin_amdgcn_global_load_lds((global_void*)(pb[q] + ko),
+                                       (lds_void*)&sm[buf][RA * KB * 64 + w * 64 + T * q], 16, 0, 0);
+  };
+  constexpr int kBias = LONG ? 0 : 128;  // see the reduction below
+  i16v acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = kBias;
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s) load(s, s);
+  int cur = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // this wave's loads of stage kt have landed when at most those of the next S - 2 stages are
+    // outstanding; behind the barrier so have all waves', and all have read stage kt - 1
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NA + NB) * (S - 2)) : "memory");
+    const i4v* sa = &sm[cur][wm * TM * KB * 64 + lane];
+    const i4v* sb = &sm[cur][RA * KB * 64 + wn * TN * KB * 64 + lane];
+    i4v a[KB][TM], b[KB][TN];
+#pragma unroll
+    for (int s = 0; s < KB; ++s) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[s][i] = sa[(i * KB + s) * 64];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[s][j] = sb[(j * KB + s) * 64];
+    }
+    load(kt + S - 1, cur == 0 ? S - 1 : cur - 1);
+#pragma unroll
+    for (int s = 0; s < KB; ++s)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+    cur = cur + 1 == S ? 0 : cur + 1;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the repeated loads, before LDS is given back
+  // Residues in [-p/2, p/2], kept 128 higher as unsigned bytes.  Up to kShortK the sums are
+  // exact in FP32 and one rounded quotient suffices; beyond, a first step on the integers
+  // (quotients below 2^23, off by at most 2) brings them there.
+  const int p = g.p[z >> 1];
+  const float pf = (float)p, ip = 1.0f / pf, off = -128.0f * ip;
+  i4v* C = reinterpret_cast<i4v*>(g.C + z * 1024);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int bm = m0 + wm * TM + i, bn = n0 + wn * TN + j;
+      if (bm >= g.mb || bn >= g.nb) continue;
+      i4v o;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        unsigned pk = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          int x = acc[i][j][4 * q + r];
+          if (LONG) x = 128 + x - __mul24((int)rintf((float)x * ip), p);
+          const float y = (float)x;
+          pk = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(-rintf(fmaf(y, ip, off)), pf, y), r, pk);
+        }
+        o[q] = (int)(pk ^ 0x80808080u);
+      }
+      C[((int64_t)bm * g.nb + bn) * (kPlanes * 64) + lane] = o;
+    }
+}
+
+// (re, im) of the four outputs in one dword of every plane, as the integer product over M.
+struct Frac4 {
+  double re[4], im[4];
+};
+__device__ __forceinline__ Frac4 crt4(const int* c, const ModTab& t) {
+  double hr[4] = {0, 0, 0, 0}, lr[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0}, li[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < kNP; ++i) {
+    const int u = c[(2 * i) * 256], v = c[(2 * i + 1) * 256];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ur = (int)((unsigned)u << (24 - 8 * r)) >> 24, vr = (int)((unsigned)v << (24 - 8 * r)) >> 24;
+      const double a = (double)(ur + vr), b = (double)(ur - vr);
+      hr[r] = fma(a, t.hr[i], hr[r]);  // exact: multiples of 2^-42 below 2^11
+      lr[r] = fma(a, t.lr[i], lr[r]);
+      hi[r] = fma(b, t.hi[i], hi[r]);
+      li[r] = fma(b, t.li[i], li[r]);
+    }
+  }
+  Frac4 f;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    double x = (hr[r] - rint(hr[r])) + lr[r], y = (hi[r] - rint(hi[r])) + li[r];
+    // the fractional part can straddle +-1/2 only above the Cauchy-Schwarz bound
+    f.re[r] = fma(x, t.mhi, x * t.mlo);
+    f.im[r] = fma(y, t.mhi, y * t.mlo);
+  }
+  return f;
+}
+
+// C(m, n) = alpha * product (+ C) for m0 <= m < m0 + 32 mb, n likewise; one dword (4 rows of
+// one column) per lane.  Bound by reading 2 kNP bytes and writing 16 per output.
+__global__ __launch_bounds__(256) void mod_crt_kernel(const int* Cp, int mb, int nb, int m0, int n0,
+                                                      const int* ea, const int* eb, Gett<double> g, ModTab t) {
+  const int64_t tot = (int64_t)mb * nb * 4;
+  const int lane = threadIdx.x & 63;
+  for (int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); u < tot; u += (int64_t)gridDim.x * 4) {
+    // dword 64 q + lane of the tile: column and first of four rows
+    const int q = (int)(u & 3), col = 16 * (q & 1) + (lane >> 2), row = 8 * (lane & 3) + 4 * (q >> 1);
+    const int64_t tile = u >> 2;
+    const int bm = (int)(tile / nb), bn = (int)(tile - (int64_t)bm * nb);
+    const int n = n0 + 32 * bn + col, mr = m0 + 32 * bm + row;
+    const Frac4 f = crt4(Cp + tile * (kPlanes * 256) + q * 64 + lane, t);
+    if (n >= g.N) continue;
+    const int en = eb[n];
+    const int64_t co = cmap(n, g.n_in, g.c_no, g.c_ni);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = mr + r;
+      if (m >= g.M) continue;
+      const int em = ea[m];
+      const bool bad = em == kNaN || en == kNaN;
+      const double xr = bad ? __builtin_nan("") : ldexp(f.re[r], -(em + en));
+      const double xi = bad ? __builtin_nan("") : ldexp(f.im[r], -(em + en));
+      d2v* c = reinterpret_cast<d2v*>(g.C + 2 * (co + cmap(m, g.m_in, g.c_mo, g.c_mi)));
+      d2v y = {g.alpha_re * xr - g.alpha_im * xi, g.alpha_re * xi + g.alpha_im * xr};
+      if (g.accumulate) y += *c;
+      *c = y;
+    }
+  }
+}
+
+inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+int tpr_of(const Src& s) { return s.K >= 4096 ? 256 : 64; }
+int norm_blocks(const Src& s) {
+  return cdiv(std::min(s.rows - s.row0, 32 * s.rb), s.kfast ? 1024 / tpr_of(s) : 32);
+}
+
+// Scale and split one or two operands (b may have rows == 0).
+void split(const Src& a, const Src& b, hipStream_t s) {
+  const int na = norm_blocks(a), nb = b.rows ? norm_blocks(b) : 0;
+  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b));
+  HIPCHECK(hipGetLastError());
+  const int sa = a.rb * (a.kb / 2), sb = b.rows ? b.rb * (b.kb / 2) : 0;
+  hipLaunchKernelGGL(mod_split_kernel, dim3(sa + sb), dim3(256), 0, s, a, sa, b, tab());
+  HIPCHECK(hipGetLastError());
+}
+
+template <int WM, int WN, int TM, int TN, int OCC>
+void launch_planes(PlaneGemm g, hipStream_t s) {
+  g.tiles_m = cdiv(g.mb, WM * TM);
+  g.tiles_n = cdiv(g.nb, WN * TN);
+  const dim3 grid(g.tiles_m * g.tiles_n, kPlanes), block(64 * WM * WN);
+  if (32 * g.kb <= kShortK)
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, false>), grid, block, 0, s, g);
+  else
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, true>), grid, block, 0, s, g);
+  HIPCHECK(hipGetLastError());
+}
+
+// Tile choice: the padded block count of each tile shape over its measured rate (TOP/s at
+// full tiles, see mod_gemm_kernel), in whole rounds of the workgroups the chip holds.
+void gemm_planes(PlaneGemm g, hipStream_t s) {
+  for (int i = 0; i < kNP; ++i) g.p[i] = kMods[i];
+  auto cost = [&](int ra, int rb, int resident, double rate) {
+    const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * kPlanes;
+    const double rounds = wgs >= 8 * resident ? (double)wgs / resident : (double)((wgs + resident - 1) / resident);
+    return rounds * resident * ra * rb / rate;
+  };
+  const double c0 = cost(8, 8, 256, 2200), c1 = cost(4, 8, 512, 1900), c2 = cost(8, 4, 512, 1940),
+               c3 = cost(4, 4, 768, 1720);
+  const double best = std::min(std::min(c0, c1), std::min(c2, c3));
+  if (best == c0)
+    launch_planes<2, 4, 4, 2, 1>(g, s);
+  else if (best == c1)
+    launch_planes<2, 2, 2, 4, 2>(g, s);
+  else if (best == c2)
+    launch_planes<2, 2, 4, 2, 2>(g, s);
+  else
+    launch_planes<2, 2, 2, 2, 3>(g, s);
+}
+
+thread_local char* t_ws = nullptr;
+thread_local size_t t_ws_bytes = 0;
+
+inline size_t up256(size_t b) { return (b + 255) / 256 * 256; }
+inline int kblocks(int K) { return 2 * cdiv(K, 64); }
+
+}  // namespace
+
+// Estimated times (us).  FP64 GETT: 64 x 64 tiles at the 70 TFLOP/s it reaches, whole rounds of
+// tiles when they are few.  Here: four launches, splitting 15 ps per element, reconstruction
+// 15 ps per output, the plane products at 1.7 POP/s on 32 x 32 blocks.  Measured at the line
+// (us, FP64 GETT / this): 513 x 777 x 1025 94 / 89, 317 x 3000 x 951 158 / 126, 2000 x 2000 x
+// 504 271 / 200, 1131^3 217 / 143; under it 700^3 71 / 83, 7875 x 2268 x 126 342 / 480.
+bool mod_gemm_pays(int64_t M, int64_t N, int64_t K) {
+  if (M < 128 || N < 128 || K < 128) return false;
+  auto up = [](int64_t x, int64_t m) { return (double)((x + m - 1) / m * m); };
+  const double t64 = 8.0 * up(M, 64) * up(N, 64) * (double)K / 70e6;
+  const double tm = 25.0 + (double)(M + N) * K * 15e-6 + (double)M * N * 15e-6 +
+                    2.0 * kPlanes * up(M, 32) * up(N, 32) * up(K, 64) / 1.7e9;
+  return tm < 0.85 * t64;
+}
+
+int64_t mod_plane_bytes(int64_t rows, int64_t K) {
+  return kPlanes * ((rows + 31) / 32) * ((K + 63) / 64) * 2048;
+}
+int64_t mod_out_bytes(int64_t M, int64_t N) { return kPlanes * ((M + 31) / 32) * ((N + 31) / 32) * 1024; }
+
+void set_mod_workspace(void* p, size_t bytes) {
+  t_ws = static_cast<char*>(p);
+  t_ws_bytes = p ? bytes : 0;
+}
+
+bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
+  Gett<double> g = g0;
+  if (!t_ws || g.nbatch != 1 || g.K < 1) return false;
+  // columns of C (n) are the nearer neighbours in memory
+  if (g.c_ni != 1 && g.c_mi == 1) {
+    std::swap(g.A, g.B);
+    std::swap(g.M, g.N);
+    std::swap(g.m_in, g.n_in);
+    std::swap(g.a_mo, g.b_no);
+    std::swap(g.a_mi, g.b_ni);
+    std::swap(g.a_ko, g.b_ko);
+    std::swap(g.a_ki, g.b_ki);
+    std::swap(g.c_mo, g.c_no);
+    std::swap(g.c_mi, g.c_ni);
+    std::swap(g.conj_a, g.conj_b);
+  }
+  if (!mod_gemm_pays(g.M, g.N, g.K)) return false;
+
+  const int mb = cdiv(g.M, 32), nb = cdiv(g.N, 32);
+  const int kc_max = std::min(g.K, kMaxK);
+  const size_t rbytes = (size_t)kPlanes * kblocks(kc_max) * 1024, tbytes = (size_t)kPlanes * 1024;
+  const size_t ebytes = up256((size_t)g.M * 4) + up256((size_t)g.N * 4);
+  // A and B blocks resident at a time (ma, nbr) and C blocks per product (mc x nc): C is kept
+  // to what the last-level cache holds, since the reconstruction reads it right away
+  constexpr size_t kC = (size_t)512 << 20;
+  if (ebytes + 64 * tbytes > t_ws_bytes) return false;
+  const size_t room = t_ws_bytes - ebytes;
+  size_t cbytes = std::min(std::min(kC, room / 4), (size_t)mb * nb * tbytes);
+  if (cbytes < (size_t)std::min(mb, 8) * std::min(nb, 8) * tbytes) return false;
+  const size_t rows_room = (room - cbytes) / rbytes;  // row blocks of A and B together
+  int ma = mb, nr = nb;
+  if ((size_t)mb + nb > rows_room) {
+    if (std::min(mb, nb) * 2 <= (int64_t)rows_room) {  // the smaller operand whole
+      if (mb <= nb)
+        nr = (int)(rows_room - mb);
+      else
+        ma = (int)(rows_room - nb);
+    } else {
+      ma = nr = (int)(rows_room / 2);
+    }
+    if (ma < std::min(mb, 16) || nr < std::min(nb, 16)) return false;
+    if (ma < mb) ma = ma / 8 * 8;
+    if (nr < nb) nr = nr / 8 * 8;
+  }
+  const int cb = (int)(cbytes / tbytes);  // C blocks
+  int mc = std::min(ma, std::max(8, cb / std::min(nr, 64) / 8 * 8));
+  int nc = std::min(nr, std::max(1, cb / mc));
+  if (nc < nr && nc >= 8) nc = nc / 8 * 8;
+  char* w = t_ws;
+  int* ea = reinterpret_cast<int*>(w);
+  int* eb = reinterpret_cast<int*>(w + up256((size_t)g.M * 4));
+  w += ebytes;
+  signed char* Cp = reinterpret_cast<signed char*>(w);
+  signed char* Ap = Cp + cbytes / 1024 * 1024;
+  signed char* Bp = Ap + (size_t)ma * rbytes;
+  if (g.K > kMaxK && g.k_in != g.K) return false;  // a k slice needs a shifted base
+  auto src = [&](bool is_a, signed char* planes, int blk0, int rb, int k0, int kc) {
+    Src x{};
+    x.p = (is_a ? g.A : g.B) + 2 * (int64_t)k0 * (is_a ? g.a_ki : g.b_ki);
+    x.row0 = 32 * blk0;
+    x.rows = is_a ? g.M : g.N;
+    x.K = kc;
+    x.r_in = is_a ? g.m_in : g.n_in;
+    x.k_in = g.k_in == g.K ? kc : g.k_in;
+    x.r_so = is_a ? g.a_mo : g.b_no;
+    x.r_si = is_a ? g.a_mi : g.b_ni;
+    x.k_so = is_a ? g.a_ko : g.b_ko;
+    x.k_si = is_a ? g.a_ki : g.b_ki;
+    x.kfast = x.k_si == 1 || x.r_si != 1;
+    x.conj = is_a ? g.conj_a : g.conj_b;
+    x.planes = planes;
+    x.rb = rb;
+    x.kb = kblocks(kc);
+    x.exps = is_a ? ea : eb;
+    return x;
+  };
+  for (int k0 = 0; k0 < g.K; k0 += kMaxK) {
+    const int kc = std::min(g.K - k0, kMaxK);
+    Gett<double> h = g;
+    if (k0 > 0) h.accumulate = 1;
+    for (int m0 = 0; m0 < mb; m0 += ma) {
+      const int am = std::min(ma, mb - m0);
+      for (int n0 = 0; n0 < nb; n0 += nr) {
+        const int bn = std::min(nr, nb - n0);
+        const bool do_a = n0 == 0, do_b = m0 == 0 || nr < nb;
+        const Src a = src(true, Ap, m0, am, k0, kc), b = src(false, Bp, n0, bn, k0, kc);
+        if (do_a)
+          split(a, do_b ? b : Src{}, s);
+        else
+          split(b, Src{}, s);
+        for (int m1 = 0; m1 < am; m1 += mc)
+          for (int n1 = 0; n1 < bn; n1 += nc) {
+            PlaneGemm pg{};
+            pg.mb = std::min(mc, am - m1);
+            pg.nb = std::min(nc, bn - n1);
+            pg.kb = a.kb;
+            pg.A = Ap + (int64_t)m1 * (a.kb / 2) * kPlanes * 2048;
+            pg.B = Bp + (int64_t)n1 * (b.kb / 2) * kPlanes * 2048;
+            pg.C = Cp;
+            pg.a_in = pg.a_outer = pg.mb;
+            pg.b_in = pg.b_outer = pg.nb;
+            gemm_planes(pg, s);
+            const int64_t units = (int64_t)pg.mb * pg.nb;
+            hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>(units, 65535)), dim3(256), 0, s,
+                               reinterpret_cast<const int*>(Cp), pg.mb, pg.nb, 32 * (m0 + m1),
+                               32 * (n0 + n1), ea, eb, h, tab());
+            HIPCHECK(hipGetLastError());
+          }
+      }
+    }
+  }
+  return true;
+}
+
+}  // namespace exacc
