@@ -72,6 +72,29 @@ int64_t mod_plane_bytes(int64_t rows, int64_t K);  // residues of a rows x K ope
 int64_t mod_out_bytes(int64_t M, int64_t N);       // residues of an M x N product
 bool mod_gemm(const Gett<double>& g, hipStream_t s);
 
+// Antisymmetrised ladder tiles from factor rows F[a][c][P] (row a at F + a row_stride complex
+// elements, [c][P] contiguous) whose residues are formed once and kept at the front of the
+// thread's workspace while the object lives.  ok() is false where that does not fit or pay.
+// Per-row FP64 products of small nvir fill the chip badly, so the line lies low: nvir 87,
+// naux 259: builds and antisymmetrise passes 3.4 ms on FP64 tiles, see exacc.cpp.
+constexpr int kModLadderNvir = 64, kModLadderNaux = 128;
+class ModLadder {
+ public:
+  ModLadder(const double* F, int64_t row_stride, int v, int X, hipStream_t s);
+  ~ModLadder();
+  ModLadder(const ModLadder&) = delete;
+  ModLadder& operator=(const ModLadder&) = delete;
+  bool ok() const { return held_ > 0; }
+  // W[(a<b)][(c<d)], a_lo <= a < a_hi, all b, a0 <= c: rows in packed pair order less row0
+  void rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_t ldw, hipStream_t s) const;
+
+ private:
+  int v_ = 0, X_ = 0;
+  int* exps_ = nullptr;
+  signed char* planes_ = nullptr;
+  size_t held_ = 0;
+};
+
 // BF16x3 on pre-split operands (layout in gett.hip): K rounded up to the split
 // width; split `rows` rows of K complex FP32 values (row r at src +
 // (r / group) * group_stride + (r % group) * row_stride complex elements) into

@@ -15,6 +15,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstring>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -42,6 +43,9 @@ void hip_check(hipError_t e, const char* what, const char* file, int line) {
 typedef std::complex<double> zc;
 
 static inline int64_t npair(int64_t m) { return m * (m - 1) / 2; }
+
+// Packed index of the first pair (a, a + 1) over v virtuals.
+static inline int64_t pair_offset(int a, int v) { return (int64_t)a * v - (int64_t)a * (a + 1) / 2; }
 
 // ------------------------------------------------------------------ memory plan
 struct Plan {
@@ -72,11 +76,18 @@ struct Plan {
 // Nothing where no product is large enough to gain.
 static size_t mod_workspace_bytes(const Plan& p) {
   const int64_t ov = (int64_t)p.o * p.v;
-  constexpr int64_t kModCap = 8ll << 30, kOut = 512ll << 20;
-  if (!mod_gemm_pays(ov, ov, ov)) return 0;
-  const int64_t ring = 2 * mod_plane_bytes(ov, ov) + std::min(kOut, mod_out_bytes(ov, ov));
-  const int64_t want = ring + (16 << 20);
-  return (size_t)std::min(want, kModCap);
+  constexpr int64_t kModCap = 10ll << 30, kOut = 512ll << 20;
+  const int64_t v32 = (p.v + 31) / 32 * 32;
+  int64_t want = 0;
+  if (mod_gemm_pays(ov, ov, ov)) want = 2 * mod_plane_bytes(ov, ov) + std::min(kOut, mod_out_bytes(ov, ov));
+  if (p.v > kModLadderNvir && p.X >= kModLadderNaux && p.Po > 0) {
+    // the factor rows, and tiles or the operands of the products with W in turn
+    const int64_t tiles = std::min(kOut, mod_out_bytes(8 * v32, (int64_t)p.v * v32));
+    const int64_t prod = mod_plane_bytes(p.Po, p.Pv) + std::min(2 * kOut, mod_plane_bytes(p.chunk_pairs, p.Pv)) +
+                         std::min(kOut, mod_out_bytes(p.Po, p.chunk_pairs));
+    want = std::max(want, mod_plane_bytes((int64_t)p.v * v32, p.X) + std::max(tiles, prod) + 4 * p.v * v32);
+  }
+  return want ? (size_t)std::min(want + (16 << 20), kModCap) : 0;
 }
 
 static Plan make_plan(int o, int v, int X, const exacc_ccsd_opts& op) {
@@ -561,9 +572,26 @@ static void ladder_apply(Handle& h, const Work<R>& w, const R* F, int64_t row_st
     start += rows;
     rows = 0;
   };
+  std::optional<ModLadder> mod;  // FP64: tiles from residues of the factor rows, formed once
+  if constexpr (sizeof(R) == sizeof(double)) {
+    Scope sc(h, "ladder_build");
+    mod.emplace(F, row_stride, v, X, s);
+  }
   for (int a = 0; a + 1 < v; ++a) {
     const int nb = v - a - 1;
     if (rows + nb > h.P.chunk_pairs) flush();
+    if constexpr (sizeof(R) == sizeof(double)) {
+      if (mod && mod->ok()) {  // as many rows a as the chunk takes
+        Scope sc(h, "ladder_build");
+        int a1 = a;
+        int64_t n = 0;
+        while (a1 + 1 < v && (n == 0 || rows + n + (v - a1 - 1) <= h.P.chunk_pairs)) n += v - a1++ - 1;
+        mod->rows(a, a1, 0, pair_offset(a, v), w.W + 2 * rows * Pv, Pv, s);
+        rows += n;
+        a = a1 - 1;
+        continue;
+      }
+    }
     {
       Scope sc(h, "ladder_build");
       if (bf && use_bvs && h.Bvs) {  // Ta[c][b][d] = sum_P B[(a,c)][P] B[(b,d)][P], b > a, pre-split rows
@@ -611,9 +639,6 @@ static std::vector<LadderChunk> ladder_chunks(int v, int64_t cap, bool tail) {
   return out;
 }
 
-// Packed index of the first pair (a, a + 1) over v virtuals.
-static inline int64_t pair_offset(int a, int v) { return (int64_t)a * v - (int64_t)a * (a + 1) / 2; }
-
 // The pairs (c<d) with c >= a0 are the tail [pair_offset(a0), P_v) of the packed pair
 // range, and the rows (a, b > a), a in [a0, a1), of a chunk are its first `rows` pairs.
 // Per chunk: for each a, Ta[c][b][d] = sum_P F_ac F_bd over c, d >= a0 and b > a
@@ -638,11 +663,23 @@ static void ladder_apply_herm(Handle& h, const Work<R>& w, const R* F, int64_t r
   // W buffer capacity in complex elements of R (the FP32 types alias the FP64 buffer)
   const int64_t cap = h.P.chunk_pairs * Pv * (int64_t)(sizeof(double) / sizeof(R));
   const int64_t ldl = Lp.str[0];
+  std::optional<ModLadder> mod;  // FP64: tiles from residues of the factor rows, formed once
+  if constexpr (sizeof(R) == sizeof(double)) {
+    Scope sc(h, "ladder_build");
+    mod.emplace(F, row_stride, v, X, s);
+  }
   for (const LadderChunk& ch : ladder_chunks(v, cap, tail_t)) {
     const int a0 = ch.a0, wv = v - a0;
     const int64_t Pw = npair(wv), rows = ch.rows, off = pair_offset(a0, v);
     int64_t xoff = 0;
-    for (int a = a0; a < ch.a1; ++a) {
+    const bool on_mod = mod && mod->ok();
+    if constexpr (sizeof(R) == sizeof(double)) {
+      if (on_mod) {
+        Scope sc(h, "ladder_build");
+        mod->rows(a0, ch.a1, a0, off, w.W, Pw, s);
+      }
+    }
+    for (int a = a0; a < ch.a1 && !on_mod; ++a) {
       const int nb = v - a - 1;
       {
         Scope sc(h, "ladder_build");

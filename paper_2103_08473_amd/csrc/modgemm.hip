@@ -112,6 +112,7 @@ struct Src {
   int row0, rows, K;  // rows [row0, rows) of the operand
   int r_in, k_in;
   int64_t r_so, r_si, k_so, k_si;
+  int r_valid;  // if not 0: rows whose inner index is r_valid or more are padding (zero)
   int kfast;  // consecutive k are the nearer neighbours in memory
   int conj;
   // planes[row / 32][k / 64][z][(k / 32) % 2][lane][16]: lane l holds row l % 32 and
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src
     stride = 32;
   }
   double sum = 0.0, mx = 0.0;
-  if (row < s.rows) {
+  if (row < s.rows && (s.r_valid == 0 || row % s.r_in < s.r_valid)) {
     const double* p = s.p + 2 * cmap(row, s.r_in, s.r_so, s.r_si);
     if (s.k_in == s.K) {
 #pragma unroll 4
@@ -216,7 +217,12 @@ __global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src
   const int rowb = s.row0 + rblk * 32;
 #pragma unroll
   for (int q = 0; q < 8; ++q) {
-    const int row = min(rowb + r0 + rstep * q, s.rows - 1), k = min(kgrp * 64 + kk0 + kstep * q, s.K - 1);
+    int row = min(rowb + r0 + rstep * q, s.rows - 1);
+    if (s.r_valid) {
+      const int in = row % s.r_in;
+      row -= max(0, in - s.r_valid + 1);
+    }
+    const int k = min(kgrp * 64 + kk0 + kstep * q, s.K - 1);
     const int64_t ro = s.r_in < s.rows ? cmap(row, s.r_in, s.r_so, s.r_si) : row * s.r_si;
     const int64_t ko = s.k_in < s.K ? cmap(k, s.k_in, s.k_so, s.k_si) : k * s.k_si;
     es[q] = s.exps[row];
@@ -226,7 +232,8 @@ __global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src
   for (int q = 0; q < 8; ++q) {
     const int r = r0 + rstep * q, kk = kk0 + kstep * q;
     d2v x = {0.0, 0.0};
-    if (rowb + r < s.rows && kgrp * 64 + kk < s.K && es[q] != kNaN) {
+    const bool pad = s.r_valid && (rowb + r) % s.r_in >= s.r_valid;
+    if (rowb + r < s.rows && kgrp * 64 + kk < s.K && es[q] != kNaN && !pad) {
       x.x = rint(ldexp(xs[q].x, es[q]));
       x.y = rint(ldexp(s.conj ? -xs[q].y : xs[q].y, es[q]));
     }
@@ -469,6 +476,69 @@ __global__ __launch_bounds__(256) void mod_crt_kernel(const int* Cp, int mb, int
   }
 }
 
+// W[(a, b)][(c < d)] = T[a][c][b][d] - T[a][d][b][c] for the pairs of 32-blocks p <= q of c and d
+// (grid x), b (y) and a (z) of one product of the residues of rows (a, c) and (b, d); T is
+// reconstructed as in mod_crt_kernel, one half transposed through LDS, and never stored:
+// 64 bytes read and 16 written per pair, against 96 for a stored T and a pass over it.
+struct LadderTiles {
+  const int* C;
+  const int* exps;  // of row (a, c): a 32 vb + c
+  int v, vb, wvb, blk0;  // blocks of c: blk0 .. vb - 1, wvb of them
+  int a0;                // pairs c < d from a0 on, packed
+  int a_first, b_first, nbn;
+  int64_t row0;          // packed pair index of W's first row
+  double* W;
+  int64_t ldw;
+};
+__global__ __launch_bounds__(256) void mod_ladder_antisym_kernel(LadderTiles g, ModTab t) {
+  const int a = g.a_first + blockIdx.z, b = g.b_first + blockIdx.y;
+  if (b <= a) return;
+  int p = 0, q = blockIdx.x;
+  while (q >= g.wvb - p) q -= g.wvb - p++;
+  q += p;
+  __shared__ d2v sy[32][33];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int col = 16 * (w & 1) + (lane >> 2), row = 8 * (lane & 3) + 4 * (w >> 1);
+  const int64_t ld = (int64_t)g.nbn * g.wvb;
+  const int bp = 32 * (g.blk0 + p), bq = 32 * (g.blk0 + q);
+  auto value = [&](int rb, int cb, d2v* y) {  // T[a][32 rb + row + r][b][32 cb + col]
+    const int64_t tile =
+        ((int64_t)blockIdx.z * g.wvb + rb) * ld + (int64_t)blockIdx.y * g.wvb + cb;
+    const Frac4 f = crt4(g.C + tile * (kPlanes * 256) + w * 64 + lane, t);
+    const int r0 = 32 * (g.blk0 + rb) + row, c0 = 32 * (g.blk0 + cb) + col;
+    const int en = c0 < g.v ? g.exps[b * 32 * g.vb + c0] : 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int em = r0 + r < g.v ? g.exps[a * 32 * g.vb + r0 + r] : 0;
+      const bool bad = em == kNaN || en == kNaN;
+      y[r].x = bad ? __builtin_nan("") : ldexp(f.re[r], -(em + en));
+      y[r].y = bad ? __builtin_nan("") : ldexp(f.im[r], -(em + en));
+    }
+  };
+  d2v x[4], y[4];
+  value(p, q, x);
+  if (p == q) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) y[r] = x[r];
+  } else {
+    value(q, p, y);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) sy[col][row + r] = y[r];
+  __syncthreads();
+  const int d = bq + col, wv = g.v - g.a0;
+  const int64_t xrow = (int64_t)a * g.v - (int64_t)a * (a + 1) / 2 + b - a - 1 - g.row0;
+  double* out = g.W + 2 * xrow * g.ldw;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int c = bp + row + r;
+    if (c < g.a0 || c >= d || d >= g.v) continue;
+    const int cc = c - g.a0;
+    const int64_t pos = (int64_t)cc * wv - (int64_t)cc * (cc + 1) / 2 + d - c - 1;
+    *reinterpret_cast<d2v*>(out + 2 * pos) = x[r] - sy[row + r][col];
+  }
+}
+
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 int tpr_of(const Src& s) { return s.K >= 4096 ? 256 : 64; }
@@ -664,6 +734,77 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     }
   }
   return true;
+}
+
+// ---------------------------------------------------------------- particle ladder
+ModLadder::ModLadder(const double* F, int64_t row_stride, int v, int X, hipStream_t s) {
+  const int vb = cdiv(v, 32), kb = kblocks(X);
+  const size_t eb = up256((size_t)v * vb * 32 * 4), pb = (size_t)mod_plane_bytes((int64_t)v * vb * 32, X);
+  const size_t least = (size_t)vb * vb * std::min(v, 8) * kPlanes * 1024;  // tiles of one a and 8 b
+  if (!t_ws || v <= kModLadderNvir || X < kModLadderNaux || (int64_t)v * vb * 32 > 0x7fffffffLL ||
+      eb + pb + least > t_ws_bytes)
+    return;
+  v_ = v;
+  X_ = X;
+  exps_ = reinterpret_cast<int*>(t_ws);
+  planes_ = reinterpret_cast<signed char*>(t_ws + eb);
+  held_ = eb + pb;
+  Src a{};
+  a.p = F;
+  a.rows = v * vb * 32;
+  a.K = X;
+  a.r_in = vb * 32;
+  a.r_valid = v;
+  a.k_in = X;
+  a.r_so = row_stride;
+  a.r_si = X;
+  a.k_so = a.k_si = 1;
+  a.kfast = 1;
+  a.planes = planes_;
+  a.exps = exps_;
+  a.rb = v * vb;
+  a.kb = kb;
+  split(a, Src{}, s);
+  t_ws += held_;  // the rest serves this ladder's tiles and, in turn, other products
+  t_ws_bytes -= held_;
+}
+
+ModLadder::~ModLadder() {
+  t_ws -= held_;
+  t_ws_bytes += held_;
+}
+
+void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_t ldw, hipStream_t s) const {
+  const int v = v_, vb = cdiv(v, 32), blk0 = a0 / 32, wvb = vb - blk0;
+  const int64_t run = (int64_t)(kblocks(X_) / 2) * kPlanes * 2048;  // bytes per row block
+  // several rows a per product: 24 blocks or more along m keep the tile padding small
+  const int ga_max = wvb >= 16 ? 2 : wvb >= 6 ? 4 : 8;
+  constexpr size_t kC = (size_t)512 << 20;
+  const int64_t cblocks = (int64_t)(std::min(kC, t_ws_bytes) / (kPlanes * 1024));
+  for (int a = a_lo; a < a_hi; a += ga_max) {
+    int ga = std::min(ga_max, a_hi - a);
+    while (ga > 1 && (int64_t)ga * wvb * wvb > cblocks) --ga;
+    for (int a1 = a; a1 < std::min(a + ga_max, a_hi); a1 += ga) {
+      const int g1 = std::min(ga, std::min(a + ga_max, a_hi) - a1);
+      const int nbmax = (int)std::min<int64_t>(v, std::max<int64_t>(1, cblocks / ((int64_t)g1 * wvb * wvb)));
+      for (int b = a1 + 1; b < v; b += nbmax) {
+        const int nbn = std::min(nbmax, v - b);
+        PlaneGemm pg{};
+        pg.A = planes_ + ((int64_t)a1 * vb + blk0) * run;
+        pg.B = planes_ + ((int64_t)b * vb + blk0) * run;
+        pg.C = reinterpret_cast<signed char*>(t_ws);
+        pg.mb = g1 * wvb;
+        pg.nb = nbn * wvb;
+        pg.kb = kblocks(X_);
+        pg.a_in = pg.b_in = wvb;
+        pg.a_outer = pg.b_outer = vb;
+        gemm_planes(pg, s);
+        LadderTiles lt{reinterpret_cast<const int*>(t_ws), exps_, v, vb, wvb, blk0, a0, a1, b, nbn, row0, W, ldw};
+        hipLaunchKernelGGL(mod_ladder_antisym_kernel, dim3(wvb * (wvb + 1) / 2, nbn, g1), dim3(256), 0, s, lt, tab());
+        HIPCHECK(hipGetLastError());
+      }
+    }
+  }
 }
 
 }  // namespace exacc

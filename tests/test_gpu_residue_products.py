@@ -25,9 +25,11 @@ def residual(o, v, X, budget, t, **opts):
     return np.asarray(s1), np.asarray(s2)
 
 
-# odd sizes off every tile, whole tiles (o v = 1280 = 5 x 256), one past a tile (o v = 1281)
+# ladder tiles: the smallest nvir that takes them, whole blocks, several chunks of virtual rows
+# (first rows inside and at the edge of a block); products: odd sizes off every tile, whole tiles (o v = 1280 = 5 x 256), one past a tile (o v = 1281)
 # and a workspace so small that both operands are split in chunks (0: all it wants)
 @pytest.mark.parametrize("o,v,X,room,opts", [
+    (4, 65, 200, 0, {}), (5, 97, 131, 0, {"ladder_chunk_pairs": 700}), (5, 128, 128, 0, {"ladder_chunk_pairs": 3600}),
     (13, 87, 259, 0, {}), (13, 87, 259, 64, {}), (20, 64, 192, 0, {"ladder_group_nvir": 0}),
     (21, 61, 180, 0, {}), (30, 101, 420, 0, {"cc2": 1}), (24, 90, 270, 120, {"doubles_only": 1})])
 def test_residual_with_and_without_residues(lib, o, v, X, room, opts):
@@ -49,6 +51,25 @@ def test_residual_with_and_without_residues(lib, o, v, X, room, opts):
         scale = max(np.abs(a).max(), 1e-300)
         print("max |d| / max %.2e (tolerance %.2e)" % (np.abs(a - b).max() / scale, tol), flush=True)
         assert np.abs(a - b).max() <= tol * scale
+
+
+def test_lambda_with_and_without_residues(lib):
+    """The Lambda ladder's T1-dressed factors are not Hermitian: full build, two W chunks."""
+    from paper_2103_08473_amd import exacc
+    o, v, X = 6, 75, 150
+    eps, B = make_system(o, v, X, seed=4)
+    t, l = amplitudes(o, v, seed=5), amplitudes(o, v, seed=6)
+    base = exacc.memory_estimate(o, v, X, hbm_budget_bytes=1, ladder_chunk_pairs=1500)
+    out = []
+    for mod in (False, True):
+        with exacc.CCSD(eps, B, o, hbm_budget_bytes=0 if mod else base + (63 << 20), ladder_chunk_pairs=1500) as cc:
+            cc.set_amplitudes(*t)
+            cc.set_lambda(*l)
+            out.append([np.asarray(x) for x in cc.lambda_residual()])
+    tol = v * (v - 1) // 2 * 2.0 ** -53
+    assert any((a != b).any() for a, b in zip(*out))  # another route was taken
+    for a, b in zip(*out):
+        assert np.abs(a - b).max() <= tol * np.abs(a).max()
 
 
 def test_non_finite_amplitudes_stay_non_finite(lib):
