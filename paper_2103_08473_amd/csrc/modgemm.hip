@@ -304,9 +304,11 @@ struct PlaneGemm {
 // C[z] = A[z] B[z]^T mod p: WM x WN waves of TM x TN 32 x 32 blocks, stages of 64 k in three
 // LDS buffers filled by direct global-to-LDS loads, two stages ahead.  Operands lie in
 // fragment order, so a block is one contiguous 1 KiB copy and every LDS read is
-// conflict-free.  Bound by the power the INT8 matrix cores draw: 12363^3 x 30 planes of
-// residues run at 2217 TOP/s (256 x 256 tile), the same launch on zeros and ones at 3051;
-// two buffers of 128 k 2126, a 4-wave 256 x 256 tile 2145, 128 x 256 1891, 128 x 128 1719.
+// conflict-free.  The grid is what the chip holds; a workgroup walks tiles grid apart and
+// loads the next tile's first stages before it reduces and stores this one's outputs.
+// Bound by the power the INT8 matrix cores draw: 4032^3 x 32 planes 2380 TOP/s, the same
+// launch on zeros and ones about 3000; one tile per workgroup 2250 there and 1426 instead of
+// 1895 at 1268 x 25000 x 951, where filling the pipeline is a larger part.
 template <int WM, int WN, int TM, int TN, int OCC, bool LONG>
 __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g) {
   constexpr int KB = 2, S = 3;
@@ -316,31 +318,34 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
   __shared__ i4v sm[S][(RA + RB) * KB * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w % WM, wn = w / WM;
-  const int z = blockIdx.y;
-  int tm, tn;
-  tile_of(blockIdx.x, gridDim.x, g.tiles_m, g.tiles_n, tm, tn);
-  const int m0 = tm * RA, n0 = tn * RB;
-  const i4v* A = reinterpret_cast<const i4v*>(g.A + z * 2048);
-  const i4v* B = reinterpret_cast<const i4v*>(g.B + z * 2048);
+  const int tiles = g.tiles_m * g.tiles_n, total = tiles * kPlanes;
   const int64_t rs = (int64_t)g.kb / 2 * kPlanes * 128;  // 16-byte units per row block
+  const int nk = g.kb / KB;
   const i4v* pa[NA];
   const i4v* pb[NB];
+  int m0, n0, z;
   // blocks past mb (nb) are clamped: they feed only outputs that are not stored
+  auto start = [&](int job) {
+    z = job / tiles;
+    int tm, tn;
+    tile_of(job - z * tiles, tiles, g.tiles_m, g.tiles_n, tm, tn);
+    m0 = tm * RA;
+    n0 = tn * RB;
+    const i4v* A = reinterpret_cast<const i4v*>(g.A + z * 2048);
+    const i4v* B = reinterpret_cast<const i4v*>(g.B + z * 2048);
 #pragma unroll
-  for (int q = 0; q < NA; ++q) {
-    const int e = tid + T * q, m = min(m0 + e / (KB * 64), g.mb - 1), o = m / g.a_in;
-    pa[q] = A + ((int64_t)o * g.a_outer + (m - o * g.a_in)) * rs + e % (KB * 64);
-  }
+    for (int q = 0; q < NA; ++q) {
+      const int e = tid + T * q, m = min(m0 + e / (KB * 64), g.mb - 1), o = m / g.a_in;
+      pa[q] = A + ((int64_t)o * g.a_outer + (m - o * g.a_in)) * rs + e % (KB * 64);
+    }
 #pragma unroll
-  for (int q = 0; q < NB; ++q) {
-    const int e = tid + T * q, n = min(n0 + e / (KB * 64), g.nb - 1), o = n / g.b_in;
-    pb[q] = B + ((int64_t)o * g.b_outer + (n - o * g.b_in)) * rs + e % (KB * 64);
-  }
-  const int nk = g.kb / KB;
-  // past the last stage the last one is loaded again, into a buffer that is not read any more,
-  // so that the count of loads in flight is the same in every step
+    for (int q = 0; q < NB; ++q) {
+      const int e = tid + T * q, n = min(n0 + e / (KB * 64), g.nb - 1), o = n / g.b_in;
+      pb[q] = B + ((int64_t)o * g.b_outer + (n - o * g.b_in)) * rs + e % (KB * 64);
+    }
+  };
   auto load = [&](int kt, int buf) {
-    const int64_t ko = (int64_t)min(kt, nk - 1) * (kPlanes * 128);
+    const int64_t ko = (int64_t)kt * (kPlanes * 128);
 #pragma unroll
     for (int q = 0; q < NA; ++q)
       __builtin_amdgcn_global_load_lds((global_void*)(pa[q] + ko), (lds_void*)&sm[buf][w * 64 + T * q], 16, 0, 0);
@@ -349,69 +354,90 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
       __builtin_amdgcn_global_load_lds((global_void*)(pb[q] + ko),
                                        (lds_void*)&sm[buf][RA * KB * 64 + w * 64 + T * q], 16, 0, 0);
   };
+  int job = blockIdx.x;
+  if (job >= total) return;
+  start(job);
+#pragma unroll
+  for (int s = 0; s < S - 1; ++s) load(min(s, nk - 1), s);
   constexpr int kBias = LONG ? 0 : 128;  // see the reduction below
-  i16v acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = kBias;
-#pragma unroll
-  for (int s = 0; s < S - 1; ++s) load(s, s);
   int cur = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    // this wave's loads of stage kt have landed when at most those of the next S - 2 stages are
-    // outstanding; behind the barrier so have all waves', and all have read stage kt - 1
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NA + NB) * (S - 2)) : "memory");
-    const i4v* sa = &sm[cur][wm * TM * KB * 64 + lane];
-    const i4v* sb = &sm[cur][RA * KB * 64 + wn * TN * KB * 64 + lane];
-    i4v a[KB][TM], b[KB][TN];
+  while (true) {
+    const int cm0 = m0, cn0 = n0, cz = z, next = job + (int)gridDim.x;
+    i16v acc[TM][TN];
 #pragma unroll
-    for (int s = 0; s < KB; ++s) {
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[s][i] = sa[(i * KB + s) * 64];
+      for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b[s][j] = sb[(j * KB + s) * 64];
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = kBias;
+    for (int kt = 0; kt < nk; ++kt) {
+      // this wave's loads of stage kt have landed when at most those of the next S - 2 stages
+      // are outstanding (stores only make the wait longer); behind the barrier so have all
+      // waves', and all have read stage kt - 1, whose buffer is loaded next
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((NA + NB) * (S - 2)) : "memory");
+      const i4v* sa = &sm[cur][wm * TM * KB * 64 + lane];
+      const i4v* sb = &sm[cur][RA * KB * 64 + wn * TN * KB * 64 + lane];
+      i4v a[KB][TM], b[KB][TN];
+#pragma unroll
+      for (int s = 0; s < KB; ++s) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[s][i] = sa[(i * KB + s) * 64];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[s][j] = sb[(j * KB + s) * 64];
+      }
+      // past the last tile the last stage is loaded again, into a buffer that is not read any
+      // more, so that the count of loads in flight is the same in every step
+      int kn = kt + S - 1;
+      if (kn >= nk) {
+        if (next < total) {
+          kn -= nk;
+          if (kn == 0) start(next);
+          kn = min(kn, nk - 1);
+        } else {
+          kn = nk - 1;
+        }
+      }
+      load(kn, cur == 0 ? S - 1 : cur - 1);
+#pragma unroll
+      for (int s = 0; s < KB; ++s)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
+      cur = cur + 1 == S ? 0 : cur + 1;
     }
-    load(kt + S - 1, cur == 0 ? S - 1 : cur - 1);
+    // Residues in [-p/2, p/2], kept 128 higher as unsigned bytes.  Up to kShortK the sums are
+    // exact in FP32 and one rounded quotient suffices; beyond, a first step on the integers
+    // (quotients below 2^23, off by at most 2) brings them there.
+    const int p = g.p[cz >> 1];
+    const float pf = (float)p, ip = 1.0f / pf, off = -128.0f * ip;
+    i4v* C = reinterpret_cast<i4v*>(g.C + cz * 1024);
 #pragma unroll
-    for (int s = 0; s < KB; ++s)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int j = 0; j < TN; ++j) {
+        const int bm = cm0 + wm * TM + i, bn = cn0 + wn * TN + j;
+        if (bm >= g.mb || bn >= g.nb) continue;
+        i4v o;
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
-    cur = cur + 1 == S ? 0 : cur + 1;
+        for (int q = 0; q < 4; ++q) {
+          unsigned pk = 0;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            int x = acc[i][j][4 * q + r];
+            if (LONG) x = 128 + x - __mul24((int)rintf((float)x * ip), p);
+            const float y = (float)x;
+            pk = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(-rintf(fmaf(y, ip, off)), pf, y), r, pk);
+          }
+          o[q] = (int)(pk ^ 0x80808080u);
+        }
+        C[((int64_t)bm * g.nb + bn) * (kPlanes * 64) + lane] = o;
+      }
+    job = next;
+    if (job >= total) break;
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the repeated loads, before LDS is given back
-  // Residues in [-p/2, p/2], kept 128 higher as unsigned bytes.  Up to kShortK the sums are
-  // exact in FP32 and one rounded quotient suffices; beyond, a first step on the integers
-  // (quotients below 2^23, off by at most 2) brings them there.
-  const int p = g.p[z >> 1];
-  const float pf = (float)p, ip = 1.0f / pf, off = -128.0f * ip;
-  i4v* C = reinterpret_cast<i4v*>(g.C + z * 1024);
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int bm = m0 + wm * TM + i, bn = n0 + wn * TN + j;
-      if (bm >= g.mb || bn >= g.nb) continue;
-      i4v o;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        unsigned pk = 0;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          int x = acc[i][j][4 * q + r];
-          if (LONG) x = 128 + x - __mul24((int)rintf((float)x * ip), p);
-          const float y = (float)x;
-          pk = __builtin_amdgcn_cvt_pk_u8_f32(fmaf(-rintf(fmaf(y, ip, off)), pf, y), r, pk);
-        }
-        o[q] = (int)(pk ^ 0x80808080u);
-      }
-      C[((int64_t)bm * g.nb + bn) * (kPlanes * 64) + lane] = o;
-    }
 }
 
 // (re, im) of the four outputs in one dword of every plane, as the integer product over M.
@@ -556,11 +582,14 @@ void split(const Src& a, const Src& b, hipStream_t s) {
   HIPCHECK(hipGetLastError());
 }
 
-template <int WM, int WN, int TM, int TN, int OCC>
+// RES: workgroups one CU holds (of 160 KiB LDS).  256 CUs.
+template <int WM, int WN, int TM, int TN, int OCC, int RES>
 void launch_planes(PlaneGemm g, hipStream_t s) {
   g.tiles_m = cdiv(g.mb, WM * TM);
   g.tiles_n = cdiv(g.nb, WN * TN);
-  const dim3 grid(g.tiles_m * g.tiles_n, kPlanes), block(64 * WM * WN);
+  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * kPlanes;
+  if (jobs > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
+  const dim3 grid((unsigned)std::min<int64_t>(jobs, 256 * RES)), block(64 * WM * WN);
   if (32 * g.kb <= kShortK)
     hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, false>), grid, block, 0, s, g);
   else
@@ -571,6 +600,7 @@ void launch_planes(PlaneGemm g, hipStream_t s) {
 // Tile choice: the padded block count of each tile shape over its measured rate (TOP/s at
 // full tiles, see mod_gemm_kernel), in whole rounds of the workgroups the chip holds.
 void gemm_planes(PlaneGemm g, hipStream_t s) {
+  if (g.kb < 4) raise(-1, "residue product: K too short for its pipeline");  // two stages at least
   for (int i = 0; i < kNP; ++i) g.p[i] = kMods[i];
   auto cost = [&](int ra, int rb, int resident, double rate) {
     const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * kPlanes;
@@ -581,13 +611,13 @@ void gemm_planes(PlaneGemm g, hipStream_t s) {
                c3 = cost(4, 4, 768, 1720);
   const double best = std::min(std::min(c0, c1), std::min(c2, c3));
   if (best == c0)
-    launch_planes<2, 4, 4, 2, 1>(g, s);
+    launch_planes<2, 4, 4, 2, 1, 1>(g, s);
   else if (best == c1)
-    launch_planes<2, 2, 2, 4, 2>(g, s);
+    launch_planes<2, 2, 2, 4, 2, 2>(g, s);
   else if (best == c2)
-    launch_planes<2, 2, 4, 2, 2>(g, s);
+    launch_planes<2, 2, 4, 2, 2, 2>(g, s);
   else
-    launch_planes<2, 2, 2, 2, 3>(g, s);
+    launch_planes<2, 2, 2, 2, 3, 3>(g, s);
 }
 
 thread_local char* t_ws = nullptr;
@@ -624,7 +654,21 @@ void set_mod_workspace(void* p, size_t bytes) {
 
 bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
   Gett<double> g = g0;
-  if (!t_ws || g.nbatch != 1 || g.K < 1) return false;
+  if (!t_ws || g.K < 1 || !mod_gemm_pays(g.M, g.N, g.K)) return false;
+  if (g.nbatch > 1) {
+    for (int q = 0; q < g0.nbatch; ++q) {
+      Gett<double> h = g0;
+      h.nbatch = 1;
+      h.A = g0.A + 2 * (int64_t)q * g0.a_b;
+      h.B = g0.B + 2 * (int64_t)q * g0.b_b;
+      h.C = g0.C + 2 * (int64_t)q * g0.c_b;
+      if (!mod_gemm(h, s)) {  // the first refuses or none does: sizes and workspace are the same
+        if (q > 0) raise(-1, "residue products of one batch took different routes");
+        return false;
+      }
+    }
+    return true;
+  }
   // columns of C (n) are the nearer neighbours in memory
   if (g.c_ni != 1 && g.c_mi == 1) {
     std::swap(g.A, g.B);
@@ -638,8 +682,6 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     std::swap(g.c_mi, g.c_ni);
     std::swap(g.conj_a, g.conj_b);
   }
-  if (!mod_gemm_pays(g.M, g.N, g.K)) return false;
-
   const int mb = cdiv(g.M, 32), nb = cdiv(g.N, 32);
   const int kc_max = std::min(g.K, kMaxK);
   const size_t rbytes = (size_t)kPlanes * kblocks(kc_max) * 1024, tbytes = (size_t)kPlanes * 1024;
