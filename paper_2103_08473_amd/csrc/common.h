@@ -32,6 +32,12 @@ void hip_check(hipError_t e, const char* what, const char* file, int line);
 // which covers any contraction whose index groups merge into two strided
 // levels per operand (the host planner in einsum.cpp finds the split).
 // ---------------------------------------------------------------------------
+struct FastDiv {
+  int d;
+  unsigned mul;  // 0: d = 1
+  int shift;
+};
+
 template <typename R>
 struct Gett {
   int M, N, K, nbatch;
@@ -46,6 +52,7 @@ struct Gett {
   R* C;
   int kslice;  // split-K: workgroup z covers k in [z*kslice, min(K, (z+1)*kslice))
   R* ws;       // split-K partial sums [z][batch][m][n] (unscaled)
+  FastDiv m_div, n_div, k_div;  // of m_in, n_in, k_in (filled at launch)
 };
 
 // Scratch the calling thread's GETT launches may use for split-K partials.

@@ -14,6 +14,8 @@
 // addresses come from the composite (outer, inner) index maps of Gett<R>, so
 // permuted and strided tensors are contracted in place without transposes in
 // HBM.
+#include <algorithm>
+
 #include "common.h"
 
 namespace exacc {
@@ -49,6 +51,36 @@ __device__ __forceinline__ int64_t cmap(int x, int in, int64_t so, int64_t si) {
   const int r = x - q * in;
   return (int64_t)q * so + (int64_t)r * si;
 }
+
+// The same with the division by the host's multiplier (FastDiv), x < 2^31.
+__device__ __forceinline__ int64_t cmap(int x, const FastDiv& d, int64_t so, int64_t si) {
+  const int q = d.mul ? (int)(__umulhi((unsigned)x, d.mul) >> d.shift) : x;
+  const int r = x - q * d.d;
+  return (int64_t)q * so + (int64_t)r * si;
+}
+
+// Offset of a k index that moves by a fixed step: one addition, and one more where the inner
+// index wraps, instead of a division and two 64-bit products per load.
+struct KWalk {
+  int r;        // inner index
+  int64_t off;  // elements
+};
+struct KStep {
+  int in, r;            // inner extent; inner index step
+  int64_t step, wrap;   // offset of the step; correction when the inner index wraps
+  __device__ KStep(int n, int in_, int64_t so, int64_t si) : in(in_) {
+    const int q = n >= in_ ? n / in_ : 0;
+    r = n - q * in_;
+    step = (int64_t)q * so + (int64_t)r * si;
+    wrap = so - (int64_t)in_ * si;
+  }
+  __device__ __forceinline__ void advance(KWalk& k) const {
+    k.r += r;
+    const bool over = k.r >= in;
+    k.r -= over ? in : 0;
+    k.off += step + (over ? wrap : 0);
+  }
+};
 
 template <typename R>
 __device__ __forceinline__ C2<R> ldc(const R* p, int64_t off) {
@@ -104,12 +136,12 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
 #pragma unroll
     for (int q = 0; q < NA; ++q) {
       const int m = min(m0 + tid / BK + RS * q, g.M - 1);
-      a_off[q] = cmap(m, g.m_in, g.a_mo, g.a_mi);
+      a_off[q] = cmap(m, g.m_div, g.a_mo, g.a_mi);
     }
   } else {
     a_mm = tid % BM;
     a_kq = tid / BM;
-    a_off[0] = cmap(min(m0 + a_mm, g.M - 1), g.m_in, g.a_mo, g.a_mi);
+    a_off[0] = cmap(min(m0 + a_mm, g.M - 1), g.m_div, g.a_mo, g.a_mi);
   }
   int64_t b_off[BKF ? NB : 1];
   int b_kk = 0, b_nn = 0, b_kq = 0;
@@ -118,12 +150,22 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
 #pragma unroll
     for (int q = 0; q < NB; ++q) {
       const int n = min(n0 + tid / BK + RS * q, g.N - 1);
-      b_off[q] = cmap(n, g.n_in, g.b_no, g.b_ni);
+      b_off[q] = cmap(n, g.n_div, g.b_no, g.b_ni);
     }
   } else {
     b_nn = tid % BN;
     b_kq = tid / BN;
-    b_off[0] = cmap(min(n0 + b_nn, g.N - 1), g.n_in, g.b_no, g.b_ni);
+    b_off[0] = cmap(min(n0 + b_nn, g.N - 1), g.n_div, g.b_no, g.b_ni);
+  }
+  // k walks: k-fast operands move by a whole tile, the others by the k rows of one loader pass
+  const KStep a_step(AKF ? BK : 256 / BM, g.k_in, g.a_ko, g.a_ki), b_step(BKF ? BK : 256 / BN, g.k_in, g.b_ko, g.b_ki);
+  KWalk a_k, b_k;
+  {
+    const int ka = kb + (AKF ? a_kk : a_kq), kbb = kb + (BKF ? b_kk : b_kq);
+    a_k.off = cmap(ka, g.k_div, g.a_ko, g.a_ki);
+    b_k.off = cmap(kbb, g.k_div, g.b_ko, g.b_ki);
+    a_k.r = ka - (g.k_div.mul ? (int)(__umulhi((unsigned)ka, g.k_div.mul) >> g.k_div.shift) : ka) * g.k_in;
+    b_k.r = kbb - (g.k_div.mul ? (int)(__umulhi((unsigned)kbb, g.k_div.mul) >> g.k_div.shift) : kbb) * g.k_in;
   }
 
   C2<R> ra[NA], rb[NB];
@@ -136,53 +178,55 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
     if (AKF) {
       const int k = k0 + a_kk;
       const bool kv = !CHECK || k < ke;
-      const int64_t ko = kv ? cmap(k, g.k_in, g.a_ko, g.a_ki) : 0;
 #pragma unroll
       for (int q = 0; q < NA; ++q) {
         if (kv) {
-          ra[q] = ldc(A, a_off[q] + ko);
+          ra[q] = ldc(A, a_off[q] + a_k.off);
         } else {
           ra[q].x = R(0);
           ra[q].y = R(0);
         }
       }
+      a_step.advance(a_k);
     } else {
       constexpr int KS = 256 / BM;
 #pragma unroll
       for (int q = 0; q < NA; ++q) {
         const int k = k0 + a_kq + KS * q;
         if (!CHECK || k < ke) {
-          ra[q] = ldc(A, a_off[0] + cmap(k, g.k_in, g.a_ko, g.a_ki));
+          ra[q] = ldc(A, a_off[0] + a_k.off);
         } else {
           ra[q].x = R(0);
           ra[q].y = R(0);
         }
+        a_step.advance(a_k);
       }
     }
     if (BKF) {
       const int k = k0 + b_kk;
       const bool kv = !CHECK || k < ke;
-      const int64_t ko = kv ? cmap(k, g.k_in, g.b_ko, g.b_ki) : 0;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
         if (kv) {
-          rb[q] = ldc(B, b_off[q] + ko);
+          rb[q] = ldc(B, b_off[q] + b_k.off);
         } else {
           rb[q].x = R(0);
           rb[q].y = R(0);
         }
       }
+      b_step.advance(b_k);
     } else {
       constexpr int KS = 256 / BN;
 #pragma unroll
       for (int q = 0; q < NB; ++q) {
         const int k = k0 + b_kq + KS * q;
         if (!CHECK || k < ke) {
-          rb[q] = ldc(B, b_off[0] + cmap(k, g.k_in, g.b_ko, g.b_ki));
+          rb[q] = ldc(B, b_off[0] + b_k.off);
         } else {
           rb[q].x = R(0);
           rb[q].y = R(0);
         }
+        b_step.advance(b_k);
       }
     }
   };
@@ -325,12 +369,12 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
     for (int j = 0; j < TN; ++j) {
       const int col = n0 + wn * (BN / 2) + 16 * j + (lane & 15);
       if (col >= g.N) continue;
-      const int64_t co = cmap(col, g.n_in, g.c_no, g.c_ni);
+      const int64_t co = cmap(col, g.n_div, g.c_no, g.c_ni);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = m0 + wm * (BM / 2) + 16 * i + MF<R>::row(lane, r);
         if (row >= g.M) continue;
-        const int64_t off = 2 * (co + cmap(row, g.m_in, g.c_mo, g.c_mi));
+        const int64_t off = 2 * (co + cmap(row, g.m_div, g.c_mo, g.c_mi));
         const R xr = accR[i][j][r], xi = accI[i][j][r];
         R yr = g.alpha_re * xr - g.alpha_im * xi;
         R yi = g.alpha_re * xi + g.alpha_im * xr;
@@ -357,7 +401,7 @@ __global__ __launch_bounds__(256) void gett_splitk_reduce(Gett<R> g, int nz, int
       sr += w[0];
       si += w[1];
     }
-    R* c = g.C + 2 * (b * g.c_b + cmap(m, g.m_in, g.c_mo, g.c_mi) + cmap(n, g.n_in, g.c_no, g.c_ni));
+    R* c = g.C + 2 * (b * g.c_b + cmap(m, g.m_div, g.c_mo, g.c_mi) + cmap(n, g.n_div, g.c_no, g.c_ni));
     R yr = g.alpha_re * sr - g.alpha_im * si;
     R yi = g.alpha_re * si + g.alpha_im * sr;
     if (g.accumulate) {
@@ -369,6 +413,18 @@ __global__ __launch_bounds__(256) void gett_splitk_reduce(Gett<R> g, int nz, int
   }
 }
 
+// Multiplier and shift with x / d = umulhi(x, mul) >> shift for 0 <= x < 2^31 (Granlund and
+// Montgomery, Division by invariant integers using multiplication, 1994); mul = 0 for d = 1.
+static FastDiv fast_div(int d) {
+  FastDiv f{d, 0, 0};
+  if (d <= 1) return f;
+  int l = 1;
+  while (((int64_t)1 << l) < d) ++l;
+  f.mul = (unsigned)(((uint64_t)1 << (31 + l)) / (uint64_t)d + 1);
+  f.shift = l - 1;
+  return f;
+}
+
 static thread_local void* g_ws = nullptr;
 static thread_local size_t g_ws_bytes = 0;
 void set_gett_workspace(void* p, size_t bytes) {
@@ -376,9 +432,11 @@ void set_gett_workspace(void* p, size_t bytes) {
   g_ws_bytes = bytes;
 }
 
-template <typename R, int BM, int BN, int KIND>
-static void launch_cfg(const Gett<R>& g, hipStream_t s) {
-  const int tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+// nz_want: split-K slices (0: by the long-K rule below; the workspace may allow fewer).
+template <typename R, int BM, int BN, int BK, bool DB, int KIND>
+static void launch_cfg(const Gett<R>& g, int nz_want, hipStream_t s) {
+  const int64_t tiles = (int64_t)((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  if (tiles > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
   const bool akf = (g.a_ki == 1) || !(g.a_mi == 1);
   const bool bkf = (g.b_ki == 1) || !(g.b_ni == 1);
   for (int64_t b0 = 0; b0 < g.nbatch; b0 += 65535) {
@@ -387,28 +445,26 @@ static void launch_cfg(const Gett<R>& g, hipStream_t s) {
     h.A = g.A + 2 * b0 * g.a_b;
     h.B = g.B + 2 * b0 * g.b_b;
     h.C = g.C + 2 * b0 * g.c_b;
-    // split K when the output alone gives too few workgroups to fill the chip
     int nz = 1;
     h.kslice = g.K > 0 ? g.K : 1;
-    const int64_t wgs = (int64_t)tiles * nb;
-    // long K: slices of >= 256 k up to ~1024 workgroups; outputs of a few tiles (small
-    // problems, whose time is the serial k-loop of each workgroup): slices of >= 32 k up to
-    // ~256 workgroups
-    const bool long_k = wgs < 1024 && g.K >= 1024, few_tiles = wgs < 128 && g.K >= 64;
-    if (g_ws && (long_k || few_tiles)) {
-      const int64_t kmin = long_k ? 256 : 32;
+    h.m_div = fast_div(g.m_in);
+    h.n_div = fast_div(g.n_in);
+    h.k_div = fast_div(g.k_in);
+    const int64_t wgs = tiles * nb;
+    // long K on an output that does not fill the chip by itself: slices of >= 256 k in whole
+    // rounds of workgroups (two per CU, 512 at a time): nz slices take ceil(wgs nz / 512)
+    // rounds of K / nz each; the smallest nz within 2% of the best rounds / nz
+    const bool long_k = nz_want == 0 && wgs < 1024 && g.K >= 1024;
+    if (g_ws && (long_k || nz_want > 1)) {
       const int64_t per = (int64_t)g.M * g.N * nb * 2 * (int64_t)sizeof(R);
       const int64_t cap = per > 0 ? (int64_t)(g_ws_bytes / per) : 0;
-      int64_t zmax = (g.K + kmin - 1) / kmin;
+      int64_t zmax = (g.K + (nz_want > 1 ? 31 : 255)) / (nz_want > 1 ? 32 : 256);
       if (zmax > cap) zmax = cap;
       if (zmax > 1024) zmax = 1024;
       int64_t want = 1;
-      if (few_tiles && !long_k) {
-        want = (256 + wgs - 1) / wgs;
+      if (nz_want > 1) {
+        want = nz_want;
       } else {
-        // whole rounds of workgroups (two per CU, 512 at a time): nz slices take
-        // ceil(wgs nz / 512) rounds of K / nz each; the smallest nz within 2% of the best
-        // rounds / nz
         auto cost = [&](int64_t z) { return (double)((wgs * z + 511) / 512) / (double)z; };
         double best = cost(1);
         for (int64_t z = 2; z <= zmax; ++z) best = cost(z) < best ? cost(z) : best;
@@ -423,11 +479,7 @@ static void launch_cfg(const Gett<R>& g, hipStream_t s) {
         h.ws = (R*)g_ws;
       }
     }
-    dim3 grid(tiles, nb, nz), block(256);
-    // FP64: BK = 32, one LDS buffer (two barriers per 96 MFMAs); FP32: BK = 16,
-    // two buffers.  Both fill 65 KB (FP64) / 33 KB (FP32) of LDS per workgroup.
-    constexpr int BK = sizeof(R) == 8 ? 32 : 16;
-    constexpr bool DB = sizeof(R) != 8;
+    dim3 grid((unsigned)tiles, nb, nz), block(256);
     if (akf && bkf)
       hipLaunchKernelGGL((gett_kernel<R, BM, BN, BK, DB, true, true, KIND>), grid, block, 0, s, h);
     else if (akf)
@@ -445,6 +497,50 @@ static void launch_cfg(const Gett<R>& g, hipStream_t s) {
       HIPCHECK(hipGetLastError());
     }
   }
+}
+
+// Tile and split of an output with few 64 x 64 tiles.  Estimated time (us) with c workgroups
+// per CU and n k-steps of 32: 2.5 + n max(lat, c thr), plus the reduction launch and its
+// traffic; lat is one workgroup alone on its CU (its loads and LDS steps are a serial chain),
+// thr what a CU takes per workgroup when several share it.  FP64: 64 x 64 tiles lat 4.1, thr
+// 3.7; 32 x 32 tiles (one 16 x 16 block per wave) 1.4, 1.1.  FP32: 2.7, 2.2 and 1.1, 0.65.
+// Measured (us), 64 x 64 with its best split against this choice: 240 x 240 x 120 12.8 / 9.5,
+// 40 x 40 x 1440 40 / 13.4, 15 x 780 x 15 8.8 / 4.0, 1131 x 169 x 259 24.9 / 17.0.
+template <typename R>
+static bool few_tiles(const Gett<R>& g, int& tile, int& nz) {
+  auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
+  if (!g_ws || up(g.M, 64) * up(g.N, 64) * g.nbatch > 640) return false;
+  constexpr bool dp = sizeof(R) == 8;
+  static const int zs[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
+  double best = 1e300;
+  for (int t = 32; t <= 64; t += 32) {
+    const double lat = t == 64 ? (dp ? 4.1 : 2.7) : (dp ? 1.4 : 1.1), thr = t == 64 ? (dp ? 3.7 : 2.2) : (dp ? 1.1 : 0.65);
+    const int64_t wgs = up(g.M, t) * up(g.N, t) * g.nbatch;
+    for (int z : zs) {
+      if (z > 1 && z * 32 > g.K) break;
+      const double n = (double)up(up(g.K > 0 ? g.K : 1, z), 32), c = (double)up(wgs * z, 256);
+      const double mn = (double)g.M * g.N * g.nbatch;
+      const double us = 2.5 + n * std::max(lat, c * thr) + (z > 1 ? 3.5 + 0.08 * z + 4.0 * sizeof(R) * z * mn / 10e6 : 0.0);
+      if (us < best) {
+        best = us;
+        tile = t;
+        nz = z;
+      }
+    }
+  }
+  return true;
+}
+
+template <typename R, int KIND>
+static void launch_tiles(const Gett<R>& g, hipStream_t s) {
+  // 64 x 64 tiles, FP64: BK = 32, one LDS buffer (two barriers per 96 MFMAs); FP32: BK = 16,
+  // two buffers.  Both fill 65 KB (FP64) / 33 KB (FP32) of LDS per workgroup.
+  constexpr bool dp = sizeof(R) == 8;
+  int tile = 64, nz = 0;
+  if (few_tiles(g, tile, nz) && tile == 32)
+    launch_cfg<R, 32, 32, dp ? 16 : 32, true, GETT_GENERIC>(g, nz, s);
+  else
+    launch_cfg<R, 64, 64, dp ? 32 : 16, !dp, KIND>(g, nz, s);
 }
 
 
@@ -899,6 +995,8 @@ static void launch_bf16x3(const Gett<float>& g, hipStream_t s) {
     h.C = g.C + 2 * b0 * g.c_b;
     h.kslice = g.K > 0 ? g.K : 1;
     h.ws = nullptr;
+    h.m_div = fast_div(g.m_in);  // the split-K reduction's
+    h.n_div = fast_div(g.n_in);
     // split K when the output gives too few workgroups for whole rounds over the CUs (one
     // 16-wave workgroup per CU): with nz slices the launch takes ceil(wgs nz / 256) rounds
     // of K / nz each, so nz is the smallest count within 2% of the best rounds / nz, taken
@@ -973,10 +1071,10 @@ void launch_gett(const Gett<R>& g, int kind_in, hipStream_t s) {
                                                    : GETT_RING;
   }
   switch (kind) {
-    case GETT_LADDER_BUILD: launch_cfg<R, 64, 64, GETT_LADDER_BUILD>(g, s); break;
-    case GETT_LADDER_CONTRACT: launch_cfg<R, 64, 64, GETT_LADDER_CONTRACT>(g, s); break;
-    case GETT_RING: launch_cfg<R, 64, 64, GETT_RING>(g, s); break;
-    default: launch_cfg<R, 64, 64, GETT_GENERIC>(g, s); break;
+    case GETT_LADDER_BUILD: launch_tiles<R, GETT_LADDER_BUILD>(g, s); break;
+    case GETT_LADDER_CONTRACT: launch_tiles<R, GETT_LADDER_CONTRACT>(g, s); break;
+    case GETT_RING: launch_tiles<R, GETT_RING>(g, s); break;
+    default: launch_tiles<R, GETT_GENERIC>(g, s); break;
   }
 }
 
