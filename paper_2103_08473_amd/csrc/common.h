@@ -130,7 +130,7 @@ template <typename T>
 void k_ring_operands(const T* T2, const double* t1, T* Tq, T* Xp, int o, int v, hipStream_t s,
                      const double* t1r = nullptr);
 template <typename T>
-void k_expand_c(const T* Vooov, const T* Cp, T* Cf, int o, int v, hipStream_t s);
+void k_expand_c(const T* Vooov, const T* Cp, const T* Y, T* Cf, int o, int v, hipStream_t s);
 // W[b'][(c<d)] = Ta[c][b'][d] - Ta[d][b'][c] over c, d < v, rows of W ldw apart
 template <typename T>
 void k_ladder_antisym(const T* Ta, T* W, int nb, int v, int64_t ldw, hipStream_t s);
@@ -150,6 +150,13 @@ void k_assemble_t2(const T* Znp, const T* Z, const T* R, const double* Voovv_p, 
 template <typename T>
 void k_assemble_t1(const T* S1, const double* t1, const double* eps, int o, int v, double shift,
                    bool frozen, double* xt, double* e, double* s1_full, double* partial, hipStream_t s);
+// UB[k][i][P] = B^P_ki + U, VB[a][i][P] = B^P_ai + Vt
+template <typename T>
+void k_dress_factors(T* UB, T* VB, const T* U, const T* Vt, const T* Bt, int o, int v, int n, int X,
+                     hipStream_t s);
+// the one-body doubles terms into the ring intermediate H[a][i][k][c]
+template <typename T>
+void k_ring_fock(T* H, const T* Gac, const T* Gki, int o, int v, hipStream_t s);
 // CC2: Vt[a][i][P] += B^P_ai - Q[a][i][P] (the T1-dressed vo DF factor; Bt is [p][q][P])
 template <typename T>
 void k_dress_vo(T* Vt, const T* Bt, const T* Q, int o, int v, int n, int X, hipStream_t s);

@@ -201,9 +201,10 @@ __global__ void ring_operands_kernel(const T* __restrict__ T2, const double* __r
 }
 
 // Cf[i][j][b][k] = conj(Vooov[i][j][k][b]) + sign(i,j) Cp[(min,max)][b][k]
+//                  + Y[i][j][b][k] - Y[j][i][b][k]  (Y may be null)
 template <typename T>
 __global__ void expand_c_kernel(const T* __restrict__ Vooov, const T* __restrict__ Cp,
-                                T* __restrict__ Cf, int o, int v) {
+                                const T* __restrict__ Y, T* __restrict__ Cf, int o, int v) {
   const int64_t tot = (int64_t)o * o * v * o;
   for (int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x; t < tot; t += (int64_t)gridDim.x * TB) {
     int64_t r = t;
@@ -220,6 +221,7 @@ __global__ void expand_c_kernel(const T* __restrict__ Vooov, const T* __restrict
       z c = ld(Cp, (pidx(p, q, o) * v + b) * o + k);
       x = (i < j) ? add(x, c) : sub(x, c);
     }
+    if (Y) x = add(x, sub(ld(Y, t), ld(Y, ((((int64_t)j * o + i) * v) + b) * o + k)));
     st(Cf, t, x);
   }
 }
@@ -346,8 +348,9 @@ __global__ void assemble_t2_kernel(const T* __restrict__ Znp, const T* __restric
     const int64_t ijba = ((int64_t)i * o + j) * vv + (int64_t)b * v + a;
     const int64_t jiab = ((int64_t)j * o + i) * vv + (int64_t)a * v + b;
     const int64_t jiba = ((int64_t)j * o + i) * vv + (int64_t)b * v + a;
-    // Znp, R and Vp may be null (CC2 doubles: Z holds the whole T1-dressed <ab||ij>)
-    z s = ld(Z, ijab);
+    // Znp, Z, R and Vp may be null (CC2 doubles: Z holds the whole T1-dressed <ab||ij>)
+    z s = {0.0, 0.0};
+    if (Z) s = ld(Z, ijab);
     if (Znp) s = add(s, ld(Znp, t));
     if (R) s = add(s, add(sub(ld(R, ijab), ld(R, jiab)), sub(ld(R, jiba), ld(R, ijba))));
     if (Vp) {
@@ -706,9 +709,9 @@ void k_ring_operands(const T* T2, const double* t1, T* Tq, T* Xp, int o, int v, 
 }
 
 template <typename T>
-void k_expand_c(const T* Vooov, const T* Cp, T* Cf, int o, int v, hipStream_t s) {
+void k_expand_c(const T* Vooov, const T* Cp, const T* Y, T* Cf, int o, int v, hipStream_t s) {
   const int64_t tot = (int64_t)o * o * o * v;
-  hipLaunchKernelGGL(expand_c_kernel<T>, dim3(nblocks(tot)), dim3(TB), 0, s, Vooov, Cp, Cf, o, v);
+  hipLaunchKernelGGL(expand_c_kernel<T>, dim3(nblocks(tot)), dim3(TB), 0, s, Vooov, Cp, Y, Cf, o, v);
   HIPCHECK(hipGetLastError());
 }
 
@@ -776,6 +779,63 @@ void k_dress_vo(T* Vt, const T* Bt, const T* Q, int o, int v, int n, int X, hipS
   const int64_t tot = (int64_t)v * o * X;
   if (tot <= 0) return;
   hipLaunchKernelGGL(dress_vo_kernel<T>, dim3(nblocks(tot)), dim3(TB), 0, s, Vt, Bt, Q, o, v, n, X);
+  HIPCHECK(hipGetLastError());
+}
+
+// T1-dressed DF factors of the ring intermediate: UB[k][i][P] = B^P_ki + U[k][i][P] and
+// VB[a][i][P] = B^P_ai + Vt[a][i][P], one pass instead of a second product with each part.
+template <typename T>
+__global__ void dress_factors_kernel(T* __restrict__ UB, T* __restrict__ VB, const T* __restrict__ U,
+                                     const T* __restrict__ Vt, const T* __restrict__ Bt, int o, int v, int n,
+                                     int X) {
+  const int64_t nu = (int64_t)o * o * X, tot = nu + (int64_t)v * o * X;
+  for (int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x; t < tot; t += (int64_t)gridDim.x * TB) {
+    const bool u = t < nu;
+    const int64_t q = u ? t : t - nu, ri = q / X, P = q - ri * X;
+    const int r = (int)(ri / o), i = (int)(ri - (int64_t)r * o);
+    const z b = ld(Bt, ((int64_t)(u ? r : o + r) * n + i) * X + P);
+    st(u ? UB : VB, q, add(ld(u ? U : Vt, q), b));
+  }
+}
+
+template <typename T>
+void k_dress_factors(T* UB, T* VB, const T* U, const T* Vt, const T* Bt, int o, int v, int n, int X,
+                     hipStream_t s) {
+  const int64_t tot = (int64_t)o * (o + v) * X;
+  hipLaunchKernelGGL(dress_factors_kernel<T>, dim3(nblocks(tot)), dim3(TB), 0, s, UB, VB, U, Vt, Bt, o, v, n, X);
+  HIPCHECK(hipGetLastError());
+}
+
+// The one-body terms P_ij G_kj t_ik^ab + P_ab G_ac t_ij^cb as part of the ring product: with
+// Tq[b][j][k][c] = t_jk^cb, H[a][i][k][c] -= (delta_ik G_ac + delta_ac G_ki) / 2 adds them under
+// P_ij P_ab (each term is antisymmetric in the other pair, which doubles it).
+template <typename T>
+__global__ void ring_fock_kernel(T* __restrict__ H, const T* __restrict__ Gac, const T* __restrict__ Gki, int o,
+                                 int v) {
+  const int64_t na = (int64_t)v * o * v, tot = na + (int64_t)v * o * o;
+  for (int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x; t < tot; t += (int64_t)gridDim.x * TB) {
+    if (t < na) {  // k = i
+      const int c = (int)(t % v);
+      const int64_t ai = t / v;
+      const int a = (int)(ai / o), i = (int)(ai - (int64_t)a * o);
+      z g = ld(Gac, (int64_t)a * v + c);
+      if (a == c) g = add(g, ld(Gki, (int64_t)i * o + i));
+      const int64_t h = (ai * o + i) * v + c;
+      st(H, h, sub(ld(H, h), scal(0.5, g)));
+    } else {  // k != i, c = a
+      const int64_t q = t - na, ai = q / o;
+      const int k = (int)(q - ai * o), a = (int)(ai / o), i = (int)(ai - (int64_t)a * o);
+      if (k == i) continue;
+      const int64_t h = (ai * o + k) * v + a;
+      st(H, h, sub(ld(H, h), scal(0.5, ld(Gki, (int64_t)k * o + i))));
+    }
+  }
+}
+
+template <typename T>
+void k_ring_fock(T* H, const T* Gac, const T* Gki, int o, int v, hipStream_t s) {
+  const int64_t tot = (int64_t)v * o * (o + v);
+  hipLaunchKernelGGL(ring_fock_kernel<T>, dim3(nblocks(tot)), dim3(TB), 0, s, H, Gac, Gki, o, v);
   HIPCHECK(hipGetLastError());
 }
 
@@ -1145,7 +1205,7 @@ void k_pack_amplitudes(const double* t1, const double* t2, double* x, int o, int
   template void k_unpack_tau<T>(const double*, const double*, T*, T*, T*, int, int, hipStream_t); \
   template void k_ring_operands<T>(const T*, const double*, T*, T*, int, int, hipStream_t,       \
                                    const double*);                                               \
-  template void k_expand_c<T>(const T*, const T*, T*, int, int, hipStream_t);                    \
+  template void k_expand_c<T>(const T*, const T*, const T*, T*, int, int, hipStream_t);                    \
   template void k_ladder_antisym<T>(const T*, T*, int, int, int64_t, hipStream_t);               \
   template void k_ladder_antisym_all<T>(const T*, T*, int, hipStream_t);                          \
   template void k_transpose_tail<T>(const T*, int64_t, int64_t, int64_t, int64_t, T*, int64_t,       \
@@ -1155,7 +1215,9 @@ void k_pack_amplitudes(const double* t1, const double* t2, double* x, int o, int
                                  double*, int, hipStream_t);                                      \
   template void k_assemble_t1<T>(const T*, const double*, const double*, int, int, double, bool, \
                                  double*, double*, double*, double*, hipStream_t);               \
-  template void k_dress_vo<T>(T*, const T*, const T*, int, int, int, int, hipStream_t);
+  template void k_dress_vo<T>(T*, const T*, const T*, int, int, int, int, hipStream_t);                   \
+  template void k_dress_factors<T>(T*, T*, const T*, const T*, const T*, int, int, int, int, hipStream_t); \
+  template void k_ring_fock<T>(T*, const T*, const T*, int, int, hipStream_t);
 EXACC_INST(double)
 EXACC_INST(float)
 #undef EXACC_INST

@@ -206,7 +206,7 @@ struct Handle {
   // Voovv and Vvovv_p exist in FP64 only while FP64 contractions are in use
   double *Bt = nullptr, *Voooo, *Vooov, *Voovv = nullptr, *Voovv_p, *Vvovv_p = nullptr;
   // Xp is reused for the ring output R once the ring intermediate is built;
-  // Z holds the doubles residual pieces that carry no permutation operator
+  // Z: scratch (CC2: its doubles)
   double *x, *diis, *TAU, *taup, *Tq, *Xp, *H4, *Z, *Znp;
   double *Hac, *Gac, *Hki, *Gki, *Hkc, *y, *U, *Vt, *M1, *Y, *S1, *Cp, *Cf, *Af, *Ap;
   double *Ta, *W, *t1w;
@@ -504,9 +504,8 @@ static void ensure_fp64_classes(Handle& h, bool keep_low_ladder = false) {
 
 // ------------------------------------------------------------------ residual pieces
 // Fills S1 (singles, without the diagonal Fock part) and the doubles pieces
-// Znp (packed) and Z (full) with no permutation left to apply, and R which
-// still needs P_ij P_ab (applied in the assembly), for the
-// amplitudes in h.x.
+// Znp (packed), with no permutation left to apply, and R, which still needs
+// P_ij P_ab (applied in the assembly), for the amplitudes in h.x.
 // Particle-ladder product Znp[p][(a<b)] += sum_{c<d} Lp[p][(c<d)] (F_ac.F_bd - F_ad.F_bc), the
 // integrals formed tile by tile from factor rows F[a][c][P] (row a at F + a * row_stride,
 // [c][P] contiguous) and never stored whole: for each a, Ta[c][b][d] = sum_P F_ac F_bd over
@@ -937,6 +936,9 @@ static void compute_residual(Handle& h) {
     return;
   }
   auto H4 = view(w.H4, {v, o, o, v});
+  // The one-body terms ride in the ring product, except where that product is BF16x3 (they are
+  // FP32 terms there) or is taken from the corrected phase's reference (they change, it not)
+  const bool fold = !bf && !(sizeof(R) == sizeof(double) && h.dc != 0 && h.P.ring_dc);
   bool ring_done = false;
   if constexpr (sizeof(R) == sizeof(double)) {
     if (h.dc == 2 && h.P.ring_dc) {
@@ -947,15 +949,25 @@ static void compute_residual(Handle& h) {
   if (!ring_done) {
   {
     Scope sc(h, "ring_build");
-    // <ak||ci> = (ac|ki) - (ai|kc), formed from the factors each iteration
-    contract(s, "acP,kiP->aikc", ONE, b.Bvv, b.Boo, false, H4, df_kind);
-    contract(s, "aiP,kcP->aikc", MONE, b.Bvo, b.Bov, true, H4, df_kind);
-    if (!ccd) {
-      contract(s, "acP,kiP->aikc", ONE, b.Bvv, U, true, H4, df_kind);
-      contract(s, "aiP,kcP->aikc", MONE, Vt, b.Bov, true, H4, df_kind);
-      contract(s, "klic,la->aikc", MONE, Vooov, t1, true, H4);
+    // <ak||ci> = (ac|ki) - (ai|kc) and its t1 terms, formed from the factors each iteration:
+    // B_ki + U_ki and B_ai + Vt_ai (in Z, free until the C term, and in Y, free until the
+    // singles) enter one product each
+    const bool dressed = !ccd && X <= (int64_t)v * v;
+    if (dressed) {
+      k_dress_factors<R>(w.Z, w.Y, w.U, w.Vt, w.Bt, o, v, h.P.n, X, s);
+      contract(s, "acP,kiP->aikc", ONE, b.Bvv, view(w.Z, {o, o, X}), false, H4, df_kind);
+      contract(s, "aiP,kcP->aikc", MONE, view(w.Y, {v, o, X}), b.Bov, true, H4, df_kind);
+    } else {
+      contract(s, "acP,kiP->aikc", ONE, b.Bvv, b.Boo, false, H4, df_kind);
+      contract(s, "aiP,kcP->aikc", MONE, b.Bvo, b.Bov, true, H4, df_kind);
+      if (!ccd) {
+        contract(s, "acP,kiP->aikc", ONE, b.Bvv, U, true, H4, df_kind);
+        contract(s, "aiP,kcP->aikc", MONE, Vt, b.Bov, true, H4, df_kind);
+      }
     }
+    if (!ccd) contract(s, "klic,la->aikc", MONE, Vooov, t1, true, H4);
     contract(s, "aild,klcd->aikc", ONE, view(w.Xp, {v, o, o, v}), Voovv, true, H4, ring_kind);
+    if (fold) k_ring_fock<R>(w.H4, w.Gac, w.Gki, o, v, s);
   }
   auto Rv = view(w.R_, {o, o, v, v});
   {
@@ -971,18 +983,13 @@ static void compute_residual(Handle& h) {
     if (!ccd) contract(s, "aiP,bjP->ijab", ONE, Vt, b.Bvo, true, Rv, df_kind);
   }
   }
-  // Z and its views with i<->j or a<->b swapped: a term X launched into Z and,
-  // negated, into a swapped view accumulates P^-_ij X (or P^-_ab X) directly
-  const int64_t vv = (int64_t)v * v, ovv = (int64_t)o * v * v;
-  auto Z = view(w.Z, {o, o, v, v});
-  auto Zji = sview(w.Z, {o, o, v, v}, {vv, ovv, v, 1});
-  auto Zba = sview(w.Z, {o, o, v, v}, {ovv, vv, 1, v});
-  {
+  // Terms with one permutation operator are antisymmetric in the other pair, so half of each,
+  // added to R, gives it once P_ij P_ab is applied
+  auto Rall = view(w.R_, {o, o, v, v});
+  if (!fold) {
     Scope sc(h, "fock_terms");
-    contract(s, "kj,ikab->ijab", ONE, Gki, T2, false, Z);
-    contract(s, "kj,ikab->ijab", MONE, Gki, T2, true, Zji);
-    contract(s, "ac,ijcb->ijab", ONE, Gac, T2, true, Z);
-    contract(s, "ac,ijcb->ijab", MONE, Gac, T2, true, Zba);
+    contract(s, "kj,ikab->ijab", HALF, Gki, T2, true, Rall);
+    contract(s, "ac,ijcb->ijab", HALF, Gac, T2, true, Rall);
   }
   if (!ccd) {  // C^{kb}_{ij} enters only through P_ab sum_k C t_k^a
     Scope sc(h, "cterm");
@@ -1006,19 +1013,25 @@ static void compute_residual(Handle& h) {
     if constexpr (sizeof(R) == sizeof(double)) {
       if (h.P.ring_dc && h.dc == 1) dcopy(h, h.Cref, w.Cp, Po * v * o);
     }
-    k_expand_c<R>(w.Vooov, w.Cp, w.Cf, o, v, s);
     auto Cf = view(w.Cf, {o, o, v, o});
     // P^-_ij sum_c <bk||ci> t_j^c with <bk||ci> = (bc|ki) - (bi|kc):
     //   sum_c (bc|ki) t_j^c = sum_P Vt^P_bj B^P_ki,  sum_c (bi|kc) t_j^c = sum_P B^P_bi U^P_kj
-    const int64_t vo = (int64_t)v * o, oo = (int64_t)o * o, oovo = oo * v * o;
-    auto Cfji = sview(w.Cf, {o, o, v, o}, {vo, o * vo, o, 1});
-    contract(s, "bjP,kiP->ijbk", ONE, Vt, b.Boo, true, Cf);
-    contract(s, "biP,kjP->ijbk", MONE, b.Bvo, U, true, Cf);
-    contract(s, "bjP,kiP->ijbk", MONE, Vt, b.Boo, true, Cfji);
-    contract(s, "biP,kjP->ijbk", ONE, b.Bvo, U, true, Cfji);
-    (void)oovo;
-    contract(s, "ijak,kb->ijab", ONE, Cf, t1, true, Z);
-    contract(s, "ijak,kb->ijab", MONE, Cf, t1, true, Zba);
+    // formed once in Z and antisymmetrised as C is expanded (where Z holds o^3 v)
+    if (o <= v) {
+      auto Yc = view(w.Z, {o, o, v, o});
+      contract(s, "bjP,kiP->ijbk", ONE, Vt, b.Boo, false, Yc);
+      contract(s, "biP,kjP->ijbk", MONE, b.Bvo, U, true, Yc);
+      k_expand_c<R>(w.Vooov, w.Cp, w.Z, w.Cf, o, v, s);
+    } else {
+      k_expand_c<R>(w.Vooov, w.Cp, nullptr, w.Cf, o, v, s);
+      const int64_t vo = (int64_t)v * o;
+      auto Cfji = sview(w.Cf, {o, o, v, o}, {vo, o * vo, o, 1});
+      contract(s, "bjP,kiP->ijbk", ONE, Vt, b.Boo, true, Cf);
+      contract(s, "biP,kjP->ijbk", MONE, b.Bvo, U, true, Cf);
+      contract(s, "bjP,kiP->ijbk", MONE, Vt, b.Boo, true, Cfji);
+      contract(s, "biP,kjP->ijbk", ONE, b.Bvo, U, true, Cfji);
+    }
+    contract(s, "ijak,kb->ijab", HALF, Cf, t1, true, Rall);
   }
   auto Znp = view(w.Znp, {Po, Pv});
   {
@@ -1162,7 +1175,7 @@ static int assemble(Handle& h, double* xt, double* e, double* s1, double* s2, do
   if (np > 0) {
     nb = assemble_t2_blocks(np);
     const bool cc2 = h.op.cc2 != 0;
-    k_assemble_t2<R>(cc2 ? nullptr : w.Znp, w.Z, cc2 ? nullptr : w.R_, cc2 ? nullptr : h.Voovv_p,
+    k_assemble_t2<R>(cc2 ? nullptr : w.Znp, cc2 ? w.Z : nullptr, cc2 ? nullptr : w.R_, cc2 ? nullptr : h.Voovv_p,
                      h.x + 2 * ov, h.eps, o, v, shift,
                      xt ? xt + 2 * ov : nullptr, e ? e + 2 * ov : nullptr, s2,
                      s2 ? nullptr : h.red + 1, nb, h.s);
@@ -1722,10 +1735,16 @@ static void lambda_prepare(Handle& h) {
   // W_ovvo as Wq[b][j][m][e] = W_ovvo[j][e][b][m] = -H'[e][m][j][b], H'[a][i][k][c] the ring
   // intermediate of the amplitude equations with the full t2 in place of t2/2
   auto Wq = sview(w.H4, {v, o, o, v}, {1, v, ov, oov});
-  contract(s, "acP,kiP->aikc", MONE, b.Bvv, b.Boo, false, Wq);
-  contract(s, "aiP,kcP->aikc", ONE, b.Bvo, b.Bov, true, Wq);
-  contract(s, "acP,kiP->aikc", MONE, b.Bvv, U, true, Wq);
-  contract(s, "aiP,kcP->aikc", ONE, Vt, b.Bov, true, Wq);
+  if (X <= (int64_t)v * v) {  // one product each with B_ki + U_ki and B_ai + Vt_ai
+    k_dress_factors<double>(w.Z, w.Y, w.U, w.Vt, w.Bt, o, v, n, X, s);
+    contract(s, "acP,kiP->aikc", MONE, b.Bvv, view(w.Z, {o, o, X}), false, Wq);
+    contract(s, "aiP,kcP->aikc", ONE, view(w.Y, {v, o, X}), b.Bov, true, Wq);
+  } else {
+    contract(s, "acP,kiP->aikc", MONE, b.Bvv, b.Boo, false, Wq);
+    contract(s, "aiP,kcP->aikc", ONE, b.Bvo, b.Bov, true, Wq);
+    contract(s, "acP,kiP->aikc", MONE, b.Bvv, U, true, Wq);
+    contract(s, "aiP,kcP->aikc", ONE, Vt, b.Bov, true, Wq);
+  }
   contract(s, "klic,la->aikc", ONE, Vooov, t1, true, Wq);
   contract(s, "aild,klcd->aikc", MONE, view(w.Xp, {v, o, o, v}), Voovv, true, Wq);
   contract(s, "aild,klcd->aikc", cplx{-0.5, 0}, view(w.Tq, {v, o, o, v}), Voovv, true, Wq);
@@ -1734,7 +1753,7 @@ static void lambda_prepare(Handle& h) {
   auto Cp = view(w.Cp, {Po, v, o});
   auto taup = view(w.taup, {Po, h.P.Pv});
   if (Po > 0) contract(s, "bkx,px->pbk", MONE, view(w.Vvovv_p, {v, o, h.P.Pv}), taup, false, Cp);
-  k_expand_c<double>(w.Vooov, w.Cp, w.Cf, o, v, s);
+  k_expand_c<double>(w.Vooov, w.Cp, nullptr, w.Cf, o, v, s);
   auto Cf = view(w.Cf, {o, o, v, o});
   auto Cfji = sview(w.Cf, {o, o, v, o}, {vo, o * vo, o, 1});
   contract(s, "me,ijbe->ijbm", MONE, Hkc, T2, true, Cf);
@@ -1755,14 +1774,13 @@ static void lambda_prepare(Handle& h) {
   L.prepared = true;
 }
 
-// R1 into S1 and the pieces of R2 into Z (no permutation), R (P_ij P_ab at assembly)
-// and Znp (packed), at the Lambda amplitudes in h.lam.lam.
+// R1 into S1 and the pieces of R2 into R (P_ij P_ab at assembly) and Znp (packed; <ij||ab>
+// comes in at assembly), at the Lambda amplitudes in h.lam.lam.
 static void lambda_compute(Handle& h) {
   lambda_prepare(h);
   Work<double> w = work<double>(h);
   const int o = h.P.o, v = h.P.v, X = h.P.X;
   const int64_t Po = h.P.Po, Pv = h.P.Pv, ov = (int64_t)o * v, oov = (int64_t)o * o * v;
-  const int64_t vv = (int64_t)v * v, ovv = (int64_t)o * v * v;
   const hipStream_t s = h.s;
   Views<double> b = bviews(h, w.Bt);
   Handle::Lam& L = h.lam;
@@ -1785,26 +1803,8 @@ static void lambda_compute(Handle& h) {
   contract(s, "mnef,mnaf->ae", cplx{-0.5, 0}, T2, L2, false, Gv);
   contract(s, "mnef,inef->mi", HALF, T2, L2, false, Go);
 
-  // ---- R2, pieces without a permutation operator (Z and its swapped views)
-  auto Z = view(w.Z, {o, o, v, v});
-  auto Zji = sview(w.Z, {o, o, v, v}, {vv, ovv, v, 1});
-  auto Zba = sview(w.Z, {o, o, v, v}, {ovv, vv, 1, v});
-  dcopy(h, w.Z, w.Voovv, h.P.oovv);  // <ij||ab>
-  contract(s, "ijae,eb->ijab", ONE, L2, Gac, true, Z);
-  contract(s, "ijae,eb->ijab", MONE, L2, Gac, true, Zba);
-  contract(s, "imab,jm->ijab", ONE, L2, Gki, true, Z);
-  contract(s, "imab,jm->ijab", MONE, L2, Gki, true, Zji);
-  auto M1 = view(w.M1, {o, o});
-  contract(s, "ie,ne->in", ONE, l1, t1, false, M1);
-  contract(s, "in,njab->ijab", MONE, M1, Voovv, true, Z);
-  contract(s, "in,njab->ijab", ONE, M1, Voovv, true, Zji);
-  contract(s, "ma,ijmb->ijab", MONE, l1, Wooov, true, Z);
-  contract(s, "ma,ijmb->ijab", ONE, l1, Wooov, true, Zba);
-  contract(s, "ijae,be->ijab", ONE, Voovv, Gv, true, Z);
-  contract(s, "ijae,be->ijab", MONE, Voovv, Gv, true, Zba);
-  contract(s, "imab,mj->ijab", MONE, Voovv, Go, true, Z);
-  contract(s, "imab,mj->ijab", ONE, Voovv, Go, true, Zji);
-  // ---- R2, pieces under P_ij P_ab (R)
+  // ---- R2, pieces under P_ij P_ab (R); a piece under one of the two is antisymmetric in the
+  // other pair, so half of it in R gives it.  <ij||ab> itself is added at assembly.
   auto Rv = view(w.R_, {o, o, v, v});
   contract(s, "aime,bjme->ijab", MONE, view(L.Lq, {v, o, o, v}), Wq, false, Rv, GETT_RING);
   auto Yv = view(w.Y, {o, v, X});
@@ -1812,6 +1812,15 @@ static void lambda_compute(Handle& h) {
   contract(s, "iaP,jbP->ijab", ONE, Yv, b.Bov, true, Rv);
   contract(s, "iaz,jbz->ijab", ONE, sview(L.l1w, {o, v, 1}, {v, 1, 1}), sview(w.Hkc, {o, v, 1}, {v, 1, 1}),
            true, Rv);
+  contract(s, "ijae,eb->ijab", HALF, L2, Gac, true, Rv);
+  contract(s, "imab,jm->ijab", HALF, L2, Gki, true, Rv);
+  auto M1 = view(w.M1, {o, o});
+  contract(s, "ie,ne->in", ONE, l1, t1, false, M1);
+  const cplx MHALF{-0.5, 0};
+  contract(s, "in,njab->ijab", MHALF, M1, Voovv, true, Rv);
+  contract(s, "ma,ijmb->ijab", MHALF, l1, Wooov, true, Rv);
+  contract(s, "ijae,be->ijab", HALF, Voovv, Gv, true, Rv);
+  contract(s, "imab,mj->ijab", MHALF, Voovv, Go, true, Rv);
   // ---- R2, packed pieces (Znp): first the W_vvvv ladder alone, which R1 also needs
   auto Znp = view(w.Znp, {Po, Pv});
   auto l2v = view(const_cast<double*>(l2p), {Po, Pv});
@@ -1882,7 +1891,7 @@ static int lambda_assemble(Handle& h, double* xt, double* e, double* s1, double*
   int nb = 0;
   if (np > 0) {
     nb = assemble_t2_blocks(np);
-    k_assemble_t2<double>(w.Znp, w.Z, w.R_, nullptr, h.lam.lam + 2 * ov, h.eps, o, v, 0.0,
+    k_assemble_t2<double>(w.Znp, w.Voovv, w.R_, nullptr, h.lam.lam + 2 * ov, h.eps, o, v, 0.0,
                           xt ? xt + 2 * ov : nullptr, e ? e + 2 * ov : nullptr, s2,
                           s2 ? nullptr : h.red + 1, nb, h.s);
   }
