@@ -348,11 +348,12 @@ __global__ void assemble_t2_kernel(const T* __restrict__ Znp, const T* __restric
     const int64_t ijba = ((int64_t)i * o + j) * vv + (int64_t)b * v + a;
     const int64_t jiab = ((int64_t)j * o + i) * vv + (int64_t)a * v + b;
     const int64_t jiba = ((int64_t)j * o + i) * vv + (int64_t)b * v + a;
-    // Znp, Z, R and Vp may be null (CC2 doubles: Z holds the whole T1-dressed <ab||ij>)
+    // Znp, Z and Vp may be null (CC2 doubles: R alone, the T1-dressed <ab||ij>; Lambda: Z is
+    // <ij||ab>)
     z s = {0.0, 0.0};
     if (Z) s = ld(Z, ijab);
     if (Znp) s = add(s, ld(Znp, t));
-    if (R) s = add(s, add(sub(ld(R, ijab), ld(R, jiab)), sub(ld(R, jiba), ld(R, ijba))));
+    s = add(s, add(sub(ld(R, ijab), ld(R, jiab)), sub(ld(R, jiba), ld(R, ijba))));
     if (Vp) {
       const z g = ld(Vp, t);
       s.x += g.x;

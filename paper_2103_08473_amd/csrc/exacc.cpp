@@ -206,7 +206,7 @@ struct Handle {
   // Voovv and Vvovv_p exist in FP64 only while FP64 contractions are in use
   double *Bt = nullptr, *Voooo, *Vooov, *Voovv = nullptr, *Voovv_p, *Vvovv_p = nullptr;
   // Xp is reused for the ring output R once the ring intermediate is built;
-  // Z: scratch (CC2: its doubles)
+  // Z: scratch
   double *x, *diis, *TAU, *taup, *Tq, *Xp, *H4, *Z, *Znp;
   double *Hac, *Gac, *Hki, *Gki, *Hkc, *y, *U, *Vt, *M1, *Y, *S1, *Cp, *Cf, *Af, *Ap;
   double *Ta, *W, *t1w;
@@ -929,10 +929,8 @@ static void compute_residual(Handle& h) {
     contract(s, "kiP,ka->aiP", ONE, U, t1, false, Q);
     contract(s, "kiP,ka->aiP", ONE, b.Boo, t1, true, Q);
     k_dress_vo<R>(w.Vt, w.Bt, w.Y, o, v, h.P.n, X, s);
-    auto Z = view(w.Z, {o, o, v, v});
-    auto Zji = sview(w.Z, {o, o, v, v}, {(int64_t)v * v, (int64_t)o * v * v, v, 1});
-    contract(s, "aiP,bjP->ijab", ONE, Vt, Vt, false, Z);
-    contract(s, "aiP,bjP->ijab", MONE, Vt, Vt, true, Zji);
+    // <ab||ij> = P_ij (ai|bj), and (ai|bj) = (bj|ai): half of the product under P_ij P_ab
+    contract(s, "aiP,bjP->ijab", HALF, Vt, Vt, false, view(w.R_, {o, o, v, v}));
     return;
   }
   auto H4 = view(w.H4, {v, o, o, v});
@@ -1175,7 +1173,7 @@ static int assemble(Handle& h, double* xt, double* e, double* s1, double* s2, do
   if (np > 0) {
     nb = assemble_t2_blocks(np);
     const bool cc2 = h.op.cc2 != 0;
-    k_assemble_t2<R>(cc2 ? nullptr : w.Znp, cc2 ? w.Z : nullptr, cc2 ? nullptr : w.R_, cc2 ? nullptr : h.Voovv_p,
+    k_assemble_t2<R>(cc2 ? nullptr : w.Znp, nullptr, w.R_, cc2 ? nullptr : h.Voovv_p,
                      h.x + 2 * ov, h.eps, o, v, shift,
                      xt ? xt + 2 * ov : nullptr, e ? e + 2 * ov : nullptr, s2,
                      s2 ? nullptr : h.red + 1, nb, h.s);

@@ -740,6 +740,9 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     x.exps = is_a ? ea : eb;
     return x;
   };
+  // a product of an operand with itself (the same element map) needs its residues once
+  const bool same = g.A == g.B && g.M == g.N && g.m_in == g.n_in && g.a_mo == g.b_no && g.a_mi == g.b_ni &&
+                    g.a_ko == g.b_ko && g.a_ki == g.b_ki && g.conj_a == g.conj_b && ma == mb && nr == nb;
   for (int k0 = 0; k0 < g.K; k0 += kMaxK) {
     const int kc = std::min(g.K - k0, kMaxK);
     Gett<double> h = g;
@@ -751,7 +754,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
         const bool do_a = n0 == 0, do_b = m0 == 0 || nr < nb;
         const Src a = src(true, Ap, m0, am, k0, kc), b = src(false, Bp, n0, bn, k0, kc);
         if (do_a)
-          split(a, do_b ? b : Src{}, s);
+          split(a, do_b && !same ? b : Src{}, s);
         else
           split(b, Src{}, s);
         for (int m1 = 0; m1 < am; m1 += mc)
@@ -761,7 +764,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
             pg.nb = std::min(nc, bn - n1);
             pg.kb = a.kb;
             pg.A = Ap + (int64_t)m1 * (a.kb / 2) * kPlanes * 2048;
-            pg.B = Bp + (int64_t)n1 * (b.kb / 2) * kPlanes * 2048;
+            pg.B = (same ? Ap : Bp) + (int64_t)n1 * (b.kb / 2) * kPlanes * 2048;
             pg.C = Cp;
             pg.a_in = pg.a_outer = pg.mb;
             pg.b_in = pg.b_outer = pg.nb;
@@ -769,7 +772,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
             const int64_t units = (int64_t)pg.mb * pg.nb;
             hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>(units, 65535)), dim3(256), 0, s,
                                reinterpret_cast<const int*>(Cp), pg.mb, pg.nb, 32 * (m0 + m1),
-                               32 * (n0 + n1), ea, eb, h, tab());
+                               32 * (n0 + n1), ea, same ? ea : eb, h, tab());
             HIPCHECK(hipGetLastError());
           }
       }
