@@ -109,9 +109,10 @@ class ModLadder {
 int bf16x3_split_k(int K);
 void split_rows_bf16x3(const float* src, int64_t rows, int64_t group, int64_t group_stride,
                        int64_t row_stride, int K, unsigned short* dst, hipStream_t s);
-// B row of column n: (n / b_in) * b_outer + n % b_in (b_in <= 0: row n)
+// A row of m: (m / a_in) * a_outer + m % a_in (a_in <= 0: row m); B row of column n likewise
 void gemm_bf16x3_split(const unsigned short* A, const unsigned short* B, int M, int N, int K, float* C,
-                       int64_t ldc, hipStream_t s, int b_in = 0, int64_t b_outer = 0);
+                       int64_t ldc, hipStream_t s, int b_in = 0, int64_t b_outer = 0, int a_in = 0,
+                       int64_t a_outer = 0);
 
 // ---------------------------------------------------------------------------
 // Bandwidth kernels (elementwise.hip).  Sizes in elements; complex arrays are
@@ -131,9 +132,10 @@ void k_ring_operands(const T* T2, const double* t1, T* Tq, T* Xp, int o, int v, 
                      const double* t1r = nullptr);
 template <typename T>
 void k_expand_c(const T* Vooov, const T* Cp, const T* Y, T* Cf, int o, int v, hipStream_t s);
-// W[b'][(c<d)] = Ta[c][b'][d] - Ta[d][b'][c] over c, d < v, rows of W ldw apart
+// W[b'][(c<d)] = Ta[c][b'][d] - Ta[d][b'][c] over c, d < v, rows of W ldw apart; for a group
+// of rows z, Ta[z][c][b'][d] with b' >= z used, their W rows one after another
 template <typename T>
-void k_ladder_antisym(const T* Ta, T* W, int nb, int v, int64_t ldw, hipStream_t s);
+void k_ladder_antisym(const T* Ta, T* W, int group, int nb, int v, int64_t ldw, hipStream_t s);
 // W[(a<b)][(c<d)] = Tf[a][c][b][d] - Tf[a][d][b][c] for all a < b (Tf: v^4, W: P_v x P_v)
 template <typename T>
 void k_ladder_antisym_all(const T* Tf, T* W, int v, hipStream_t s);

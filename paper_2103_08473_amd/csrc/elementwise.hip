@@ -226,6 +226,7 @@ __global__ void expand_c_kernel(const T* __restrict__ Vooov, const T* __restrict
   }
 }
 
+// A group of rows a (blockIdx.z; 1 for a single row):
 // W[b'][x=(c<d)] = Ta[c][b'][d] - Ta[d][b'][c] (row stride ldw).  One block per (b', c-tile,
 // d-tile) with c-tile <= d-tile: both Ta tiles are read along their contiguous last index
 // and the second is transposed through LDS, so every global access is coalesced.
@@ -241,7 +242,12 @@ __global__ void ladder_antisym_kernel(const T* __restrict__ Ta, T* __restrict__ 
     ++tc;
   }
   const int td = tc + rem;
-  const int64_t bp = blockIdx.y;
+  // row z of a group: its tile is z rows of c on, its b' start at z, its W rows follow the
+  // rows of the group's earlier members
+  const int64_t bp = blockIdx.y, zr = blockIdx.z;
+  if (bp < zr) return;
+  Ta += 2 * zr * v * nb * v;
+  W += 2 * (zr * nb - zr * (zr + 1) / 2) * ldw;
   const int c0 = 32 * tc, d0 = 32 * td;
   const int tx = threadIdx.x, ty = threadIdx.y;  // 32 x 8
   // stage Ta[d][b'][c] for d in d-tile, c in c-tile (contiguous in c) as [c - c0][d - d0]
@@ -717,11 +723,11 @@ void k_expand_c(const T* Vooov, const T* Cp, const T* Y, T* Cf, int o, int v, hi
 }
 
 template <typename T>
-void k_ladder_antisym(const T* Ta, T* W, int nb, int v, int64_t ldw, hipStream_t s) {
+void k_ladder_antisym(const T* Ta, T* W, int group, int nb, int v, int64_t ldw, hipStream_t s) {
   if (nb <= 0 || v < 2) return;
   const int nt = (v + 31) / 32;
   if (nb > 65535) raise(-5, "ladder row too long");
-  dim3 grid((unsigned)(nt * (nt + 1) / 2), (unsigned)nb), block(32, 8);
+  dim3 grid((unsigned)(nt * (nt + 1) / 2), (unsigned)nb, (unsigned)group), block(32, 8);
   hipLaunchKernelGGL(ladder_antisym_kernel<T>, grid, block, 0, s, Ta, W, nb, v, ldw);
   HIPCHECK(hipGetLastError());
 }
@@ -1207,7 +1213,7 @@ void k_pack_amplitudes(const double* t1, const double* t2, double* x, int o, int
   template void k_ring_operands<T>(const T*, const double*, T*, T*, int, int, hipStream_t,       \
                                    const double*);                                               \
   template void k_expand_c<T>(const T*, const T*, const T*, T*, int, int, hipStream_t);                    \
-  template void k_ladder_antisym<T>(const T*, T*, int, int, int64_t, hipStream_t);               \
+  template void k_ladder_antisym<T>(const T*, T*, int, int, int, int64_t, hipStream_t);               \
   template void k_ladder_antisym_all<T>(const T*, T*, int, hipStream_t);                          \
   template void k_transpose_tail<T>(const T*, int64_t, int64_t, int64_t, int64_t, T*, int64_t,       \
                                     hipStream_t);                                                 \

@@ -605,7 +605,7 @@ static void ladder_apply(Handle& h, const Work<R>& w, const R* F, int64_t row_st
     }
     {
       Scope sc(h, "ladder_antisym");
-      k_ladder_antisym<R>(w.Ta, w.W + 2 * rows * Pv, nb, v, Pv, s);
+      k_ladder_antisym<R>(w.Ta, w.W + 2 * rows * Pv, 1, nb, v, Pv, s);
     }
     rows += nb;
   }
@@ -678,26 +678,40 @@ static void ladder_apply_herm(Handle& h, const Work<R>& w, const R* F, int64_t r
         mod->rows(a0, ch.a1, a0, off, w.W, Pw, s);
       }
     }
-    for (int a = a0; a < ch.a1 && !on_mod; ++a) {
+    for (int a = a0; a < ch.a1 && !on_mod;) {
       const int nb = v - a - 1;
+      // FP32 types: several rows a in one product while one alone gives fewer than 4 tiles of
+      // 128 x 128 per CU (its pairs with b <= a of the group are formed for nothing), their
+      // tiles in the residue workspace, idle here.  16/120/360, BF16x3: 119 launches of about
+      // 27 us each, half the chip busy, and as many antisymmetrise passes per ladder.
+      int grp = 1;
+      R* T = w.Ta;
+      if constexpr (sizeof(R) == sizeof(float)) {
+        const int64_t row = (int64_t)wv * nb * wv * 8, room = h.mod_ws ? (int64_t)h.P.bytes_mod / row : 0;
+        auto tiles = [&](int g) { return (((int64_t)g * wv + 127) / 128) * (((int64_t)nb * wv + 127) / 128); };
+        while (grp < 16 && a + grp < ch.a1 && grp < room && tiles(grp) < 1024) ++grp;
+        if (grp > 1) T = reinterpret_cast<R*>(h.mod_ws);
+      }
       {
         Scope sc(h, "ladder_build");
         if (bf && use_bvs && h.Bvs) {  // pre-split rows B[(a, c)] and B[(b, d)], c, d >= a0
           const int64_t rs = 4 * (int64_t)bf16x3_split_k(X);
           gemm_bf16x3_split(h.Bvs + ((int64_t)a * v + a0) * rs, h.Bvs + ((int64_t)(a + 1) * v + a0) * rs,
-                            wv, nb * wv, X, reinterpret_cast<float*>(w.Ta), (int64_t)nb * wv, s, wv, v);
+                            grp * wv, nb * wv, X, reinterpret_cast<float*>(T), (int64_t)nb * wv, s, wv, v, wv, v);
         } else {
-          auto Ba = sview(const_cast<R*>(F) + 2 * ((int64_t)a * row_stride + (int64_t)a0 * X), {wv, X}, {X, 1});
+          auto Ba = sview(const_cast<R*>(F) + 2 * ((int64_t)a * row_stride + (int64_t)a0 * X), {grp, wv, X},
+                          {row_stride, X, 1});
           auto Bb = sview(const_cast<R*>(F) + 2 * ((int64_t)(a + 1) * row_stride + (int64_t)a0 * X),
                           {nb, wv, X}, {row_stride, X, 1});
-          contract(s, "cP,bdP->cbd", ONE, Ba, Bb, false, view(w.Ta, {wv, nb, wv}), lad_build);
+          contract(s, "acP,bdP->acbd", ONE, Ba, Bb, false, view(T, {grp, wv, nb, wv}), lad_build);
         }
       }
       {
         Scope sc(h, "ladder_antisym");
-        k_ladder_antisym<R>(w.Ta, w.W + 2 * xoff * Pw, nb, wv, Pw, s);
+        k_ladder_antisym<R>(T, w.W + 2 * xoff * Pw, grp, nb, wv, Pw, s);
       }
-      xoff += nb;
+      xoff += (int64_t)grp * nb - (int64_t)grp * (grp - 1) / 2;
+      a += grp;
     }
     Scope sc(h, "ladder_contract");
     auto Lt = sview(Lp.p + 2 * off, {Po, Pw}, {ldl, 1});

@@ -832,13 +832,14 @@ __global__ __launch_bounds__(256) void split_rows_kernel(const float* __restrict
   }
 }
 
-// C[m][n] = sum_k A[m][k] B[n][k] over pre-split rows (row strides 4*Kp bf16), B row of n at
-// (n / b_in) * b_outer + n % b_in, C complex FP32 row-major with leading dimension ldc
+// C[m][n] = sum_k A[m][k] B[n][k] over pre-split rows (row strides 4*Kp bf16), A row of m at
+// (m / a_in) * a_outer + m % a_in and B row of n likewise, C complex FP32 row-major with leading dimension ldc
 // (complex elements).  BM x BN workgroup tile, (BM/32) x (BN/32) waves of 32 x 32 outputs each.
 template <int BM, int BN, bool XCD>
 __global__ __launch_bounds__(64 * (BM / 32) * (BN / 32), (BM * BN == 64 * 64) ? 2 : 1) void
 gett_bf16x3_split_kernel(const unsigned short* __restrict__ A, const unsigned short* __restrict__ B, int M,
-                         int N, int Kp, float* __restrict__ C, int64_t ldc, int b_in, int64_t b_outer) {
+                         int N, int Kp, float* __restrict__ C, int64_t ldc, int b_in, int64_t b_outer,
+                         int a_in, int64_t a_outer) {
   constexpr int BK = 32;
   constexpr int WM = BM / 32, T = 64 * (BM / 32) * (BN / 32);
   constexpr int QA = BM * 16 / T, QB = BN * 16 / T, RS = T / 16;
@@ -861,8 +862,11 @@ gett_bf16x3_split_kernel(const unsigned short* __restrict__ A, const unsigned sh
   const u4v* pa[QA];
   const u4v* pb[QB];
 #pragma unroll
-  for (int q = 0; q < QA; ++q)
-    pa[q] = reinterpret_cast<const u4v*>(A + min(m0 + tid / 16 + RS * q, M - 1) * rs) + ch;
+  for (int q = 0; q < QA; ++q) {
+    const int m = min(m0 + tid / 16 + RS * q, M - 1);
+    const int mq = m / a_in;
+    pa[q] = reinterpret_cast<const u4v*>(A + ((int64_t)mq * a_outer + (m - mq * a_in)) * rs) + ch;
+  }
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
     const int n = min(n0 + tid / 16 + RS * q, N - 1);
@@ -964,8 +968,12 @@ void split_rows_bf16x3(const float* src, int64_t rows, int64_t group, int64_t gr
 }
 
 void gemm_bf16x3_split(const unsigned short* A, const unsigned short* B, int M, int N, int K, float* C,
-                       int64_t ldc, hipStream_t s, int b_in, int64_t b_outer) {
+                       int64_t ldc, hipStream_t s, int b_in, int64_t b_outer, int a_in, int64_t a_outer) {
   if (M <= 0 || N <= 0) return;
+  if (a_in <= 0) {  // A rows contiguous
+    a_in = M;
+    a_outer = M;
+  }
   if (b_in <= 0) {  // B rows contiguous
     b_in = N;
     b_outer = N;
@@ -977,7 +985,7 @@ void gemm_bf16x3_split(const unsigned short* A, const unsigned short* B, int M, 
   if (tiles > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
   hipLaunchKernelGGL((gett_bf16x3_split_kernel<BM, BN, true>), dim3((unsigned)tiles),
                      dim3(64 * (BM / 32) * (BN / 32)), 0, s, A, B, M, N, bf16x3_split_k(K), C, ldc,
-                     b_in, b_outer);
+                     b_in, b_outer, a_in, a_outer);
   HIPCHECK(hipGetLastError());
 }
 

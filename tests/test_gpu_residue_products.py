@@ -72,6 +72,24 @@ def test_lambda_with_and_without_residues(lib):
         assert np.abs(a - b).max() <= tol * np.abs(a).max()
 
 
+@pytest.mark.parametrize("mode", ["MIXED_BF16X3", "MIXED_FP32"])
+@pytest.mark.parametrize("o,v,X,pairs", [(4, 65, 200, 0), (5, 97, 131, 700), (3, 130, 128, 0)])
+def test_low_precision_ladder_rows_in_groups(lib, mode, o, v, X, pairs):
+    """The low-precision ladder builds several rows per product where the workspace (idle in
+    that phase) holds their tiles, one row without it: the same sums."""
+    from paper_2103_08473_amd import exacc
+    opts = dict(precision=getattr(exacc, mode), ladder_chunk_pairs=pairs)
+    base = exacc.memory_estimate(o, v, X, hbm_budget_bytes=1, **opts)
+    t = amplitudes(o, v, seed=2)
+    one = residual(o, v, X, base, t, **opts)
+    grouped = residual(o, v, X, 0, t, **opts)
+    for a, b in zip(one, grouped):
+        if mode == "MIXED_BF16X3":
+            assert (a == b).all()    # the same kernel per tile
+        else:  # tiles and splits differ with the size: FP32 sums of P_v terms
+            assert np.abs(a - b).max() <= np.sqrt(v * (v - 1) / 2) * 2.0 ** -23 * np.abs(a).max()
+
+
 def test_non_finite_amplitudes_stay_non_finite(lib):
     from paper_2103_08473_amd import exacc
     o, v, X = 13, 87, 259
