@@ -101,7 +101,7 @@ size_t fixed_bytes(int X) {
   return up256(256) + up256((size_t)(std::max<int64_t>(nb, X) + 8) * 8) +
          6 * up256((size_t)X * X * 16);
 }
-// Bytes of the two transform intermediates for a slice of ps spinor rows p.
+// Least bytes of intermediates that a call must find room for: one spinor row p of all Q.
 size_t slice_bytes(int m, int n, int X, int ps) {
   return up256((size_t)X * ps * m * 16) + up256((size_t)X * ps * n * 16);
 }
@@ -134,18 +134,66 @@ struct PlannerState {
   }
 };
 
-// B from device C, J, V with every temporary inside [base, base + cap): the fixed part,
-// the transform intermediates for slices of ps spinor rows (the widest that fits, at most
-// nspinor) and a split-K workspace of what is left, at most ws_cap.  Returns the
+// dst[r][x] = src[r * stride + x], rows of len complex elements
+__global__ void copy_rows_kernel(double* __restrict__ dst, const double* __restrict__ src, int64_t rows,
+                                 int64_t stride, int64_t len) {
+  typedef double d2v __attribute__((ext_vector_type(2)));
+  for (int64_t r = blockIdx.y; r < rows; r += gridDim.y)
+    for (int64_t x = (int64_t)blockIdx.x * kTB + threadIdx.x; x < len; x += (int64_t)gridDim.x * kTB)
+      reinterpret_cast<d2v*>(dst)[r * len + x] = reinterpret_cast<const d2v*>(src)[r * stride + x];
+}
+
+// Intermediates: the first half transform runs over chunks of Q (rows p too where one Q does not
+// fit) and is finished into B itself, and the metric product runs over column chunks of B
+// copied out first, so neither is held whole (7.7 GB at 600/400/1200, cleared by the driver
+// on each call; the extra copy is 1.5 ms).
+constexpr size_t kChunk = (size_t)128 << 20;
+size_t chunk_bytes(int m, int n, int X) {
+  return std::min(kChunk, up256((size_t)X * n * m * 16)) + std::min(kChunk, up256((size_t)X * n * n * 16));
+}
+size_t splitk_bytes(int X) { return std::min<size_t>((size_t)64 << 20, std::max<size_t>(1 << 20, (size_t)X * X * 256)); }
+
+// Host memory that one step's residual norm lands in while the next is on its way.
+struct Readback {
+  double* h = nullptr;
+  hipEvent_t ev[2] = {};
+  hipStream_t s;
+  explicit Readback(hipStream_t st) : s(st) {
+    HIPCHECK(hipHostMalloc((void**)&h, 4 * sizeof(double), hipHostMallocDefault));
+    for (auto& e : ev)
+      if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
+        release();
+        raise(-3, "DF factors: event creation failed");
+      }
+  }
+  void release() {
+    (void)hipStreamSynchronize(s);  // a copy may still be on its way
+    for (auto& e : ev)
+      if (e) (void)hipEventDestroy(e);
+    if (h) (void)hipHostFree(h);
+  }
+  ~Readback() { release(); }
+  Readback(const Readback&) = delete;
+  Readback& operator=(const Readback&) = delete;
+};
+
+// B from device C, J, V with every temporary inside [base, base + cap): the fixed part, the
+// intermediates' chunks and a split-K workspace of what is left, at most ws_cap; mod: residue
+// workspace of the large products (may be null).  Returns the
 // Newton-Schulz step count.  Nothing in the region needs to start at zero: every
 // temporary is written before it is read.
 int df_core(int m, int n, int X, const double* Cd, const double* Jd, const double* Vd, double* Bd,
-            hipStream_t s, char* base, size_t cap, size_t ws_cap) {
+            hipStream_t s, char* base, size_t cap, size_t ws_cap, void* mod, size_t mod_bytes) {
   const cplx ONE{1.0, 0.0};
   const size_t fixed = fixed_bytes(X);
   if (fixed + slice_bytes(m, n, X, 1) > cap) raise(-2, "DF factors: scratch region too small");
-  int ps = n;
-  while (ps > 1 && fixed + slice_bytes(m, n, X, ps) > cap) ps = std::max(1, ps / 2);
+  const int64_t nn = (int64_t)n * n;
+  const size_t room = (cap - fixed) / 2 / 256 * 256;
+  const size_t t1b = std::min(std::min(kChunk, up256((size_t)X * n * m * 16)), room);
+  const size_t mb = std::min(std::min(kChunk, up256((size_t)X * nn * 16)), room);
+  const int qc = (int)std::max<int64_t>(1, std::min<int64_t>(X, (int64_t)(t1b / ((size_t)n * m * 16))));
+  const int pc = (int)std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(t1b / ((size_t)qc * m * 16))));
+  const int64_t xc = std::max<int64_t>(1, std::min<int64_t>(nn, (int64_t)(mb / ((size_t)X * 16))));
   PlannerState ps_state;
   ps_state.add(Cd, (size_t)m * n * 16);
   ps_state.add(Jd, (size_t)X * m * m * 16);
@@ -162,59 +210,76 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
   double* T = cv.take((size_t)X * X * 16);
   double* Y2 = cv.take((size_t)X * X * 16);
   double* Z2 = cv.take((size_t)X * X * 16);
-  double* T1 = cv.take((size_t)X * ps * m * 16);
-  double* M = cv.take((size_t)X * ps * n * 16);
+  double* T1 = cv.take((size_t)qc * pc * m * 16);
+  double* M = cv.take((size_t)X * xc * 16);
   const size_t left = cap > cv.used ? (cap - cv.used) / 256 * 256 : 0;
   const size_t wsb = std::min(left, ws_cap);
   set_gett_workspace(wsb >= (1u << 20) ? cv.take(wsb) : nullptr, wsb >= (1u << 20) ? wsb : 0);
-  double h1 = 0.0;
-
+  set_mod_workspace(mod, mod_bytes);
+  Readback rb(s);
   // scale: c = max_i sum_j |V_ij| bounds the spectrum of the symmetric V from above
   hipLaunchKernelGGL(row_abs_sum_kernel, dim3(nblk(X, 1024)), dim3(kTB), 0, s, Vd, X, part);
   HIPCHECK(hipGetLastError());
   hipLaunchKernelGGL(max_kernel, dim3(1), dim3(kTB), 0, s, part, X, red);
   HIPCHECK(hipGetLastError());
-  HIPCHECK(hipMemcpyAsync(&h1, red, 8, hipMemcpyDeviceToHost, s));
+  HIPCHECK(hipMemcpyAsync(&rb.h[2], red, 8, hipMemcpyDeviceToHost, s));
   HIPCHECK(hipStreamSynchronize(s));
-  const double c = h1;
+  const double c = rb.h[2];
   if (!(c > 0.0) || !std::isfinite(c)) raise(-1, "DF factors: metric is zero or not finite");
   hipLaunchKernelGGL(ns_init_kernel, dim3(nb), dim3(kTB), 0, s, Vd, X, 1.0 / c, Y, Z);
   HIPCHECK(hipGetLastError());
 
   auto XXv = [&](double* p) { return view(p, {X, X}); };
-  int iters = 0;
-  bool done = false;
-  for (; iters < 200 && !done; ++iters) {
-    contract(s, "ab,bc->ac", ONE, XXv(Z), XXv(Y), false, XXv(P));
-    hipLaunchKernelGGL(ns_step_kernel, dim3(nb), dim3(kTB), 0, s, P, X, T, part);
+  // P = Z Y, T and the norm |I - P| of step k into rb.h[k % 2].  The norm of a step is waited
+  // for only once the next step's product is queued, so the host's turnaround is hidden; the
+  // next step's P and T are then formed for nothing after the last one.
+  auto look = [&](int k, double* Pk, double* Tk) {
+    contract(s, "ab,bc->ac", ONE, XXv(Z), XXv(Y), false, XXv(Pk));
+    hipLaunchKernelGGL(ns_step_kernel, dim3(nb), dim3(kTB), 0, s, Pk, X, Tk, part);
     HIPCHECK(hipGetLastError());
-    k_reduce_sum(part, nb, 1, red, s);
-    HIPCHECK(hipMemcpyAsync(&h1, red, 8, hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipStreamSynchronize(s));
-    const double r = std::sqrt(h1);
-    if (!std::isfinite(r) || r > 1e3 * X) break;
-    // quadratic phase: one more step takes the error to ~r^2 (rounding level)
-    if (r < 1e-8) done = true;
+    k_reduce_sum(part, nb, 1, red + k % 2, s);
+    HIPCHECK(hipMemcpyAsync(&rb.h[k % 2], red + k % 2, 8, hipMemcpyDeviceToHost, s));
+    HIPCHECK(hipEventRecord(rb.ev[k % 2], s));
+  };
+  int iters = 0;
+  bool done = false, failed = false;
+  look(0, P, T);
+  while (iters < 200 && !done && !failed) {
+    const int k = iters++;
     contract(s, "ab,bc->ac", ONE, XXv(Y), XXv(T), false, XXv(Y2));
     contract(s, "ab,bc->ac", ONE, XXv(T), XXv(Z), false, XXv(Z2));
     std::swap(Y, Y2);
     std::swap(Z, Z2);
+    if (iters < 200) look(iters, P, T);
+    HIPCHECK(hipEventSynchronize(rb.ev[k % 2]));
+    const double r = std::sqrt(rb.h[k % 2]);
+    // quadratic phase: the step just taken brought the error to ~r^2 (rounding level)
+    if (!std::isfinite(r) || r > 1e3 * X)
+      failed = true;
+    else
+      done = r < 1e-8;
   }
   if (!done)
     raise(-1, "DF factors: the inverse square root iteration did not converge (metric not positive "
               "definite or too ill-conditioned)");
 
-  // per slice of spinor rows p: (pq|Q) = sum_mu nu conj(C_mu p) (mu nu|Q) C_nu q, then
-  // B[P][p][q] = sum_Q [V^-1/2]_PQ (pq|Q)
-  const int64_t nn = (int64_t)n * n;
-  for (int p0 = 0; p0 < n; p0 += ps) {
-    const int pn = std::min(ps, n - p0);
-    contract(s, "mp,Qmn->Qpn", ONE, conj(sview(const_cast<double*>(Cd) + 2 * p0, {m, pn}, {n, 1})),
-             view(const_cast<double*>(Jd), {X, m, m}), false, view(T1, {X, pn, m}));
-    contract(s, "Qpn,nq->Qpq", ONE, view(T1, {X, pn, m}), view(const_cast<double*>(Cd), {m, n}), false,
-             view(M, {X, pn, n}));
-    contract(s, "PQ,Qx->Px", cplx{1.0 / std::sqrt(c), 0.0}, XXv(Z), view(M, {X, (int64_t)pn * n}), false,
-             sview(Bd + 2 * (int64_t)p0 * n, {X, (int64_t)pn * n}, {nn, 1}));
+  // (pq|Q) = sum_mu nu conj(C_mu p) (mu nu|Q) C_nu q into B, chunks of Q (and p); then
+  // B[P][p][q] = sum_Q [V^-1/2]_PQ (pq|Q), chunks of pq
+  for (int q0 = 0; q0 < X; q0 += qc)
+    for (int p0 = 0; p0 < n; p0 += pc) {
+      const int qn = std::min(qc, X - q0), pn = std::min(pc, n - p0);
+      contract(s, "mp,Qmn->Qpn", ONE, conj(sview(const_cast<double*>(Cd) + 2 * p0, {m, pn}, {n, 1})),
+               view(const_cast<double*>(Jd) + 2 * (int64_t)q0 * m * m, {qn, m, m}), false, view(T1, {qn, pn, m}));
+      contract(s, "Qpn,nq->Qpq", ONE, view(T1, {qn, pn, m}), view(const_cast<double*>(Cd), {m, n}), false,
+               sview(Bd + 2 * ((int64_t)q0 * nn + (int64_t)p0 * n), {qn, pn, n}, {nn, n, 1}));
+    }
+  for (int64_t x0 = 0; x0 < nn; x0 += xc) {
+    const int64_t xn = std::min<int64_t>(xc, nn - x0);
+    hipLaunchKernelGGL(copy_rows_kernel, dim3(nblk(xn, 64), std::min(X, 16384)), dim3(kTB), 0, s, M, Bd + 2 * x0,
+                       (int64_t)X, nn, xn);
+    HIPCHECK(hipGetLastError());
+    contract(s, "PQ,Qx->Px", cplx{1.0 / std::sqrt(c), 0.0}, XXv(Z), view(M, {X, xn}), false,
+             sview(Bd + 2 * x0, {X, xn}, {nn, 1}));
   }
   HIPCHECK(hipStreamSynchronize(s));
   return iters;
@@ -222,7 +287,7 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
 
 // Device memory of one allocating call, freed on every exit path.
 struct Owned {
-  void* p[5] = {};
+  void* p[6] = {};
   ~Owned() {
     for (void* q : p)
       if (q) (void)hipFree(q);
@@ -278,12 +343,25 @@ int df_factors_impl(int m, int n, int X, const double* C, const double* J, const
     Vd = reinterpret_cast<double*>(v);
     Bd = reinterpret_cast<double*>(own.alloc(3, bB));
   }
-  // every temporary in one region: the whole spinor range in one slice and a 64 MiB
-  // split-K workspace
-  const size_t wsb = (size_t)64 << 20;
-  const size_t cap = fixed_bytes(X) + slice_bytes(m, n, X, n) + wsb;
+  // every temporary in one region, no larger than its sizes need: allocations up to 16 MB
+  // take 0.02 ms here, larger ones 0.3 ms and more (0.04 to allocate, 0.27 to free 70 MB)
+  const size_t wsb = splitk_bytes(X);
+  const size_t cap = fixed_bytes(X) + std::max(chunk_bytes(m, n, X), slice_bytes(m, n, X, 1)) + wsb;
   char* region = own.alloc(4, cap);
-  const int iters = df_core(m, n, X, Cd, Jd, Vd, Bd, s, region, cap, wsb);
+  // residues of the transforms' and the metric product's operands, where that gains and leaves
+  // the device memory it takes to spare
+  size_t mod_bytes = 0;
+  if (mod_gemm_pays(n, (int64_t)X * m, m) || mod_gemm_pays(X, (int64_t)n * n, X)) {
+    mod_bytes = (size_t)768 << 20;
+    size_t fr = 0, tot = 0;
+    HIPCHECK(hipMemGetInfo(&fr, &tot));
+    if (2 * mod_bytes > fr || hipMalloc(&own.p[5], mod_bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      own.p[5] = nullptr;
+      mod_bytes = 0;
+    }
+  }
+  const int iters = df_core(m, n, X, Cd, Jd, Vd, Bd, s, region, cap, wsb, own.p[5], mod_bytes);
   if (!on_device) {
     HIPCHECK(hipMemcpyAsync(B, Bd, bB, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
@@ -299,7 +377,7 @@ int df_factors_noalloc_impl(int m, int n, int X, const double* C, const double* 
                   ", nspinor = " + std::to_string(n) + " need " + std::to_string(need) +
                   " bytes of scratch, above the static " + std::to_string((size_t)EXACC_DF_SCRATCH_BYTES));
   char* base = scratch_address();
-  return df_core(m, n, X, C, J, V, B, s, base, (size_t)EXACC_DF_SCRATCH_BYTES, (size_t)64 << 20);
+  return df_core(m, n, X, C, J, V, B, s, base, (size_t)EXACC_DF_SCRATCH_BYTES, (size_t)64 << 20, nullptr, 0);
 }
 
 }  // namespace exacc

@@ -628,18 +628,18 @@ inline int kblocks(int K) { return 2 * cdiv(K, 64); }
 
 }  // namespace
 
-// Estimated times (us).  FP64 GETT: 64 x 64 tiles at the 70 TFLOP/s it reaches, whole rounds of
-// tiles when they are few.  Here: four launches, splitting 15 ps per element, reconstruction
-// 15 ps per output, the plane products at 1.7 POP/s on 32 x 32 blocks.  Measured at the line
-// (us, FP64 GETT / this): 513 x 777 x 1025 94 / 89, 317 x 3000 x 951 158 / 126, 2000 x 2000 x
-// 504 271 / 200, 1131^3 217 / 143; under it 700^3 71 / 83, 7875 x 2268 x 126 342 / 480.
+// Estimated times (us).  FP64 GETT: 64 x 64 tiles at 62 TFLOP/s (55 to 72 reached).  Here: four
+// launches, splitting 15 ps per element, reconstruction 15 ps per output, the plane products at
+// 1.7 POP/s on 32 x 32 blocks.  Measured at the line (us, FP64 GETT / this): 900^3 138 / 107,
+// 400 x 19800 x 600 687 / 540, 4032 x 576 x 504 176 / 155, 190 x 9730 x 9730 2266 / 2215; under
+// it 640^3 59 / 66, 28224 x 168 x 504 391 / 440, 1131 x 1131 x 259 67 / 82.
 bool mod_gemm_pays(int64_t M, int64_t N, int64_t K) {
   if (M < 128 || N < 128 || K < 128) return false;
   auto up = [](int64_t x, int64_t m) { return (double)((x + m - 1) / m * m); };
-  const double t64 = 8.0 * up(M, 64) * up(N, 64) * (double)K / 70e6;
+  const double t64 = 8.0 * up(M, 64) * up(N, 64) * (double)K / 62e6;
   const double tm = 25.0 + (double)(M + N) * K * 15e-6 + (double)M * N * 15e-6 +
                     2.0 * kPlanes * up(M, 32) * up(N, 32) * up(K, 64) / 1.7e9;
-  return tm < 0.85 * t64;
+  return tm < 0.95 * t64;
 }
 
 int64_t mod_plane_bytes(int64_t rows, int64_t K) {
