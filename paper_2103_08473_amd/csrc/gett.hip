@@ -388,6 +388,111 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
     }
 }
 
+// 16 x 16 output tile, W waves that share out its k in steps of 4: every wave loads its MFMA
+// fragments straight from memory (a lane needs one complex value of each operand per step), U
+// steps ahead, so there is no LDS stage and no barrier until the waves' sums are added in a
+// fixed order.  For outputs of few tiles, where a kernel's time is its serial chain: 240 x 240
+// x 120 takes one load latency and 12 MFMA steps per wave instead of the eight load, barrier
+// and MFMA rounds of a 32 x 32 tile.
+template <typename R, int W>
+__global__ __launch_bounds__(64 * W, 4) void gett_tiny_kernel(Gett<R> g) {
+  typedef typename MF<R>::acc_t acc_t;
+  constexpr int U = 4;
+  __shared__ R red[W - 1][12][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int tiles_m = (g.M + 15) / 16;
+  const int m0 = (blockIdx.x % tiles_m) * 16, n0 = (blockIdx.x / tiles_m) * 16;
+  const int64_t batch = blockIdx.y;
+  const int kb = blockIdx.z * g.kslice;
+  const int ke = (g.K - kb) < g.kslice ? g.K : kb + g.kslice;
+  // rows past M (columns past N) are clamped: they feed only outputs that are not stored
+  const R* __restrict__ A =
+      g.A + 2 * (batch * g.a_b + cmap(min(m0 + (lane & 15), g.M - 1), g.m_div, g.a_mo, g.a_mi));
+  const R* __restrict__ B =
+      g.B + 2 * (batch * g.b_b + cmap(min(n0 + (lane & 15), g.N - 1), g.n_div, g.b_no, g.b_ni));
+  const KStep a_step(4 * W, g.k_in, g.a_ko, g.a_ki), b_step(4 * W, g.k_in, g.b_ko, g.b_ki);
+  int k = kb + 4 * w + (lane >> 4);
+  KWalk a_k, b_k;
+  a_k.off = cmap(k, g.k_div, g.a_ko, g.a_ki);
+  b_k.off = cmap(k, g.k_div, g.b_ko, g.b_ki);
+  a_k.r = b_k.r = k - (g.k_div.mul ? (int)(__umulhi((unsigned)k, g.k_div.mul) >> g.k_div.shift) : k) * g.k_in;
+  const R sa = g.conj_a ? R(-1) : R(1), sb = g.conj_b ? R(-1) : R(1);
+  acc_t aR = {0, 0, 0, 0}, aI = {0, 0, 0, 0}, aS = {0, 0, 0, 0};
+  C2<R> a[U], b[U], an[U], bn[U];
+  auto fetch = [&](C2<R>* x, C2<R>* y) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      x[u] = y[u] = C2<R>{R(0), R(0)};
+      if (k < ke) {
+        x[u] = ldc(A, a_k.off);
+        y[u] = ldc(B, b_k.off);
+      }
+      a_step.advance(a_k);
+      b_step.advance(b_k);
+      k += 4 * W;
+    }
+  };
+  const int steps = ke > kb ? (ke - kb + 4 * W - 1) / (4 * W) : 0, nb = (steps + U - 1) / U;
+  if (nb > 0) fetch(a, b);
+  for (int q = 0; q < nb; ++q) {
+    if (q + 1 < nb) fetch(an, bn);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const R ai = sa * a[u].y, bi = sb * b[u].y;
+      aR = MF<R>::mma(a[u].x, b[u].x, aR);
+      aI = MF<R>::mma(ai, bi, aI);
+      aS = MF<R>::mma(a[u].x + ai, b[u].x + bi, aS);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      a[u] = an[u];
+      b[u] = bn[u];
+    }
+  }
+  if (w > 0) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      red[w - 1][r][lane] = aR[r];
+      red[w - 1][4 + r][lane] = aI[r];
+      red[w - 1][8 + r][lane] = aS[r];
+    }
+  }
+  __syncthreads();
+  if (w > 0) return;
+#pragma unroll
+  for (int q = 0; q < W - 1; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      aR[r] += red[q][r][lane];
+      aI[r] += red[q][4 + r][lane];
+      aS[r] += red[q][8 + r][lane];
+    }
+  const int col = n0 + (lane & 15);
+  if (col >= g.N) return;
+  R* __restrict__ ws = g.ws + 2 * (((int64_t)blockIdx.z * gridDim.y + batch) * g.M) * g.N;
+  R* __restrict__ C = g.C + 2 * (batch * g.c_b + cmap(col, g.n_div, g.c_no, g.c_ni));
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int row = m0 + MF<R>::row(lane, r);
+    if (row >= g.M) continue;
+    const R xr = aR[r] - aI[r], xi = aS[r] - aR[r] - aI[r];
+    if (gridDim.z > 1) {  // split-K: raw partial sums, reduced by gett_splitk_reduce
+      const int64_t off = 2 * ((int64_t)row * g.N + col);
+      ws[off] = xr;
+      ws[off + 1] = xi;
+      continue;
+    }
+    R* c = C + 2 * cmap(row, g.m_div, g.c_mo, g.c_mi);
+    R yr = g.alpha_re * xr - g.alpha_im * xi, yi = g.alpha_re * xi + g.alpha_im * xr;
+    if (g.accumulate) {
+      yr += c[0];
+      yi += c[1];
+    }
+    c[0] = yr;
+    c[1] = yi;
+  }
+}
+
 // C[b](m, n) = alpha * sum_z ws[z][b][m][n] (+ C), fixed summation order.
 template <typename R>
 __global__ __launch_bounds__(256) void gett_splitk_reduce(Gett<R> g, int nz, int nb) {
@@ -480,7 +585,9 @@ static void launch_cfg(const Gett<R>& g, int nz_want, hipStream_t s) {
       }
     }
     dim3 grid((unsigned)tiles, nb, nz), block(256);
-    if (akf && bkf)
+    if constexpr (BM == 16)
+      hipLaunchKernelGGL((gett_tiny_kernel<R, 4>), grid, block, 0, s, h);
+    else if (akf && bkf)
       hipLaunchKernelGGL((gett_kernel<R, BM, BN, BK, DB, true, true, KIND>), grid, block, 0, s, h);
     else if (akf)
       hipLaunchKernelGGL((gett_kernel<R, BM, BN, BK, DB, true, false, KIND>), grid, block, 0, s, h);
@@ -500,30 +607,36 @@ static void launch_cfg(const Gett<R>& g, int nz_want, hipStream_t s) {
 }
 
 // Tile and split of an output with few 64 x 64 tiles.  Estimated time (us) with c workgroups
-// per CU and n k-steps of 32: 2.5 + n max(lat, c thr), plus the reduction launch and its
-// traffic; lat is one workgroup alone on its CU (its loads and LDS steps are a serial chain),
-// thr what a CU takes per workgroup when several share it.  FP64: 64 x 64 tiles lat 4.1, thr
-// 3.7; 32 x 32 tiles (one 16 x 16 block per wave) 1.4, 1.1.  FP32: 2.7, 2.2 and 1.1, 0.65.
-// Measured (us), 64 x 64 with its best split against this choice: 240 x 240 x 120 12.8 / 9.5,
-// 40 x 40 x 1440 40 / 13.4, 15 x 780 x 15 8.8 / 4.0, 1131 x 169 x 259 24.9 / 17.0.
+// per CU and n k-steps: t0 + n max(lat, c thr), plus the reduction launch and its traffic; lat
+// is one workgroup alone on its CU (its loads and steps are a serial chain), thr what a CU
+// takes per workgroup when several share it.  Steps are 32 k in 64 x 64 and 32 x 32 tiles
+// (one 16 x 16 block per wave), 16 k in 16 x 16 tiles (gett_tiny_kernel).
+// Measured (us), FP64, 64 x 64 tiles with their best split / 32 x 32 / 16 x 16: 240 x 240 x 120
+// 12.6 / 9.5 / 5.7, 240 x 240 x 240 15.5 / 10.7 / 8.0, 40 x 40 x 1440 40 / 13.8 / 10.7, 549 x 549
+// x 183 22.5 / 18.6 / 15.5, 549 x 549 x 549 43 / 37.7 / 42.7, 1131 x 1131 x 259 71 / 57 / 81.
+struct TileCost {
+  int tile, step;
+  double t0, lat, thr;
+};
 template <typename R>
 static bool few_tiles(const Gett<R>& g, int& tile, int& nz) {
   auto up = [](int64_t x, int64_t y) { return (x + y - 1) / y; };
   if (!g_ws || up(g.M, 64) * up(g.N, 64) * g.nbatch > 640) return false;
-  constexpr bool dp = sizeof(R) == 8;
+  static const TileCost dp[] = {{16, 16, 3.5, 0.27, 0.22}, {32, 32, 2.5, 1.4, 1.1}, {64, 32, 2.5, 4.1, 3.7}};
+  static const TileCost sp[] = {{16, 16, 3.2, 0.24, 0.13}, {32, 32, 2.5, 1.1, 0.65}, {64, 32, 2.5, 2.7, 2.2}};
   static const int zs[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
   double best = 1e300;
-  for (int t = 32; t <= 64; t += 32) {
-    const double lat = t == 64 ? (dp ? 4.1 : 2.7) : (dp ? 1.4 : 1.1), thr = t == 64 ? (dp ? 3.7 : 2.2) : (dp ? 1.1 : 0.65);
-    const int64_t wgs = up(g.M, t) * up(g.N, t) * g.nbatch;
+  for (const TileCost& t : sizeof(R) == 8 ? dp : sp) {
+    const int64_t wgs = up(g.M, t.tile) * up(g.N, t.tile) * g.nbatch;
     for (int z : zs) {
       if (z > 1 && z * 32 > g.K) break;
-      const double n = (double)up(up(g.K > 0 ? g.K : 1, z), 32), c = (double)up(wgs * z, 256);
+      const double n = (double)up(up(g.K > 0 ? g.K : 1, z), t.step), c = (double)up(wgs * z, 256);
       const double mn = (double)g.M * g.N * g.nbatch;
-      const double us = 2.5 + n * std::max(lat, c * thr) + (z > 1 ? 3.5 + 0.08 * z + 4.0 * sizeof(R) * z * mn / 10e6 : 0.0);
+      const double us = t.t0 + n * std::max(t.lat, c * t.thr) +
+                        (z > 1 ? 3.5 + 0.08 * z + 4.0 * sizeof(R) * z * mn / 10e6 : 0.0);
       if (us < best) {
         best = us;
-        tile = t;
+        tile = t.tile;
         nz = z;
       }
     }
@@ -537,7 +650,10 @@ static void launch_tiles(const Gett<R>& g, hipStream_t s) {
   // two buffers.  Both fill 65 KB (FP64) / 33 KB (FP32) of LDS per workgroup.
   constexpr bool dp = sizeof(R) == 8;
   int tile = 64, nz = 0;
-  if (few_tiles(g, tile, nz) && tile == 32)
+  const bool few = few_tiles(g, tile, nz);
+  if (few && tile == 16)
+    launch_cfg<R, 16, 16, 16, false, GETT_GENERIC>(g, nz, s);
+  else if (few && tile == 32)
     launch_cfg<R, 32, 32, dp ? 16 : 32, true, GETT_GENERIC>(g, nz, s);
   else
     launch_cfg<R, 64, 64, dp ? 32 : 16, !dp, KIND>(g, nz, s);
