@@ -53,6 +53,7 @@ struct Gett {
   int kslice;  // split-K: workgroup z covers k in [z*kslice, min(K, (z+1)*kslice))
   R* ws;       // split-K partial sums [z][batch][m][n] (unscaled)
   FastDiv m_div, n_div, k_div;  // of m_in, n_in, k_in (filled at launch)
+  int tri;  // if not 0: only outputs with n / tri > m / tri are wanted (others may be left unset)
 };
 
 // Scratch the calling thread's GETT launches may use for split-K partials.
@@ -109,10 +110,11 @@ class ModLadder {
 int bf16x3_split_k(int K);
 void split_rows_bf16x3(const float* src, int64_t rows, int64_t group, int64_t group_stride,
                        int64_t row_stride, int K, unsigned short* dst, hipStream_t s);
-// A row of m: (m / a_in) * a_outer + m % a_in (a_in <= 0: row m); B row of column n likewise
+// A row of m: (m / a_in) * a_outer + m % a_in (a_in <= 0: row m); B row of column n likewise;
+// tri as in Gett
 void gemm_bf16x3_split(const unsigned short* A, const unsigned short* B, int M, int N, int K, float* C,
                        int64_t ldc, hipStream_t s, int b_in = 0, int64_t b_outer = 0, int a_in = 0,
-                       int64_t a_outer = 0);
+                       int64_t a_outer = 0, int tri = 0);
 
 // ---------------------------------------------------------------------------
 // Bandwidth kernels (elementwise.hip).  Sizes in elements; complex arrays are

@@ -117,7 +117,7 @@ struct Peeled {
 template <typename R>
 static void contract_impl(hipStream_t s, const std::string& la, const std::string& lb,
                           const std::string& lc, cplx alpha, const TV<R>& A, const TV<R>& B,
-                          bool accumulate, const TV<R>& C, int kind, const Peeled& peeled = {}) {
+                          bool accumulate, const TV<R>& C, int kind, int tri, const Peeled& peeled = {}) {
   const std::string sp = la + "," + lb + "->" + lc;
   const TV<R>* T[3] = {&A, &B, &C};
   const std::string* L[3] = {&la, &lb, &lc};
@@ -197,7 +197,7 @@ static void contract_impl(hipStream_t s, const std::string& la, const std::strin
       drop(la, A, 0, a2, la2);
       drop(lb, B, 0, b2, lb2);
       drop(lc, C, 0, c2, lc2);
-      contract_impl(s, la2, lb2, lc2, alpha, a2, b2, accumulate, c2, kind, pb);
+      contract_impl(s, la2, lb2, lc2, alpha, a2, b2, accumulate, c2, kind, 0, pb);
       return;
     }
     for (int64_t q = 0; q < pdim; ++q) {
@@ -206,7 +206,7 @@ static void contract_impl(hipStream_t s, const std::string& la, const std::strin
       drop(la, A, q, a2, la2);
       drop(lb, B, q, b2, lb2);
       drop(lc, C, q, c2, lc2);
-      contract_impl(s, la2, lb2, lc2, alpha, a2, b2, accumulate || (summed && q > 0), c2, kind, peeled);
+      contract_impl(s, la2, lb2, lc2, alpha, a2, b2, accumulate || (summed && q > 0), c2, kind, 0, peeled);
     }
     return;
   }
@@ -235,6 +235,7 @@ static void contract_impl(hipStream_t s, const std::string& la, const std::strin
   g.conj_a = A.conj;
   g.conj_b = B.conj;
   g.accumulate = accumulate ? 1 : 0;
+  g.tri = tri;
   g.alpha_re = (R)alpha.re;
   g.alpha_im = (R)alpha.im;
   // batch: inner level is the launch batch, outer level (if any) a host loop
@@ -260,7 +261,7 @@ static void contract_impl(hipStream_t s, const std::string& la, const std::strin
 
 template <typename R>
 void contract(hipStream_t s, const char* spec, cplx alpha, const TV<R>& A, const TV<R>& B,
-              bool accumulate, const TV<R>& C, int kind) {
+              bool accumulate, const TV<R>& C, int kind, int tri) {
   std::string sp(spec);
   const size_t comma = sp.find(','), arrow = sp.find("->");
   if (comma == std::string::npos || arrow == std::string::npos || arrow < comma)
@@ -269,12 +270,12 @@ void contract(hipStream_t s, const char* spec, cplx alpha, const TV<R>& A, const
   check_extent(B, "B", sp);
   check_extent(C, "C", sp);
   contract_impl(s, sp.substr(0, comma), sp.substr(comma + 1, arrow - comma - 1),
-                sp.substr(arrow + 2), alpha, A, B, accumulate, C, kind);
+                sp.substr(arrow + 2), alpha, A, B, accumulate, C, kind, tri);
 }
 
 template void contract<double>(hipStream_t, const char*, cplx, const TV<double>&, const TV<double>&,
-                               bool, const TV<double>&, int);
+                               bool, const TV<double>&, int, int);
 template void contract<float>(hipStream_t, const char*, cplx, const TV<float>&, const TV<float>&,
-                              bool, const TV<float>&, int);
+                              bool, const TV<float>&, int, int);
 
 }  // namespace exacc

@@ -63,9 +63,9 @@ void set_alloc_registry(const AllocRange* r, int n);
 
 // C = alpha * einsum(spec, A, B) (+ C if accumulate).  spec is "ab,bc->ac":
 // every label of C must occur in A or B; labels in A and B but not C are
-// summed; labels in all three are a batch.  Throws on unsupported layouts.
+// summed; labels in all three are a batch.  Throws on unsupported layouts.  tri: see Gett.
 template <typename R>
 void contract(hipStream_t s, const char* spec, cplx alpha, const TV<R>& A, const TV<R>& B,
-              bool accumulate, const TV<R>& C, int kind = GETT_GENERIC);
+              bool accumulate, const TV<R>& C, int kind = GETT_GENERIC, int tri = 0);
 
 }  // namespace exacc

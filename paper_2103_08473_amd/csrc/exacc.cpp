@@ -521,8 +521,8 @@ static void ladder_apply_herm(Handle& h, const Work<R>& w, const R* F, int64_t r
                               const TV<R>& Lp, R* Znp, bool bf, bool use_bvs);
 // Small nvir (plan.ladder_grouped): all virtual rows in three launches instead of two per
 // row, the per-row products being too small to fill the chip.  T[a][c][b][d] = sum_P F_ac F_bd
-// over all a, b, c, d in one product (v^4 naux complex multiply-adds against the Hermitian
-// build's v^4 naux / 4, cheap at this size), W[(a<b)][(c<d)] = T[a][c][b][d] - T[a][d][b][c]
+// over all c, d and the tiles with some b > a in one product (v^4 naux / 2 complex
+// multiply-adds against the Hermitian build's v^4 naux / 4, cheap at this size), W[(a<b)][(c<d)] = T[a][c][b][d] - T[a][d][b][c]
 // in one pass, then Znp += Lp W^T.  Needs no Hermitian factors.
 template <typename R>
 static void ladder_apply_grouped(Handle& h, const Work<R>& w, const R* F, int64_t row_stride,
@@ -533,11 +533,11 @@ static void ladder_apply_grouped(Handle& h, const Work<R>& w, const R* F, int64_
   {
     Scope sc(h, "ladder_build");
     if (bf && use_bvs && h.Bvs) {  // pre-split rows (a, c), all v^2 of them contiguous
-      gemm_bf16x3_split(h.Bvs, h.Bvs, (int)vv, (int)vv, X, reinterpret_cast<float*>(w.Ta), vv, s);
+      gemm_bf16x3_split(h.Bvs, h.Bvs, (int)vv, (int)vv, X, reinterpret_cast<float*>(w.Ta), vv, s, 0, 0, 0, 0, v);
     } else {
       auto Fv = sview(const_cast<R*>(F), {v, v, X}, {row_stride, X, 1});
       contract(s, "acP,bdP->acbd", ONE, Fv, Fv, false, view(w.Ta, {v, v, v, v}),
-               bf ? GETT_LADDER_BUILD_BF16X3 : GETT_LADDER_BUILD);
+               bf ? GETT_LADDER_BUILD_BF16X3 : GETT_LADDER_BUILD, v);
     }
   }
   {

@@ -119,6 +119,7 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
   const int tm = bid % tiles_m;
   const int tn = bid / tiles_m;
   const int m0 = tm * BM, n0 = tn * BN;
+  if (g.tri && (min(n0 + BN, g.N) - 1) / g.tri <= m0 / g.tri) return;
   const int64_t batch = blockIdx.y;
   const R* __restrict__ A = g.A + 2 * batch * g.a_b;
   const R* __restrict__ B = g.B + 2 * batch * g.b_b;
@@ -402,6 +403,7 @@ __global__ __launch_bounds__(64 * W, 4) void gett_tiny_kernel(Gett<R> g) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tiles_m = (g.M + 15) / 16;
   const int m0 = (blockIdx.x % tiles_m) * 16, n0 = (blockIdx.x / tiles_m) * 16;
+  if (g.tri && (min(n0 + 16, g.N) - 1) / g.tri <= m0 / g.tri) return;
   const int64_t batch = blockIdx.y;
   const int kb = blockIdx.z * g.kslice;
   const int ke = (g.K - kb) < g.kslice ? g.K : kb + g.kslice;
@@ -501,10 +503,23 @@ __global__ __launch_bounds__(256) void gett_splitk_reduce(Gett<R> g, int nz, int
     const int64_t b = t / MN, mn = t - b * MN;
     const int m = (int)(mn / g.N), n = (int)(mn - (int64_t)m * g.N);
     R sr = 0, si = 0;
-    for (int z = 0; z < nz; ++z) {
-      const R* w = g.ws + 2 * (((int64_t)z * nb + b) * MN + mn);
-      sr += w[0];
-      si += w[1];
+    const R* w = g.ws + 2 * (b * MN + mn);
+    const int64_t zs = 2 * (int64_t)nb * MN;
+    int z = 0;
+    for (; z + 8 <= nz; z += 8) {  // eight loads in flight, added in order
+      C2<R> v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = ldc(w + (z + q) * zs, 0);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        sr += v[q].x;
+        si += v[q].y;
+      }
+    }
+    for (; z < nz; ++z) {
+      const C2<R> v = ldc(w + z * zs, 0);
+      sr += v.x;
+      si += v.y;
     }
     R* c = g.C + 2 * (b * g.c_b + cmap(m, g.m_div, g.c_mo, g.c_mi) + cmap(n, g.n_div, g.c_no, g.c_ni));
     R yr = g.alpha_re * sr - g.alpha_im * si;
@@ -559,7 +574,7 @@ static void launch_cfg(const Gett<R>& g, int nz_want, hipStream_t s) {
     // long K on an output that does not fill the chip by itself: slices of >= 256 k in whole
     // rounds of workgroups (two per CU, 512 at a time): nz slices take ceil(wgs nz / 512)
     // rounds of K / nz each; the smallest nz within 2% of the best rounds / nz
-    const bool long_k = nz_want == 0 && wgs < 1024 && g.K >= 1024;
+    const bool long_k = nz_want == 0 && wgs < 1024 && g.K >= 1024 && !g.tri;
     if (g_ws && (long_k || nz_want > 1)) {
       const int64_t per = (int64_t)g.M * g.N * nb * 2 * (int64_t)sizeof(R);
       const int64_t cap = per > 0 ? (int64_t)(g_ws_bytes / per) : 0;
@@ -629,7 +644,7 @@ static bool few_tiles(const Gett<R>& g, int& tile, int& nz) {
   for (const TileCost& t : sizeof(R) == 8 ? dp : sp) {
     const int64_t wgs = up(g.M, t.tile) * up(g.N, t.tile) * g.nbatch;
     for (int z : zs) {
-      if (z > 1 && z * 32 > g.K) break;
+      if (z > 1 && (z * 32 > g.K || g.tri)) break;  // a split sum needs every tile
       const double n = (double)up(up(g.K > 0 ? g.K : 1, z), t.step), c = (double)up(wgs * z, 256);
       const double mn = (double)g.M * g.N * g.nbatch;
       const double us = t.t0 + n * std::max(t.lat, c * t.thr) +
@@ -955,7 +970,7 @@ template <int BM, int BN, bool XCD>
 __global__ __launch_bounds__(64 * (BM / 32) * (BN / 32), (BM * BN == 64 * 64) ? 2 : 1) void
 gett_bf16x3_split_kernel(const unsigned short* __restrict__ A, const unsigned short* __restrict__ B, int M,
                          int N, int Kp, float* __restrict__ C, int64_t ldc, int b_in, int64_t b_outer,
-                         int a_in, int64_t a_outer) {
+                         int a_in, int64_t a_outer, int tri) {
   constexpr int BK = 32;
   constexpr int WM = BM / 32, T = 64 * (BM / 32) * (BN / 32);
   constexpr int QA = BM * 16 / T, QB = BN * 16 / T, RS = T / 16;
@@ -969,6 +984,7 @@ gett_bf16x3_split_kernel(const unsigned short* __restrict__ A, const unsigned sh
   const int tiles_m = (M + BM - 1) / BM;
   const int tile = XCD ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
   const int m0 = (tile % tiles_m) * BM, n0 = (tile / tiles_m) * BN;
+  if (tri && (min(n0 + BN, N) - 1) / tri <= m0 / tri) return;
   const int64_t rs = 4 * (int64_t)Kp;  // bf16 per row
 
   // loader: chunk tid%16 (k block (tid%16)/4, plane tid%4) of tile rows
@@ -1084,7 +1100,8 @@ void split_rows_bf16x3(const float* src, int64_t rows, int64_t group, int64_t gr
 }
 
 void gemm_bf16x3_split(const unsigned short* A, const unsigned short* B, int M, int N, int K, float* C,
-                       int64_t ldc, hipStream_t s, int b_in, int64_t b_outer, int a_in, int64_t a_outer) {
+                       int64_t ldc, hipStream_t s, int b_in, int64_t b_outer, int a_in, int64_t a_outer,
+                       int tri) {
   if (M <= 0 || N <= 0) return;
   if (a_in <= 0) {  // A rows contiguous
     a_in = M;
@@ -1101,7 +1118,7 @@ void gemm_bf16x3_split(const unsigned short* A, const unsigned short* B, int M, 
   if (tiles > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
   hipLaunchKernelGGL((gett_bf16x3_split_kernel<BM, BN, true>), dim3((unsigned)tiles),
                      dim3(64 * (BM / 32) * (BN / 32)), 0, s, A, B, M, N, bf16x3_split_k(K), C, ldc,
-                     b_in, b_outer, a_in, a_outer);
+                     b_in, b_outer, a_in, a_outer, tri);
   HIPCHECK(hipGetLastError());
 }
 
