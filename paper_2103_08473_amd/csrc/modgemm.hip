@@ -4,11 +4,11 @@
 // 0.8 to 0.95 of it on large products.  The INT8 rate is about 64 times higher, so a large
 // product is formed exactly on integers instead, in a residue number system:
 //   * every operand row a_m is scaled by a power of two to the 2-norm range (2^(S-1), 2^S]
-//     and rounded to integers (S = kS bits, more than the 53 of a double);
+//     and rounded to integers (S = 55 or 58 bits, more than the 53 of a double);
 //   * modulo a prime (or product of primes) p = 1 mod 4 there is j with j^2 = -1, and a
 //     complex integer x + iy is held as the pair (x + jy, x - jy) mod p: in this form a
 //     complex product is two real products (the quadratic residue number system of
-//     Leung and of Jenkins and Krogmeier), so kNP moduli give 2 kNP independent INT8 planes;
+//     Leung and of Jenkins and Krogmeier), so 15 or 16 moduli give 30 or 32 INT8 planes;
 //   * per plane one INT8 GEMM with INT32 accumulation (exact: |sum| <= K (p/2)^2 < 2^31 for
 //     K <= kMaxK), reduced mod p to one byte per output;
 //   * the Chinese remainder theorem gives the exact integer product back: by the
@@ -26,9 +26,8 @@
 namespace exacc {
 namespace {
 
-constexpr int kNP = 16;
+constexpr int kNP = 16;           // most moduli; see moduli_for
 constexpr int kPlanes = 2 * kNP;
-constexpr int kS = 58;            // 2^(2 kS) (1 + 2^-40) < M / 2
 constexpr int kMaxK = 131072;     // K (p / 2)^2 < 2^31 with p <= 241
 constexpr int kShortK = 1152;     // K (p / 2)^2 + 128 < 2^24
 constexpr int kNaN = 0x40000000;  // exponent of a row that holds a non-finite element
@@ -42,6 +41,8 @@ typedef unsigned __int128 u128;
 constexpr int kMods[16] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97};
 
 struct ModTab {
+  int np;  // moduli in use
+  int S;   // operand bits: 2^(2 S) (1 + 2^-40) < M / 2
   int p[kNP];
   float pf[kNP], ipf[kNP];  // p, 1 / p
   int w[kNP][4];  // 256^d mod p (d = 0..7, one byte each), then j 256^d mod p
@@ -55,11 +56,14 @@ constexpr int inv_mod(int a, int p) {
   return 0;
 }
 
-ModTab make_tab() {
+ModTab make_tab(int np) {
   ModTab t{};
+  t.np = np;
   u128 M = 1;
-  for (int i = 0; i < kNP; ++i) M *= (u128)kMods[i];
-  for (int i = 0; i < kNP; ++i) {
+  for (int i = 0; i < np; ++i) M *= (u128)kMods[i];
+  u128 top = 1;
+  for (t.S = 0; top * 4 < M / 2 - M / 64; ++t.S) top *= 4;  // 3% left for the rounding of operands
+  for (int i = 0; i < np; ++i) {
     const int p = kMods[i];
     int j = 1;
     while ((j * j + 1) % p) ++j;
@@ -96,9 +100,19 @@ ModTab make_tab() {
   return t;
 }
 
-const ModTab& tab() {
-  static const ModTab t = make_tab();
-  return t;
+// 15 moduli (S = 55) or 16 (S = 58).  The operands' rounding grows with sqrt(K) like the FP64
+// GETT's sums do, and 15 moduli stay below those (relative rms error of re / im against
+// 80-bit sums, FP64 GETT | 15 moduli: K 504 7.0e-16 / 1.2e-15 | 5.4e-16, 1131 6.4e-16 / 1.1e-15 |
+// 7.2e-16, 4032 2.1e-15 / 3.8e-15 | 1.5e-15, 8000 1.7e-15 / 3.0e-15 | 1.5e-15) but where the
+// FP64 GETT splits a long K into short chains (600 x 700 x 40000 1.7e-15 / 2.9e-15 | 5.9e-15):
+// there 16 are taken (7.2e-16).
+const ModTab& tab(int np) {
+  static const ModTab t15 = make_tab(15), t16 = make_tab(16);
+  return np == 15 ? t15 : t16;
+}
+int moduli_for(int64_t M, int64_t N, int64_t K) {
+  const bool split = ((M + 63) / 64) * ((N + 63) / 64) < 1024;
+  return K <= 8192 || !split ? 15 : 16;
 }
 
 __device__ __forceinline__ int64_t cmap(int x, int in, int64_t so, int64_t si) {
@@ -127,7 +141,7 @@ struct Src {
 // Scale exponents: per row the largest |component| and the sum of squares (fixed order).
 // kfast: tpr threads per row; else 32 rows x 32 k phases per workgroup.  Bound by reading
 // the operand once.
-__global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src b, int tpr_a, int tpr_b) {
+__global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src b, int tpr_a, int tpr_b, int S) {
   const bool first = (int)blockIdx.x < blocks_a;
   const Src s = first ? a : b;
   const int blk = first ? blockIdx.x : blockIdx.x - blocks_a;
@@ -190,7 +204,7 @@ __global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src
         (void)frexp(mx, &ex);
         ex += (33 - __clz(2 * s.K)) >> 1;
       }
-      e = kS - ex;
+      e = S - ex;
     }
     s.exps[row] = e;
   }
@@ -249,7 +263,7 @@ __global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src
 #pragma unroll
   for (int q = 0; q < 16; ++q) x[q] = sv[lane & 31][kblk * 32 + (lane >> 5) * 16 + q];
   signed char* out = s.planes + (int64_t)blk * (kPlanes * 2048) + kblk * 1024 + lane * 16;
-  for (int i = half; i < kNP; i += 2) {
+  for (int i = half; i < t.np; i += 2) {
     const float pf = t.pf[i], ipf = t.ipf[i], off = -128.0f * ipf;
     const int w0 = t.w[i][0], w1 = t.w[i][1], j0 = t.w[i][2], j1 = t.w[i][3];
     i4v u, v;
@@ -298,6 +312,7 @@ struct PlaneGemm {
   int a_in, a_outer;           // A block of m-block x: (x / a_in) * a_outer + x % a_in
   int b_in, b_outer;           // likewise B
   int tiles_m, tiles_n;
+  int planes;                  // 2 np of the kPlanes that the layouts have room for
   int p[kNP];
 };
 
@@ -318,7 +333,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
   __shared__ i4v sm[S][(RA + RB) * KB * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w % WM, wn = w / WM;
-  const int tiles = g.tiles_m * g.tiles_n, total = tiles * kPlanes;
+  const int tiles = g.tiles_m * g.tiles_n, total = tiles * g.planes;
   const int64_t rs = (int64_t)g.kb / 2 * kPlanes * 128;  // 16-byte units per row block
   const int nk = g.kb / KB;
   const i4v* pa[NA];
@@ -448,6 +463,7 @@ __device__ __forceinline__ Frac4 crt4(const int* c, const ModTab& t) {
   double hr[4] = {0, 0, 0, 0}, lr[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0}, li[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int i = 0; i < kNP; ++i) {
+    if (i >= 15 && i >= t.np) break;
     const int u = c[(2 * i) * 256], v = c[(2 * i + 1) * 256];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -573,12 +589,12 @@ int norm_blocks(const Src& s) {
 }
 
 // Scale and split one or two operands (b may have rows == 0).
-void split(const Src& a, const Src& b, hipStream_t s) {
+void split(const Src& a, const Src& b, const ModTab& t, hipStream_t s) {
   const int na = norm_blocks(a), nb = b.rows ? norm_blocks(b) : 0;
-  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b));
+  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), t.S);
   HIPCHECK(hipGetLastError());
   const int sa = a.rb * (a.kb / 2), sb = b.rows ? b.rb * (b.kb / 2) : 0;
-  hipLaunchKernelGGL(mod_split_kernel, dim3(sa + sb), dim3(256), 0, s, a, sa, b, tab());
+  hipLaunchKernelGGL(mod_split_kernel, dim3(sa + sb), dim3(256), 0, s, a, sa, b, t);
   HIPCHECK(hipGetLastError());
 }
 
@@ -587,7 +603,7 @@ template <int WM, int WN, int TM, int TN, int OCC, int RES>
 void launch_planes(PlaneGemm g, hipStream_t s) {
   g.tiles_m = cdiv(g.mb, WM * TM);
   g.tiles_n = cdiv(g.nb, WN * TN);
-  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * kPlanes;
+  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * g.planes;
   if (jobs > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
   const dim3 grid((unsigned)std::min<int64_t>(jobs, 256 * RES)), block(64 * WM * WN);
   if (32 * g.kb <= kShortK)
@@ -603,7 +619,7 @@ void gemm_planes(PlaneGemm g, hipStream_t s) {
   if (g.kb < 4) raise(-1, "residue product: K too short for its pipeline");  // two stages at least
   for (int i = 0; i < kNP; ++i) g.p[i] = kMods[i];
   auto cost = [&](int ra, int rb, int resident, double rate) {
-    const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * kPlanes;
+    const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * g.planes;
     const double rounds = wgs >= 8 * resident ? (double)wgs / resident : (double)((wgs + resident - 1) / resident);
     return rounds * resident * ra * rb / rate;
   };
@@ -740,6 +756,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     x.exps = is_a ? ea : eb;
     return x;
   };
+  const ModTab& t = tab(moduli_for(g.M, g.N, g.K));
   // a product of an operand with itself (the same element map) needs its residues once
   const bool same = g.A == g.B && g.M == g.N && g.m_in == g.n_in && g.a_mo == g.b_no && g.a_mi == g.b_ni &&
                     g.a_ko == g.b_ko && g.a_ki == g.b_ki && g.conj_a == g.conj_b && ma == mb && nr == nb;
@@ -754,15 +771,16 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
         const bool do_a = n0 == 0, do_b = m0 == 0 || nr < nb;
         const Src a = src(true, Ap, m0, am, k0, kc), b = src(false, Bp, n0, bn, k0, kc);
         if (do_a)
-          split(a, do_b && !same ? b : Src{}, s);
+          split(a, do_b && !same ? b : Src{}, t, s);
         else
-          split(b, Src{}, s);
+          split(b, Src{}, t, s);
         for (int m1 = 0; m1 < am; m1 += mc)
           for (int n1 = 0; n1 < bn; n1 += nc) {
             PlaneGemm pg{};
             pg.mb = std::min(mc, am - m1);
             pg.nb = std::min(nc, bn - n1);
             pg.kb = a.kb;
+            pg.planes = 2 * t.np;
             pg.A = Ap + (int64_t)m1 * (a.kb / 2) * kPlanes * 2048;
             pg.B = (same ? Ap : Bp) + (int64_t)n1 * (b.kb / 2) * kPlanes * 2048;
             pg.C = Cp;
@@ -772,7 +790,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
             const int64_t units = (int64_t)pg.mb * pg.nb;
             hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>(units, 65535)), dim3(256), 0, s,
                                reinterpret_cast<const int*>(Cp), pg.mb, pg.nb, 32 * (m0 + m1),
-                               32 * (n0 + n1), ea, same ? ea : eb, h, tab());
+                               32 * (n0 + n1), ea, same ? ea : eb, h, t);
             HIPCHECK(hipGetLastError());
           }
       }
@@ -809,7 +827,7 @@ ModLadder::ModLadder(const double* F, int64_t row_stride, int v, int X, hipStrea
   a.exps = exps_;
   a.rb = v * vb;
   a.kb = kb;
-  split(a, Src{}, s);
+  split(a, Src{}, tab(15), s);  // K = naux: below the line of moduli_for, or no split
   t_ws += held_;  // the rest serves this ladder's tiles and, in turn, other products
   t_ws_bytes -= held_;
 }
@@ -841,11 +859,12 @@ void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_
         pg.mb = g1 * wvb;
         pg.nb = nbn * wvb;
         pg.kb = kblocks(X_);
+        pg.planes = 2 * 15;
         pg.a_in = pg.b_in = wvb;
         pg.a_outer = pg.b_outer = vb;
         gemm_planes(pg, s);
         LadderTiles lt{reinterpret_cast<const int*>(t_ws), exps_, v, vb, wvb, blk0, a0, a1, b, nbn, row0, W, ldw};
-        hipLaunchKernelGGL(mod_ladder_antisym_kernel, dim3(wvb * (wvb + 1) / 2, nbn, g1), dim3(256), 0, s, lt, tab());
+        hipLaunchKernelGGL(mod_ladder_antisym_kernel, dim3(wvb * (wvb + 1) / 2, nbn, g1), dim3(256), 0, s, lt, tab(15));
         HIPCHECK(hipGetLastError());
       }
     }
