@@ -866,9 +866,11 @@ static void compute_residual(Handle& h) {
   const double* t1p = h.x;
   const double* t2p = h.x + 2 * (int64_t)o * v;
   auto t1 = view(w.t1, {o, v});
-  // T2[i][k][a][b] read through the permuted copy Tq[b][i][k][a]
+  // T2[i][k][a][b] read through the permuted copy Tq[b][i][k][a]; CC2 has no ring and reads the
+  // unpacked T2 itself
   const int64_t ov = (int64_t)o * v, oov = (int64_t)o * o * v;
-  auto T2 = sview(w.Tq, {o, o, v, v}, {ov, v, 1, oov});
+  const bool cc2 = h.op.cc2 != 0;
+  auto T2 = cc2 ? view(w.Z, {o, o, v, v}) : sview(w.Tq, {o, o, v, v}, {ov, v, 1, oov});
   auto TAU = view(w.TAU, {o, o, v, v});
   auto taup = view(w.taup, {Po, Pv});
   // <kl||cd>: FP64 stored [k][l][c][d]; the FP32 copy is stored [k][c][l][d] so that the
@@ -886,7 +888,7 @@ static void compute_residual(Handle& h) {
       k_cast(h.x, (float*)w.t1, 2 * (int64_t)o * v, s);
     // full T2 goes to Z as scratch: Z is first written after Tq and Xp exist
     k_unpack_tau<R>(t1p, t2p, w.Z, w.TAU, w.taup, o, v, s);
-    k_ring_operands<R>(w.Z, t1p, w.Tq, w.Xp, o, v, s);
+    if (!cc2) k_ring_operands<R>(w.Z, t1p, w.Tq, w.Xp, o, v, s);
   }
   auto U = view(w.U, {o, o, X});
   auto Vt = view(w.Vt, {v, o, X});
@@ -894,11 +896,15 @@ static void compute_residual(Handle& h) {
   auto Hki = view(w.Hki, {o, o}), Gki = view(w.Gki, {o, o});
   auto Hkc = view(w.Hkc, {o, v});
   {
+    // CC2: G enters doubles terms it does not have, and H_ac only the singles, which take it
+    // with t1 contracted first
     Scope sc(h, "onebody");
-    contract(s, "klcd,klda->ac", HALF, Voovv, TAU, false, Hac);
+    if (!cc2) contract(s, "klcd,klda->ac", HALF, Voovv, TAU, false, Hac);
     contract(s, "klcd,licd->ki", HALF, Voovv, TAU, false, Hki);
-    dcopy(h, w.Gac, w.Hac, (int64_t)v * v);
-    dcopy(h, w.Gki, w.Hki, (int64_t)o * o);
+    if (!cc2) {
+      dcopy(h, w.Gac, w.Hac, (int64_t)v * v);
+      dcopy(h, w.Gki, w.Hki, (int64_t)o * o);
+    }
   }
   if (!ccd) {
     Scope sc(h, "onebody");
@@ -911,15 +917,23 @@ static void compute_residual(Handle& h) {
     contract(s, "acP,ic->aiP", ONE, b.Bvv, t1, false, Vt);
     // sum_kd <ak||cd> t_k^d = sum_kd (ac|kd) t_k^d - sum_kd (ad|kc) t_k^d
     //                       = sum_P B^P_ac y^P - sum_kP Vt^P_ak B^P_kc
-    contract(s, "acP,P->ac", ONE, b.Bvv, y, true, Gac);
-    contract(s, "akP,kcP->ac", MONE, Vt, b.Bov, true, Gac);
-    contract(s, "klic,lc->ki", MONE, Vooov, t1, true, Gki);
+    if (!cc2) {
+      contract(s, "acP,P->ac", ONE, b.Bvv, y, true, Gac);
+      contract(s, "akP,kcP->ac", MONE, Vt, b.Bov, true, Gac);
+      contract(s, "klic,lc->ki", MONE, Vooov, t1, true, Gki);
+    }
   }
   // singles residual S1 (CCSD's, also CC2's)
   auto singles = [&]() {
     Scope sc(h, "singles");
     auto S1 = view(w.S1, {o, v});
-    contract(s, "ac,ic->ia", ONE, Hac, t1, false, S1);
+    if (cc2) {  // 2 o^3 v^2 complex multiply-adds instead of o^2 v^3
+      auto Vt1 = view(w.Cf, {o, o, o, v});
+      contract(s, "klcd,ic->klid", HALF, Voovv, t1, false, Vt1);
+      contract(s, "klid,klda->ia", ONE, Vt1, TAU, false, S1);
+    } else {
+      contract(s, "ac,ic->ia", ONE, Hac, t1, false, S1);
+    }
     contract(s, "ki,ka->ia", ONE, Hki, t1, true, S1);
     contract(s, "kc,ikac->ia", ONE, Hkc, T2, true, S1);
     auto M1 = view(w.M1, {o, o});
@@ -933,7 +947,7 @@ static void compute_residual(Handle& h) {
     contract(s, "akP,kiP->ia", MONE, Vt, b.Boo, true, S1);
     contract(s, "aiP,P->ia", ONE, b.Bvo, view(w.y, {X}), true, S1);
   };
-  if (h.op.cc2) {
+  if (cc2) {
     // CC2 doubles: <ab||ij> of the T1-transformed Hamiltonian, from the dressed factor
     // B~^P_ai = B^P_ai + sum_c B^P_ac t_i^c - sum_k t_k^a (B^P_ki + sum_d B^P_kd t_i^d);
     // the assembly adds (e_a + e_b - e_i - e_j) t_ij^ab and nothing else
