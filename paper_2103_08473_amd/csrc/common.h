@@ -103,6 +103,25 @@ class ModLadder {
   size_t held_ = 0;
 };
 
+// The e-sums of the triples' W by exact residues: <ab||ie> of all i and t2 are split once, and
+// per triple We[(a<b)][c] = - sum_e (V_i t_jk + V_j t_ki + V_k t_ij) is one plane product over
+// K = 3 nvir and one reconstruction.  A row (a, b) has one scale for all i and a row c of t2
+// one for all pairs, so that the three terms add as integers.
+class ModTriples {
+ public:
+  static bool pays(int o, int v);
+  static size_t bytes(int o, int v, int ni);
+  // ws: bytes(o, v, ni), held by the caller; V[i][(a<b)][e] and T2[i][j][c][e] are read here only
+  ModTriples(void* ws, const double* V, const double* T2, int o, int v, int ni, hipStream_t s);
+  // We of (i, j, k), i0 <= i < i0 + ni, one after the other
+  void rows(int i0, int ni, int j, int k, double* We, hipStream_t s) const;
+
+ private:
+  int o_, v_, ni_, mb_, nb_;
+  int *ea_, *eb_;
+  signed char *pa_, *pb_, *out_;
+};
+
 // BF16x3 on pre-split operands (layout in gett.hip): K rounded up to the split
 // width; split `rows` rows of K complex FP32 values (row r at src +
 // (r / group) * group_stride + (r % group) * row_stride complex elements) into

@@ -1508,23 +1508,42 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   check_budget(h, tiles + (size_t)cap * wrow + (size_t)(4 * cap * nblk + 4 * ooo) * 8 +
                      (size_t)cap * v * 2 * o * 16,
                "triples temporaries");
-  double *Ve = nullptr, *We = nullptr, *Wm = nullptr, *part = nullptr, *tri = nullptr, *Acat = nullptr;
+  // residues of the tiles and t2, where all tiles are resident and they fit beside the rest;
+  // the products of several i together while those stay within 512 MB
+  int mod_ni = 0;
+  size_t mod_bytes = 0;
+  if (nb_occ == 1 && ModTriples::pays(o, v)) {
+    const size_t one = ModTriples::bytes(o, v, 1), each = ModTriples::bytes(o, v, 2) - one;
+    mod_ni = (int)std::min<int64_t>(cap, std::max<int64_t>(1, (int64_t)(((size_t)512 << 20) / each)));
+    mod_bytes = one + (size_t)(mod_ni - 1) * each;
+    size_t held = 0;
+    for (const AllocRange& r : h.ranges) held += r.bytes;
+    const size_t rest = small + tiles + (size_t)cap * wrow + (size_t)cap * v * 2 * o * 16 + mod_bytes;
+    if (rest > free_b || (h.op.hbm_budget_bytes && held + rest > h.op.hbm_budget_bytes)) mod_ni = 0;
+  }
+  double *Ve = nullptr, *We = nullptr, *Wm = nullptr, *part = nullptr, *tri = nullptr, *Acat = nullptr,
+         *mod = nullptr;
   struct Free {  // released on every exit, a failed allocation included
     Handle& h;
-    double** p[6];
+    double** p[7];
     ~Free() {
       for (auto q : p) try {
           h.dfree(*q);
         } catch (...) {
         }
     }
-  } fr{h, {&Ve, &We, &Wm, &part, &tri, &Acat}};
+  } fr{h, {&Ve, &We, &Wm, &part, &tri, &Acat, &mod}};
   Ve = h.dalloc((int64_t)slots * red * pvv);
   We = h.dalloc(cap * pvv);
   Wm = h.dalloc(cap * pvv);
   part = h.dalloc(2 * cap * nblk);  // 4 doubles per block
   tri = h.dalloc(2 * ooo);          // (e4, e5, ey, -) at [i][j][k]
   Acat = h.dalloc(cap * v * 2 * o);
+  if (mod_ni) try {
+      mod = h.dalloc((int64_t)(mod_bytes / 16));
+    } catch (...) {  // no block of that size: the FP64 products need none
+      (void)hipGetLastError();
+    }
   // full t2 [i][j][a][b] into H4 and t2 packed over the virtual pair [k][m][(b<c)] into
   // TAU (FP64 work arrays rebuilt every iteration)
   k_unpack_full(h.x, h.x + 2 * (int64_t)o * v, nullptr, h.H4, o, v, s);
@@ -1561,6 +1580,11 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   const int64_t ovv = (int64_t)o * vv, oov = (int64_t)o * o * v, ov = (int64_t)o * v, opv = (int64_t)o * Pv;
   // t_jk^{ce} as [c][e] (e contiguous); t_jk^{ec} = -t_jk^{ce}
   auto Tpair = [&](int j, int k) { return sview(T2 + 2 * ((int64_t)j * o + k) * vv, {v, v}, {(int64_t)v, 1}); };
+  std::optional<ModTriples> mt;
+  if (mod) {
+    build(0, 0);
+    mt.emplace(mod, Ve, T2, o, v, mod_ni, s);
+  }
   // three nested loops over occupied blocks, unique block triples bi <= bj <= bk
   for (int bk = 0; bk < nb_occ; ++bk)
     for (int bj = 0; bj <= bk; ++bj)
@@ -1595,15 +1619,19 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
               auto Wev = view(We, {ni, Pv, v});
               auto Wmv = view(Wm, {ni, v, Pv});
               auto Vt3 = [&](double* p) { return sview(p, {Pv, v}, {(int64_t)v, 1}); };
-              // sum_e <ab||ie> t_jk^ec = -sum_e <ab||ie> t_jk^ce, i over the batch
-              contract(s, "ixe,ce->ixc", MONE, sview(tile(i0, 2), {ni, Pv, v}, {pvv, (int64_t)v, 1}),
-                       Tpair(j, k), false, Wev);
-              // sum_e <ab||je> t_ki^ec, t_ki^ce = T2[k][i][c][e]
-              contract(s, "xe,ice->ixc", MONE, Vt3(tile(j, 1)),
-                       sview(T2 + 2 * ((int64_t)k * o + i0) * vv, {ni, v, v}, {vv, (int64_t)v, 1}), true, Wev);
-              // sum_e <ab||ke> t_ij^ec, t_ij^ce = T2[i][j][c][e]
-              contract(s, "xe,ice->ixc", MONE, Vt3(tile(k, 0)),
-                       sview(T2 + 2 * ((int64_t)i0 * o + j) * vv, {ni, v, v}, {ovv, (int64_t)v, 1}), true, Wev);
+              if (mt) {
+                mt->rows(i0, ni, j, k, We, s);
+              } else {
+                // sum_e <ab||ie> t_jk^ec = -sum_e <ab||ie> t_jk^ce, i over the batch
+                contract(s, "ixe,ce->ixc", MONE, sview(tile(i0, 2), {ni, Pv, v}, {pvv, (int64_t)v, 1}),
+                         Tpair(j, k), false, Wev);
+                // sum_e <ab||je> t_ki^ec, t_ki^ce = T2[k][i][c][e]
+                contract(s, "xe,ice->ixc", MONE, Vt3(tile(j, 1)),
+                         sview(T2 + 2 * ((int64_t)k * o + i0) * vv, {ni, v, v}, {vv, (int64_t)v, 1}), true, Wev);
+                // sum_e <ab||ke> t_ij^ec, t_ij^ce = T2[i][j][c][e]
+                contract(s, "xe,ice->ixc", MONE, Vt3(tile(k, 0)),
+                         sview(T2 + 2 * ((int64_t)i0 * o + j) * vv, {ni, v, v}, {ovv, (int64_t)v, 1}), true, Wev);
+              }
               // sum_m <am||ki> t_jm^bc + sum_m <am||ij> t_km^bc (b<c) as one product over
               // K = (t, m), 2 nocc: the two excitation elements gathered into Acat[i][a][t][m],
               // t_jm and t_km read as T2pv[j + t (k - j)]

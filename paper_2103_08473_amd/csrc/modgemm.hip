@@ -19,6 +19,7 @@
 // and of the result to FP64; sums over k are exact, so results do not depend on tiling.
 // A row with a non-finite element gives NaN outputs.
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "common.h"
@@ -31,6 +32,7 @@ constexpr int kPlanes = 2 * kNP;
 constexpr int kMaxK = 131072;     // K (p / 2)^2 < 2^31 with p <= 241
 constexpr int kShortK = 1152;     // K (p / 2)^2 + 128 < 2^24
 constexpr int kNaN = 0x40000000;  // exponent of a row that holds a non-finite element
+constexpr int kZero = 4096;       // of a row of zeros: above that of any other finite row
 
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef int i16v __attribute__((ext_vector_type(16)));
@@ -192,7 +194,7 @@ __global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src
   if (k0 == 0 && row < s.rows) {
     sum = ssum[tid];
     mx = smax[tid];
-    int e = 0;
+    int e = kZero;
     if (sum != sum || mx > 1.7976931348623157e308) {
       e = kNaN;
     } else if (mx > 0.0) {
@@ -314,6 +316,10 @@ struct PlaneGemm {
   int tiles_m, tiles_n;
   int planes;                  // 2 np of the kPlanes that the layouts have room for
   int p[kNP];
+  // SEG kernels: k in three segments of kb / 3 blocks, segment q of product y of a batch at
+  // 16-byte units a_seg[q] + y a_bat[q] of A (B likewise), C of product y c_bat bytes further
+  int batch;
+  int64_t a_seg[3], b_seg[3], a_bat[3], b_bat[3], c_bat;
 };
 
 // C[z] = A[z] B[z]^T mod p: WM x WN waves of TM x TN 32 x 32 blocks, stages of 64 k in three
@@ -324,7 +330,7 @@ struct PlaneGemm {
 // Bound by the power the INT8 matrix cores draw: 4032^3 x 32 planes 2380 TOP/s, the same
 // launch on zeros and ones about 3000; one tile per workgroup 2250 there and 1426 instead of
 // 1895 at 1268 x 25000 x 951, where filling the pipeline is a larger part.
-template <int WM, int WN, int TM, int TN, int OCC, bool LONG>
+template <int WM, int WN, int TM, int TN, int OCC, bool LONG, bool SEG>
 __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g) {
   constexpr int KB = 2, S = 3;
   constexpr int T = 64 * WM * WN, RA = WM * TM, RB = WN * TN;
@@ -333,17 +339,29 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
   __shared__ i4v sm[S][(RA + RB) * KB * 64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = w % WM, wn = w / WM;
-  const int tiles = g.tiles_m * g.tiles_n, total = tiles * g.planes;
-  const int64_t rs = (int64_t)g.kb / 2 * kPlanes * 128;  // 16-byte units per row block
-  const int nk = g.kb / KB;
+  // a batch's products are further tiles along n, so that what they share of A is read together
+  const int tiles_n = SEG ? g.tiles_n * g.batch : g.tiles_n;
+  const int tiles = g.tiles_m * tiles_n, total = tiles * g.planes;
+  const int nk = g.kb / KB, nseg = SEG ? nk / 3 : nk;
+  const int64_t rs = (int64_t)nseg * kPlanes * 128;  // 16-byte units per row block
   const i4v* pa[NA];
   const i4v* pb[NB];
-  int m0, n0, z;
+  int m0, n0, z, bat = 0;
+  int64_t sa[3] = {0, 0, 0}, sb[3] = {0, 0, 0};
   // blocks past mb (nb) are clamped: they feed only outputs that are not stored
   auto start = [&](int job) {
     z = job / tiles;
     int tm, tn;
-    tile_of(job - z * tiles, tiles, g.tiles_m, g.tiles_n, tm, tn);
+    tile_of(job - z * tiles, tiles, g.tiles_m, tiles_n, tm, tn);
+    if (SEG) {
+      bat = tn / g.tiles_n;
+      tn -= bat * g.tiles_n;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        sa[q] = g.a_seg[q] + bat * g.a_bat[q];
+        sb[q] = g.b_seg[q] + bat * g.b_bat[q];
+      }
+    }
     m0 = tm * RA;
     n0 = tn * RB;
     const i4v* A = reinterpret_cast<const i4v*>(g.A + z * 2048);
@@ -360,13 +378,19 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
     }
   };
   auto load = [&](int kt, int buf) {
-    const int64_t ko = (int64_t)kt * (kPlanes * 128);
+    int64_t ka = (int64_t)kt * (kPlanes * 128), kb = ka;
+    if (SEG) {
+      const int sg = kt >= 2 * nseg ? 2 : kt >= nseg ? 1 : 0;
+      ka -= (int64_t)sg * nseg * (kPlanes * 128);
+      kb = ka + (sg == 2 ? sb[2] : sg == 1 ? sb[1] : sb[0]);
+      ka += sg == 2 ? sa[2] : sg == 1 ? sa[1] : sa[0];
+    }
 #pragma unroll
     for (int q = 0; q < NA; ++q)
-      __builtin_amdgcn_global_load_lds((global_void*)(pa[q] + ko), (lds_void*)&sm[buf][w * 64 + T * q], 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((global_void*)(pa[q] + ka), (lds_void*)&sm[buf][w * 64 + T * q], 16, 0, 0);
 #pragma unroll
     for (int q = 0; q < NB; ++q)
-      __builtin_amdgcn_global_load_lds((global_void*)(pb[q] + ko),
+      __builtin_amdgcn_global_load_lds((global_void*)(pb[q] + kb),
                                        (lds_void*)&sm[buf][RA * KB * 64 + w * 64 + T * q], 16, 0, 0);
   };
   int job = blockIdx.x;
@@ -377,7 +401,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
   constexpr int kBias = LONG ? 0 : 128;  // see the reduction below
   int cur = 0;
   while (true) {
-    const int cm0 = m0, cn0 = n0, cz = z, next = job + (int)gridDim.x;
+    const int cm0 = m0, cn0 = n0, cz = z, cbat = bat, next = job + (int)gridDim.x;
     i16v acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -427,7 +451,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
     // (quotients below 2^23, off by at most 2) brings them there.
     const int p = g.p[cz >> 1];
     const float pf = (float)p, ip = 1.0f / pf, off = -128.0f * ip;
-    i4v* C = reinterpret_cast<i4v*>(g.C + cz * 1024);
+    i4v* C = reinterpret_cast<i4v*>(g.C + (SEG ? cbat * g.c_bat : 0) + cz * 1024);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -487,9 +511,13 @@ __device__ __forceinline__ Frac4 crt4(const int* c, const ModTab& t) {
 }
 
 // C(m, n) = alpha * product (+ C) for m0 <= m < m0 + 32 mb, n likewise; one dword (4 rows of
-// one column) per lane.  Bound by reading 2 kNP bytes and writing 16 per output.
+// one column) per lane.  Grid y: products of a batch, cp_bat dwords and c_bat elements apart.
+// Bound by reading 2 kNP bytes and writing 16 per output.
 __global__ __launch_bounds__(256) void mod_crt_kernel(const int* Cp, int mb, int nb, int m0, int n0,
-                                                      const int* ea, const int* eb, Gett<double> g, ModTab t) {
+                                                      const int* ea, const int* eb, Gett<double> g, int64_t cp_bat,
+                                                      int64_t c_bat, ModTab t) {
+  Cp += blockIdx.y * cp_bat;
+  g.C += 2 * (int64_t)blockIdx.y * c_bat;
   const int64_t tot = (int64_t)mb * nb * 4;
   const int lane = threadIdx.x & 63;
   for (int64_t u = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); u < tot; u += (int64_t)gridDim.x * 4) {
@@ -581,6 +609,24 @@ __global__ __launch_bounds__(256) void mod_ladder_antisym_kernel(LadderTiles g, 
   }
 }
 
+// Rows whose products are summed get one scale: exps[g n + r], g < groups, becomes the least
+// of them less 1, room for three rows in one Cauchy-Schwarz bound (sqrt(3) < 2).  One thread
+// per r; nothing beside what it prepares (groups n dwords).
+__global__ __launch_bounds__(256) void mod_joint_exps_kernel(int* exps, int groups, int n) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= n) return;
+  int e = kZero;
+  bool bad = false;
+#pragma unroll 8
+  for (int g = 0; g < groups; ++g) {
+    const int x = exps[(int64_t)g * n + r];
+    bad |= x == kNaN;
+    e = min(e, x);
+  }
+  e = bad ? kNaN : e - 1;
+  for (int g = 0; g < groups; ++g) exps[(int64_t)g * n + r] = e;
+}
+
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 int tpr_of(const Src& s) { return s.K >= 4096 ? 256 : 64; }
@@ -589,27 +635,30 @@ int norm_blocks(const Src& s) {
 }
 
 // Scale and split one or two operands (b may have rows == 0).
-void split(const Src& a, const Src& b, const ModTab& t, hipStream_t s) {
-  const int na = norm_blocks(a), nb = b.rows ? norm_blocks(b) : 0;
-  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), t.S);
-  HIPCHECK(hipGetLastError());
+void split_scaled(const Src& a, const Src& b, const ModTab& t, hipStream_t s) {
   const int sa = a.rb * (a.kb / 2), sb = b.rows ? b.rb * (b.kb / 2) : 0;
   hipLaunchKernelGGL(mod_split_kernel, dim3(sa + sb), dim3(256), 0, s, a, sa, b, t);
   HIPCHECK(hipGetLastError());
 }
+void split(const Src& a, const Src& b, const ModTab& t, hipStream_t s) {
+  const int na = norm_blocks(a), nb = b.rows ? norm_blocks(b) : 0;
+  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), t.S);
+  HIPCHECK(hipGetLastError());
+  split_scaled(a, b, t, s);
+}
 
 // RES: workgroups one CU holds (of 160 KiB LDS).  256 CUs.
-template <int WM, int WN, int TM, int TN, int OCC, int RES>
+template <int WM, int WN, int TM, int TN, int OCC, int RES, bool SEG = false>
 void launch_planes(PlaneGemm g, hipStream_t s) {
   g.tiles_m = cdiv(g.mb, WM * TM);
   g.tiles_n = cdiv(g.nb, WN * TN);
-  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * g.planes;
+  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * g.planes * (SEG ? g.batch : 1);
   if (jobs > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
   const dim3 grid((unsigned)std::min<int64_t>(jobs, 256 * RES)), block(64 * WM * WN);
   if (32 * g.kb <= kShortK)
-    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, false>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, false, SEG>), grid, block, 0, s, g);
   else
-    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, true>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, true, SEG>), grid, block, 0, s, g);
   HIPCHECK(hipGetLastError());
 }
 
@@ -790,7 +839,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
             const int64_t units = (int64_t)pg.mb * pg.nb;
             hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>(units, 65535)), dim3(256), 0, s,
                                reinterpret_cast<const int*>(Cp), pg.mb, pg.nb, 32 * (m0 + m1),
-                               32 * (n0 + n1), ea, same ? ea : eb, h, t);
+                               32 * (n0 + n1), ea, same ? ea : eb, h, (int64_t)0, (int64_t)0, t);
             HIPCHECK(hipGetLastError());
           }
       }
@@ -868,6 +917,115 @@ void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_
         HIPCHECK(hipGetLastError());
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------- triples
+// Per triple the FP64 tiles take TFP us at 62 TFLOP/s (K = nvir in three passes over the
+// output), the residues their plane products and one reconstruction (the estimates of
+// mod_gemm_pays; splitting is amortised over nocc^2 / 6 triples per operand).
+bool ModTriples::pays(int o, int v) {
+  if (o < 3 || v < 32) return false;
+  auto up = [](double x, double m) { return std::ceil(x / m) * m; };
+  if ((int64_t)o * ((int64_t)v * v + 32) > 0x3fffffffLL || (int64_t)o * o * (v + 32) > 0x3fffffffLL) return false;
+  const double P = 0.5 * v * (v - 1.0), n = o * (o - 1.0) * (o - 2.0) / 6.0;
+  const double t64 = 3 * 8.0 * up(P, 64) * up(v, 64) * v / 62e6;
+  const double tm = P * v * 15e-6 + 2.0 * kPlanes * up(P, 32) * up(v, 32) * 3 * up(v, 64) / 1.7e9;
+  const double once = 50.0 + ((double)o * P * v + (double)o * o * v * v) * 15e-6;
+  return tm + once / n < 0.9 * t64;
+}
+
+size_t ModTriples::bytes(int o, int v, int ni) {
+  const int64_t P = (int64_t)v * (v - 1) / 2;
+  const size_t mb = (size_t)cdiv(P, 32), nb = (size_t)cdiv(v, 32), rows = 32 * (o * mb + (size_t)o * o * nb);
+  return up256(rows * 4) + (size_t)mod_plane_bytes(rows, v) + (size_t)ni * mb * nb * kPlanes * 1024;
+}
+
+ModTriples::ModTriples(void* ws, const double* V, const double* T2, int o, int v, int ni, hipStream_t s)
+    : o_(o), v_(v), ni_(ni) {
+  const int64_t P = (int64_t)v * (v - 1) / 2;
+  mb_ = cdiv(P, 32);
+  nb_ = cdiv(v, 32);
+  const int kb = kblocks(v);
+  ea_ = static_cast<int*>(ws);
+  eb_ = ea_ + (size_t)32 * o * mb_;
+  pa_ = static_cast<signed char*>(ws) + up256((size_t)32 * ((size_t)o * mb_ + (size_t)o * o * nb_) * 4);
+  pb_ = pa_ + mod_plane_bytes(32LL * o * mb_, v);
+  out_ = pb_ + mod_plane_bytes(32LL * o * o * nb_, v);
+  Src a{};
+  a.p = V;
+  a.rows = 32 * o * mb_;
+  a.K = a.k_in = v;
+  a.r_in = 32 * mb_;
+  a.r_valid = (int)P;
+  a.r_so = P * v;
+  a.r_si = v;
+  a.k_so = a.k_si = 1;
+  a.kfast = 1;
+  a.planes = pa_;
+  a.exps = ea_;
+  a.rb = o * mb_;
+  a.kb = kb;
+  Src b = a;
+  b.p = T2;
+  b.rows = 32 * o * o * nb_;
+  b.r_in = 32 * nb_;
+  b.r_valid = v;
+  b.r_so = (int64_t)v * v;
+  b.planes = pb_;
+  b.exps = eb_;
+  b.rb = o * o * nb_;
+  const ModTab& t = tab(15);  // K = 3 nvir: short chains in the FP64 products too
+  const int na = norm_blocks(a), nbk = norm_blocks(b);
+  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nbk), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), t.S);
+  HIPCHECK(hipGetLastError());
+  hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * mb_, 256)), dim3(256), 0, s, ea_, o, 32 * mb_);
+  HIPCHECK(hipGetLastError());
+  hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * nb_, 256)), dim3(256), 0, s, eb_, o * o, 32 * nb_);
+  HIPCHECK(hipGetLastError());
+  split_scaled(a, b, t, s);
+}
+
+void ModTriples::rows(int i0, int ni, int j, int k, double* We, hipStream_t s) const {
+  const int64_t P = (int64_t)v_ * (v_ - 1) / 2;
+  const int64_t seg = (int64_t)kblocks(v_) / 2 * kPlanes * 128;  // 16-byte units per row block
+  const int64_t ta = mb_ * seg, tb = nb_ * seg;                  // per tile and per pair
+  const int64_t cb = (int64_t)mb_ * nb_ * kPlanes * 1024;
+  for (int y = 0; y < ni; y += ni_) {
+    const int i = i0 + y, n = std::min(ni_, ni - y);
+    PlaneGemm g{};
+    g.A = pa_;
+    g.B = pb_;
+    g.C = out_;
+    g.mb = g.a_in = g.a_outer = mb_;
+    g.nb = g.b_in = g.b_outer = nb_;
+    g.kb = 3 * kblocks(v_);
+    g.planes = 2 * 15;
+    for (int q = 0; q < kNP; ++q) g.p[q] = kMods[q];
+    g.batch = n;
+    const int64_t at[3] = {i, j, k}, bt[3] = {(int64_t)j * o_ + k, (int64_t)k * o_ + i, (int64_t)i * o_ + j};
+    const int abat[3] = {1, 0, 0}, bbat[3] = {0, 1, o_};
+    for (int q = 0; q < 3; ++q) {
+      g.a_seg[q] = at[q] * ta;
+      g.b_seg[q] = bt[q] * tb;
+      g.a_bat[q] = abat[q] * ta;
+      g.b_bat[q] = bbat[q] * tb;
+    }
+    g.c_bat = cb;
+    if (nb_ <= 4)
+      launch_planes<2, 2, 4, 2, 2, 2, true>(g, s);
+    else
+      launch_planes<2, 4, 4, 2, 1, 1, true>(g, s);
+    Gett<double> c{};
+    c.M = c.m_in = (int)P;
+    c.N = c.n_in = v_;
+    c.c_mi = v_;
+    c.c_ni = 1;
+    c.alpha_re = -1.0;
+    c.C = We + 2 * y * P * v_;
+    hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>((int64_t)mb_ * nb_, 65535), n), dim3(256), 0, s,
+                       reinterpret_cast<const int*>(out_), mb_, nb_, 0, 0, ea_, eb_, c, cb / 4, P * v_, tab(15));
+    HIPCHECK(hipGetLastError());
   }
 }
 
