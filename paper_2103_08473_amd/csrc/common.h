@@ -190,8 +190,12 @@ int triples_blocks(int v);
 // zero nbytes at p / copy nbytes from src to d (nbytes a multiple of 8, pointers 8-byte aligned)
 void k_zero_bytes(void* p, int64_t nbytes, hipStream_t s);
 void k_copy_bytes(void* d, const void* src, int64_t nbytes, hipStream_t s);
-// Acat[y][a][t][m] = conj(<x_t y_t||m a>), (x_0, y_0) = (k, i0 + y), (x_1, y_1) = (i0 + y, j)
-void k_triples_acat(const double* Vooov, int i0, int ni, int j, int k, int o, int v, double* out,
+// Acat[y][a][t][m] = conj(<x_t y_t||m a>), (x_0, y_0) = (k, i0 + y), (x_1, y_1) = (i0 + y, j),
+// (x_2, y_2) = (j, k), t < nt; Bcat[y][t][len] the rows of T2pv (len elements each) of j, k, i0 + y,
+// k and i0 + y only for y >= filled
+void k_triples_bcat(const double* T2pv, int i0, int ni, int j, int k, int filled, int64_t len, double* out,
+                    hipStream_t s);
+void k_triples_acat(const double* Vooov, int i0, int ni, int j, int k, int o, int v, int nt, double* out,
                     hipStream_t s);
 void k_triples_energy(const double* We, const double* Wm, const double* Voovv, const double* T2,
                       const double* t1, const double* eps, int i0, int ni, int j, int k, int o, int v,

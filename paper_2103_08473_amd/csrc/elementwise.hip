@@ -1033,20 +1033,31 @@ __global__ void triples_energy_kernel(const double* __restrict__ Web, const doub
 // excitation elements depend on i = i0 + y: t = 0 -> <k i||m a>, t = 1 -> <i j||m a>
 // (Vooov [x][y][m][a])
 __global__ void triples_acat_kernel(const double* __restrict__ Vooov, int i0, int ni, int j, int k,
-                                    int o, int v, double* __restrict__ out) {
-  const int64_t tot = (int64_t)ni * v * 2 * o;
+                                    int o, int v, int nt, double* __restrict__ out) {
+  const int64_t tot = (int64_t)ni * v * nt * o;
   for (int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x; t < tot; t += (int64_t)gridDim.x * TB) {
     const int m = (int)(t % o);
     int64_t r = t / o;
-    const int tt = (int)(r % 2);
-    r /= 2;
+    const int tt = (int)(r % nt);
+    r /= nt;
     const int a = (int)(r % v);
     const int y = (int)(r / v);
     const int i = i0 + y;
-    const int x0 = tt == 0 ? k : i, y0 = tt == 0 ? i : j;
+    const int x0 = tt == 0 ? k : tt == 1 ? i : j, y0 = tt == 0 ? i : tt == 1 ? j : k;
     const z g = ld(Vooov, (((int64_t)x0 * o + y0) * o + m) * v + a);
     st(out, t, z{g.x, -g.y});
   }
+}
+
+// Bcat[y][t][m][(bc)] = T2pv of j, k and i0 + y (t = 0, 1, 2).  Slots below `filled` hold their
+// k and i parts already.  A copy, 16 bytes read and written per element.
+__global__ __launch_bounds__(TB) void triples_bcat_kernel(const double* __restrict__ T2pv, int i0, int j, int k,
+                                                          int filled, int64_t len, double* __restrict__ out) {
+  const int y = blockIdx.y, t = blockIdx.z;
+  if (t > 0 && y < filled) return;
+  const double* src = T2pv + 2 * len * (t == 0 ? j : t == 1 ? k : i0 + y);
+  double* dst = out + 2 * len * ((int64_t)y * 3 + t);
+  for (int64_t e = (int64_t)blockIdx.x * TB + threadIdx.x; e < len; e += (int64_t)gridDim.x * TB) st(dst, e, ld(src, e));
 }
 
 // One block per triple of the batch: the nblk partials in a fixed order, to
@@ -1122,11 +1133,19 @@ void k_copy_bytes(void* d, const void* src, int64_t nbytes, hipStream_t s) {
   HIPCHECK(hipGetLastError());
 }
 
-void k_triples_acat(const double* Vooov, int i0, int ni, int j, int k, int o, int v, double* out,
+void k_triples_bcat(const double* T2pv, int i0, int ni, int j, int k, int filled, int64_t len, double* out,
                     hipStream_t s) {
-  const int64_t tot = (int64_t)ni * v * 2 * o;
+  if (ni <= 0 || len <= 0) return;
+  hipLaunchKernelGGL(triples_bcat_kernel, dim3((unsigned)std::min<int64_t>((len + TB - 1) / TB, 1024), ni, 3), dim3(TB),
+                     0, s, T2pv, i0, j, k, filled, len, out);
+  HIPCHECK(hipGetLastError());
+}
+
+void k_triples_acat(const double* Vooov, int i0, int ni, int j, int k, int o, int v, int nt, double* out,
+                    hipStream_t s) {
+  const int64_t tot = (int64_t)ni * v * nt * o;
   if (tot <= 0) return;
-  hipLaunchKernelGGL(triples_acat_kernel, dim3(nblocks(tot)), dim3(TB), 0, s, Vooov, i0, ni, j, k, o, v, out);
+  hipLaunchKernelGGL(triples_acat_kernel, dim3(nblocks(tot)), dim3(TB), 0, s, Vooov, i0, ni, j, k, o, v, nt, out);
   HIPCHECK(hipGetLastError());
 }
 

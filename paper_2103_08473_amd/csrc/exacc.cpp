@@ -1512,38 +1512,52 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   // the products of several i together while those stay within 512 MB
   int mod_ni = 0;
   size_t mod_bytes = 0;
+  size_t in_use = 0;
+  for (const AllocRange& r : h.ranges) in_use += r.bytes;
+  // what the optional buffers come on top of (Acat at its larger size)
+  size_t rest = small + tiles + (size_t)cap * wrow + (size_t)cap * v * 3 * o * 16;
+  auto fits = [&](size_t more) {
+    return rest + more <= free_b && (!h.op.hbm_budget_bytes || in_use + rest + more <= h.op.hbm_budget_bytes);
+  };
+  // t2 of the three occupied indices of each triple of a batch side by side
+  const size_t bcat_bytes = (size_t)cap * 3 * o * Pv * 16;
+  const bool one_m = fits(bcat_bytes);
+  if (one_m) rest += bcat_bytes;
   if (nb_occ == 1 && ModTriples::pays(o, v)) {
     const size_t one = ModTriples::bytes(o, v, 1), each = ModTriples::bytes(o, v, 2) - one;
     mod_ni = (int)std::min<int64_t>(cap, std::max<int64_t>(1, (int64_t)(((size_t)512 << 20) / each)));
     mod_bytes = one + (size_t)(mod_ni - 1) * each;
-    size_t held = 0;
-    for (const AllocRange& r : h.ranges) held += r.bytes;
-    const size_t rest = small + tiles + (size_t)cap * wrow + (size_t)cap * v * 2 * o * 16 + mod_bytes;
-    if (rest > free_b || (h.op.hbm_budget_bytes && held + rest > h.op.hbm_budget_bytes)) mod_ni = 0;
+    if (!fits(mod_bytes)) mod_ni = 0;
   }
   double *Ve = nullptr, *We = nullptr, *Wm = nullptr, *part = nullptr, *tri = nullptr, *Acat = nullptr,
-         *mod = nullptr;
+         *mod = nullptr, *Bcat = nullptr;
   struct Free {  // released on every exit, a failed allocation included
     Handle& h;
-    double** p[7];
+    double** p[8];
     ~Free() {
       for (auto q : p) try {
           h.dfree(*q);
         } catch (...) {
         }
     }
-  } fr{h, {&Ve, &We, &Wm, &part, &tri, &Acat, &mod}};
+  } fr{h, {&Ve, &We, &Wm, &part, &tri, &Acat, &mod, &Bcat}};
   Ve = h.dalloc((int64_t)slots * red * pvv);
   We = h.dalloc(cap * pvv);
   Wm = h.dalloc(cap * pvv);
   part = h.dalloc(2 * cap * nblk);  // 4 doubles per block
   tri = h.dalloc(2 * ooo);          // (e4, e5, ey, -) at [i][j][k]
-  Acat = h.dalloc(cap * v * 2 * o);
-  if (mod_ni) try {
-      mod = h.dalloc((int64_t)(mod_bytes / 16));
-    } catch (...) {  // no block of that size: the FP64 products need none
+  Acat = h.dalloc(cap * v * (one_m ? 3 : 2) * o);
+  auto optional = [&](size_t bytes) -> double* {
+    try {
+      return h.dalloc((int64_t)(bytes / 16));
+    } catch (...) {  // no block of that size: done without
       (void)hipGetLastError();
+      return nullptr;
     }
+  };
+  if (one_m) Bcat = optional(bcat_bytes);
+  if (mod_ni) mod = optional(mod_bytes);
+  int b_k = -1, b_i0 = -1, b_filled = 0;  // slots of Bcat that hold their k and i parts
   // full t2 [i][j][a][b] into H4 and t2 packed over the virtual pair [k][m][(b<c)] into
   // TAU (FP64 work arrays rebuilt every iteration)
   k_unpack_full(h.x, h.x + 2 * (int64_t)o * v, nullptr, h.H4, o, v, s);
@@ -1632,17 +1646,29 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
                 contract(s, "xe,ice->ixc", MONE, Vt3(tile(k, 0)),
                          sview(T2 + 2 * ((int64_t)i0 * o + j) * vv, {ni, v, v}, {ovv, (int64_t)v, 1}), true, Wev);
               }
-              // sum_m <am||ki> t_jm^bc + sum_m <am||ij> t_km^bc (b<c) as one product over
-              // K = (t, m), 2 nocc: the two excitation elements gathered into Acat[i][a][t][m],
-              // t_jm and t_km read as T2pv[j + t (k - j)]
-              k_triples_acat(h.Vooov, i0, ni, j, k, o, v, Acat, s);
-              contract(s, "iatm,tmy->iay", MONE, view(Acat, {ni, v, 2, o}),
-                       sview(T2pv + 2 * (int64_t)j * opv, {2, o, Pv}, {(int64_t)(k - j) * opv, Pv, 1}),
-                       false, Wmv);
-              // sum_m <am||jk> t_im^bc
-              contract(s, "ma,imy->iay", MONE,
-                       conj(sview(h.Vooov + 2 * ((int64_t)j * o + k) * ov, {o, v}, {(int64_t)v, 1})),
-                       sview(T2pv + 2 * (int64_t)i0 * opv, {ni, o, Pv}, {opv, Pv, 1}), true, Wmv);
+              if (Bcat) {
+                // the three sums over m as one product over K = (t, m), 3 nocc: the excitation
+                // elements gathered into Acat[i][a][t][m], t_jm, t_km and t_im into Bcat
+                if (k != b_k || i0 != b_i0) b_filled = 0;
+                k_triples_acat(h.Vooov, i0, ni, j, k, o, v, 3, Acat, s);
+                k_triples_bcat(T2pv, i0, ni, j, k, b_filled, opv, Bcat, s);
+                b_k = k;
+                b_i0 = i0;
+                b_filled = std::max(b_filled, ni);
+                contract(s, "iatm,itmy->iay", MONE, view(Acat, {ni, v, 3, o}), view(Bcat, {ni, 3, o, Pv}), false, Wmv);
+              } else {
+                // sum_m <am||ki> t_jm^bc + sum_m <am||ij> t_km^bc (b<c) as one product over
+                // K = (t, m), 2 nocc: the two excitation elements gathered into Acat[i][a][t][m],
+                // t_jm and t_km read as T2pv[j + t (k - j)]
+                k_triples_acat(h.Vooov, i0, ni, j, k, o, v, 2, Acat, s);
+                contract(s, "iatm,tmy->iay", MONE, view(Acat, {ni, v, 2, o}),
+                         sview(T2pv + 2 * (int64_t)j * opv, {2, o, Pv}, {(int64_t)(k - j) * opv, Pv, 1}),
+                         false, Wmv);
+                // sum_m <am||jk> t_im^bc
+                contract(s, "ma,imy->iay", MONE,
+                         conj(sview(h.Vooov + 2 * ((int64_t)j * o + k) * ov, {o, v}, {(int64_t)v, 1})),
+                         sview(T2pv + 2 * (int64_t)i0 * opv, {ni, o, Pv}, {opv, Pv, 1}), true, Wmv);
+              }
               k_triples_energy(We, Wm, h.Voovv, T2, h.x, h.eps, i0, ni, j, k, o, v, part, nblk, tri, s);
             }
           }
