@@ -870,14 +870,16 @@ void k_ring_fock(T* H, const T* Gac, const T* Gki, int o, int v, hipStream_t s) 
 //        + t_ki^ab t_j^c
 //   e4 += -6 |W~|^2 / D,  e5 += -6 Re(conj(Z~) W~) / D,  ey += 6 Re(conj(Y~) W~),
 //   D = e_a + e_b + e_c - e_i - e_j - e_k.
-// One workgroup per triple of 8-wide virtual tiles (tA <= tB <= tC).  Staged in LDS, each
-// read with its contiguous index fastest (every global read coalesced): the six 8x8x8 cubes
-// of packed values that W~ needs on (A, B, C); the 8x8 blocks of <xy||pq> and t_xy^pq for
-// the three occupied pairs (ij, jk, ki) and the three virtual tile pairs (AB, CA, BC) that
-// Z~ and Y~ read; and t_x^p for x in (i, j, k) on the three tiles.  Then each thread
-// evaluates its a < b < c points.  Block partial sums (e4, e5, ey) to
-// part[4 * (y * gridDim.x + block)].
-__global__ void triples_energy_kernel(const double* __restrict__ Web, const double* __restrict__ Wmb,
+// One workgroup per triple of 8-wide virtual tiles (tA <= tB <= tC).  Each is read with its
+// contiguous index fastest (every global read coalesced): the six 8x8x8 cubes of packed values
+// that W~ needs on (A, B, C), summed to three and two of those staged in LDS; the 8x8 blocks of
+// <xy||pq> and t_xy^pq for the three occupied pairs (ij, jk, ki) and the three virtual tile
+// pairs (AB, CA, BC) that Z~ and Y~ read; and t_x^p for x in (i, j, k) on the three tiles.
+// Then each thread evaluates its a < b < c points.  Block partial sums (e4, e5, ey) to
+// part[4 * (y * gridDim.x + block)].  Bound by the latency of the 12 gathered loads per thread,
+// so by the workgroups a CU holds: 39 KiB of LDS, four of them (78 KiB, two, with six cubes and
+// block sums in LDS); nvir 126, 32 MB per triple: 18.7 -> 12.0 us (2.7 TB/s).
+__global__ __launch_bounds__(TB, 4) void triples_energy_kernel(const double* __restrict__ Web, const double* __restrict__ Wmb,
                                       const double* __restrict__ Voovv,
                                       const double* __restrict__ T2, const double* __restrict__ t1,
                                       const double* __restrict__ eps, int i0, int j, int k, int o, int v,
@@ -903,41 +905,40 @@ __global__ void triples_energy_kernel(const double* __restrict__ Web, const doub
   }
   const int tc = tb + rem;
   const int a0 = 8 * ta, b0 = 8 * tb, c0 = 8 * tc;
-  // cube q at LDS index (x * 8 + y) * 8 + w holds its value for (a, b, c) = (a0+x, b0+y, c0+w);
-  // entries whose pair is not p < q (unused by a < b < c) are zero
-  __shared__ double qr[6][512], qi[6][512];
-  for (int e = threadIdx.x; e < 512; e += TB) {
+  // W~ at (a, b, c) = (a0+x, b0+y, c0+w), entry e = (x * 8 + y) * 8 + w: the values with c
+  // fastest in memory go to the thread that sums them, those with a (cube 0) or b (cube 1)
+  // fastest through LDS at 72 x + 8 y + w (conflict-free in either order); entries whose
+  // pair is not p < q (unused by a < b < c) are zero
+  static_assert(TB == 256, "four waves, two points per thread");
+  __shared__ double qr[2][576], qi[2][576];
+  z wc[512 / TB];
+#pragma unroll
+  for (int q = 0; q < 512 / TB; ++q) {
+    const int e = threadIdx.x + q * TB;
     const int u = e >> 6, m = (e >> 3) & 7, f = e & 7;  // f fastest
     z g[6];
-    int at[6];
-    // 0: We(ab, c), c fastest;  3: Wm(a, bc), c fastest;  4: Wm(b, ac), c fastest
-    {
+    {  // We(ab, c), Wm(a, bc), Wm(b, ac)
       const int a = a0 + u, b = b0 + m, c = c0 + f;
       const bool in = a < v && b < v && c < v;
       g[0] = (in && a < b) ? Ep(a, b, c) : z{0, 0};
       g[3] = (in && b < c) ? Mp(a, b, c) : z{0, 0};
       g[4] = (in && a < c) ? Mp(b, a, c) : z{0, 0};
-      at[0] = at[3] = at[4] = (u * 8 + m) * 8 + f;
     }
-    // 1: We(bc, a), a fastest
-    {
+    {  // We(bc, a), a fastest
       const int b = b0 + u, c = c0 + m, a = a0 + f;
       g[1] = (a < v && b < v && c < v && b < c) ? Ep(b, c, a) : z{0, 0};
-      at[1] = (f * 8 + u) * 8 + m;
     }
-    // 2: We(ac, b), b fastest;  5: Wm(c, ab), b fastest
-    {
+    {  // We(ac, b), Wm(c, ab), b fastest
       const int a = a0 + u, c = c0 + m, b = b0 + f;
       const bool in = a < v && b < v && c < v;
       g[2] = (in && a < c) ? Ep(a, c, b) : z{0, 0};
       g[5] = (in && a < b) ? Mp(c, a, b) : z{0, 0};
-      at[2] = at[5] = (u * 8 + f) * 8 + m;
     }
-#pragma unroll
-    for (int q = 0; q < 6; ++q) {
-      qr[q][at[q]] = g[q].x;
-      qi[q][at[q]] = g[q].y;
-    }
+    wc[q] = z{g[0].x + g[3].x - g[4].x, g[0].y + g[3].y - g[4].y};
+    qr[0][72 * f + 8 * u + m] = g[1].x;
+    qi[0][72 * f + 8 * u + m] = g[1].y;
+    qr[1][72 * u + 8 * f + m] = g[5].x - g[2].x;
+    qi[1][72 * u + 8 * f + m] = g[5].y - g[2].y;
   }
   // block 3 p + r, cell 8 row + col: <pair p||tile pair r> (conjugated) and t_(pair p)^(tile pair
   // r); pairs p = (ij, jk, ki), tile pairs r = (AB, CA, BC) as (row, col); t1s[x][8 tile + w]
@@ -955,6 +956,10 @@ __global__ void triples_energy_kernel(const double* __restrict__ Web, const doub
       const int64_t off = ((int64_t)x * o + y) * vv + (int64_t)row * v + col;
       g = ld(Voovv, off);
       h = ld(T2, off);
+      if (role == 0) {  // t_xy^ab + t_x^a t_y^b - t_y^a t_x^b, see Y~
+        h = add(h, mul(ld(t1, (int64_t)x * v + row), ld(t1, (int64_t)y * v + col)));
+        h = sub(h, mul(ld(t1, (int64_t)y * v + row), ld(t1, (int64_t)x * v + col)));
+      }
     }
     vr[blk][cell] = g.x;
     vi[blk][cell] = -g.y;
@@ -973,59 +978,53 @@ __global__ void triples_energy_kernel(const double* __restrict__ Web, const doub
   auto Vs = [&](int blk, int cell) { return z{vr[blk][cell], vi[blk][cell]}; };
   auto Ts = [&](int blk, int cell) { return z{sr[blk][cell], si[blk][cell]}; };
   // Z(p, q, r) and Y(p, q, r) for (p, q, r) one of (a, b, c), (c, a, b), (b, c, a): tile pair
-  // `role` of (p, q), its cell, and the t1s columns qp, qq, qr of p, q, r
+  // `role` of (p, q), its cell, and the t1s column of r
   auto Zr = [&](int role, int cell, int qr_) {
     z r = mul(Vs(role, cell), T1(2, qr_));
     r = add(r, mul(Vs(3 + role, cell), T1(0, qr_)));
     return add(r, mul(Vs(6 + role, cell), T1(1, qr_)));
   };
-  auto Yr = [&](int role, int cell, int qp, int qq, int qr_) {
-    z d = mul(mul(T1(0, qp), T1(1, qq)), T1(2, qr_));
-    d = sub(d, mul(mul(T1(1, qp), T1(0, qq)), T1(2, qr_)));
-    d = add(d, mul(mul(T1(1, qp), T1(2, qq)), T1(0, qr_)));
-    d = sub(d, mul(mul(T1(2, qp), T1(1, qq)), T1(0, qr_)));
-    d = add(d, mul(mul(T1(2, qp), T1(0, qq)), T1(1, qr_)));
-    d = sub(d, mul(mul(T1(0, qp), T1(2, qq)), T1(1, qr_)));
-    z r = scal(1.0 / 3.0, d);
-    r = add(r, mul(Ts(role, cell), T1(2, qr_)));
+  // the determinant of t_i, t_j, t_k at a, b, c is the same for the three even orders; expanded
+  // along c, its 2 x 2 minors stand beside t2 in the blocks of (a, b)
+  auto Yr = [&](int role, int cell, int qr_) {
+    z r = mul(Ts(role, cell), T1(2, qr_));
     r = add(r, mul(Ts(3 + role, cell), T1(0, qr_)));
     return add(r, mul(Ts(6 + role, cell), T1(1, qr_)));
   };
   double e4 = 0, e5 = 0, ey = 0;
   const double eo = eps[i] + eps[j] + eps[k];
-  for (int e = threadIdx.x; e < 512; e += TB) {
+#pragma unroll
+  for (int q = 0; q < 512 / TB; ++q) {
+    const int e = threadIdx.x + q * TB;
     const int x = e >> 6, y = (e >> 3) & 7, w = e & 7;
     const int a = a0 + x, b = b0 + y, c = c0 + w;
     if (!(c < v && a < b && b < c)) continue;
-    const z wt{qr[0][e] + qr[1][e] - qr[2][e] + qr[3][e] - qr[4][e] + qr[5][e],
-               qi[0][e] + qi[1][e] - qi[2][e] + qi[3][e] - qi[4][e] + qi[5][e]};
+    const int at = 72 * x + 8 * y + w;
+    const z wt{wc[q].x + qr[0][at] + qr[1][at], wc[q].y + qi[0][at] + qi[1][at]};
     const int qa = x, qb = 8 + y, qc = 16 + w;
     const z zz = add(Zr(0, x * 8 + y, qc), add(Zr(1, w * 8 + x, qb), Zr(2, y * 8 + w, qa)));
-    const z yy = add(Yr(0, x * 8 + y, qa, qb, qc),
-                     add(Yr(1, w * 8 + x, qc, qa, qb), Yr(2, y * 8 + w, qb, qc, qa)));
+    const z yy = add(Yr(0, x * 8 + y, qc), add(Yr(1, w * 8 + x, qb), Yr(2, y * 8 + w, qa)));
     const double D = eps[o + a] + eps[o + b] + eps[o + c] - eo;
     e4 -= 6.0 * (wt.x * wt.x + wt.y * wt.y) / D;
     e5 -= 6.0 * (zz.x * wt.x + zz.y * wt.y) / D;
     ey += 6.0 * (yy.x * wt.x + yy.y * wt.y);
   }
-  __shared__ double s4[TB], s5[TB], sy[TB];
-  s4[threadIdx.x] = e4;
-  s5[threadIdx.x] = e5;
-  sy[threadIdx.x] = ey;
-  __syncthreads();
-  for (int s = TB / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) {
-      s4[threadIdx.x] += s4[threadIdx.x + s];
-      s5[threadIdx.x] += s5[threadIdx.x + s];
-      sy[threadIdx.x] += sy[threadIdx.x + s];
-    }
-    __syncthreads();
+  __shared__ double ws[3][TB / 64];
+  for (int d = 32; d > 0; d >>= 1) {
+    e4 += __shfl_xor(e4, d);
+    e5 += __shfl_xor(e5, d);
+    ey += __shfl_xor(ey, d);
   }
-  if (threadIdx.x == 0) {
+  if ((threadIdx.x & 63) == 0) {
+    ws[0][threadIdx.x >> 6] = e4;
+    ws[1][threadIdx.x >> 6] = e5;
+    ws[2][threadIdx.x >> 6] = ey;
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const double* x = ws[threadIdx.x];
     const int64_t q = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
-    part[4 * q] = s4[0];
-    part[4 * q + 1] = s5[0];
-    part[4 * q + 2] = sy[0];
+    part[4 * q + threadIdx.x] = (x[0] + x[1]) + (x[2] + x[3]);
   }
 }
 

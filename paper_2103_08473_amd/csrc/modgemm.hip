@@ -921,6 +921,10 @@ void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_
 }
 
 // ---------------------------------------------------------------- triples
+// nvir 126 per triple: FP64 products 49 us; here 22.9 (1.0 POP/s: 6 stages of K per tile, 70 MB
+// of planes and residues moved) and 11.5 for the reconstruction.  With the products of a batch
+// one after the other instead of side by side along n the planes of V_j and V_k are read from
+// memory for each: 24.6 us.
 // Per triple the FP64 tiles take TFP us at 62 TFLOP/s (K = nvir in three passes over the
 // output), the residues their plane products and one reconstruction (the estimates of
 // mod_gemm_pays; splitting is amortised over nocc^2 / 6 triples per operand).
