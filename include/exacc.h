@@ -234,8 +234,9 @@ int exacc_ccsd_density(exacc_ccsd_t h, double* gamma, int ptr_on_device);
  * pointers (ptrs_on_device = 1) or host pointers (0); the caller owns them.
  * stream: hipStream_t or NULL (the call then uses a stream of its own).
  * Temporary device memory of 6 naux^2 + naux nspinor (nao + nspinor) complex
- * values (plus copies of the inputs for host pointers) is allocated and freed
- * inside the call (NOMEM if it does not fit).  INVALID_ARG for sizes outside
+ * values at most, the second part never above 256 MB, and 768 MB for large
+ * sizes where twice that is free (plus copies of the inputs for host pointers),
+ * is allocated and freed inside the call (NOMEM if it does not fit).  INVALID_ARG for sizes outside
  * 1 <= nspinor <= nao, naux >= 1, null pointers, or a metric on which the
  * iteration does not converge (not positive definite, or condition number
  * beyond about 1e14). */

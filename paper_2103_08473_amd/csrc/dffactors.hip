@@ -153,12 +153,17 @@ size_t chunk_bytes(int m, int n, int X) {
 }
 size_t splitk_bytes(int X) { return std::min<size_t>((size_t)64 << 20, std::max<size_t>(1 << 20, (size_t)X * X * 256)); }
 
-// Host memory that one step's residual norm lands in while the next is on its way.
+// Host memory that one step's residual norm lands in: pinned, while the next step is on its way
+// (lag), or, for the entry point that must not allocate (pinned memory neither: not under a
+// capture elsewhere), plain memory that each step waits for.
 struct Readback {
-  double* h = nullptr;
+  double plain[4] = {};
+  double* h = plain;
   hipEvent_t ev[2] = {};
   hipStream_t s;
-  explicit Readback(hipStream_t st) : s(st) {
+  const bool lag;
+  Readback(hipStream_t st, bool lagged) : s(st), lag(lagged) {
+    if (!lag) return;
     HIPCHECK(hipHostMalloc((void**)&h, 4 * sizeof(double), hipHostMallocDefault));
     for (auto& e : ev)
       if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
@@ -166,11 +171,23 @@ struct Readback {
         raise(-3, "DF factors: event creation failed");
       }
   }
+  // red[k] to h[k], in flight or landed
+  void fetch(int k, const double* red) {
+    HIPCHECK(hipMemcpyAsync(&h[k], red + k, 8, hipMemcpyDeviceToHost, s));
+    if (lag)
+      HIPCHECK(hipEventRecord(ev[k], s));
+    else
+      HIPCHECK(hipStreamSynchronize(s));
+  }
+  double get(int k) {
+    if (lag) HIPCHECK(hipEventSynchronize(ev[k]));
+    return h[k];
+  }
   void release() {
     (void)hipStreamSynchronize(s);  // a copy may still be on its way
     for (auto& e : ev)
       if (e) (void)hipEventDestroy(e);
-    if (h) (void)hipHostFree(h);
+    if (lag && h) (void)hipHostFree(h);
   }
   ~Readback() { release(); }
   Readback(const Readback&) = delete;
@@ -183,7 +200,7 @@ struct Readback {
 // Newton-Schulz step count.  Nothing in the region needs to start at zero: every
 // temporary is written before it is read.
 int df_core(int m, int n, int X, const double* Cd, const double* Jd, const double* Vd, double* Bd,
-            hipStream_t s, char* base, size_t cap, size_t ws_cap, void* mod, size_t mod_bytes) {
+            hipStream_t s, char* base, size_t cap, size_t ws_cap, bool lag, void* mod, size_t mod_bytes) {
   const cplx ONE{1.0, 0.0};
   const size_t fixed = fixed_bytes(X);
   if (fixed + slice_bytes(m, n, X, 1) > cap) raise(-2, "DF factors: scratch region too small");
@@ -216,30 +233,28 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
   const size_t wsb = std::min(left, ws_cap);
   set_gett_workspace(wsb >= (1u << 20) ? cv.take(wsb) : nullptr, wsb >= (1u << 20) ? wsb : 0);
   set_mod_workspace(mod, mod_bytes);
-  Readback rb(s);
+  Readback rb(s, lag);
   // scale: c = max_i sum_j |V_ij| bounds the spectrum of the symmetric V from above
   hipLaunchKernelGGL(row_abs_sum_kernel, dim3(nblk(X, 1024)), dim3(kTB), 0, s, Vd, X, part);
   HIPCHECK(hipGetLastError());
   hipLaunchKernelGGL(max_kernel, dim3(1), dim3(kTB), 0, s, part, X, red);
   HIPCHECK(hipGetLastError());
-  HIPCHECK(hipMemcpyAsync(&rb.h[2], red, 8, hipMemcpyDeviceToHost, s));
-  HIPCHECK(hipStreamSynchronize(s));
-  const double c = rb.h[2];
+  rb.fetch(0, red);
+  const double c = rb.get(0);
   if (!(c > 0.0) || !std::isfinite(c)) raise(-1, "DF factors: metric is zero or not finite");
   hipLaunchKernelGGL(ns_init_kernel, dim3(nb), dim3(kTB), 0, s, Vd, X, 1.0 / c, Y, Z);
   HIPCHECK(hipGetLastError());
 
   auto XXv = [&](double* p) { return view(p, {X, X}); };
-  // P = Z Y, T and the norm |I - P| of step k into rb.h[k % 2].  The norm of a step is waited
-  // for only once the next step's product is queued, so the host's turnaround is hidden; the
-  // next step's P and T are then formed for nothing after the last one.
+  // P = Z Y, T and the norm |I - P| of step k into rb.h[k % 2].  With lag the norm of a step is
+  // waited for only once the next step's product is queued, so the host's turnaround is hidden;
+  // the next step's P and T are then formed for nothing after the last one.
   auto look = [&](int k, double* Pk, double* Tk) {
     contract(s, "ab,bc->ac", ONE, XXv(Z), XXv(Y), false, XXv(Pk));
     hipLaunchKernelGGL(ns_step_kernel, dim3(nb), dim3(kTB), 0, s, Pk, X, Tk, part);
     HIPCHECK(hipGetLastError());
     k_reduce_sum(part, nb, 1, red + k % 2, s);
-    HIPCHECK(hipMemcpyAsync(&rb.h[k % 2], red + k % 2, 8, hipMemcpyDeviceToHost, s));
-    HIPCHECK(hipEventRecord(rb.ev[k % 2], s));
+    rb.fetch(k % 2, red);
   };
   int iters = 0;
   bool done = false, failed = false;
@@ -250,14 +265,14 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
     contract(s, "ab,bc->ac", ONE, XXv(T), XXv(Z), false, XXv(Z2));
     std::swap(Y, Y2);
     std::swap(Z, Z2);
-    if (iters < 200) look(iters, P, T);
-    HIPCHECK(hipEventSynchronize(rb.ev[k % 2]));
-    const double r = std::sqrt(rb.h[k % 2]);
+    if (lag && iters < 200) look(iters, P, T);
+    const double r = std::sqrt(rb.get(k % 2));
     // quadratic phase: the step just taken brought the error to ~r^2 (rounding level)
     if (!std::isfinite(r) || r > 1e3 * X)
       failed = true;
     else
       done = r < 1e-8;
+    if (!lag && !done && !failed && iters < 200) look(iters, P, T);
   }
   if (!done)
     raise(-1, "DF factors: the inverse square root iteration did not converge (metric not positive "
@@ -361,7 +376,7 @@ int df_factors_impl(int m, int n, int X, const double* C, const double* J, const
       mod_bytes = 0;
     }
   }
-  const int iters = df_core(m, n, X, Cd, Jd, Vd, Bd, s, region, cap, wsb, own.p[5], mod_bytes);
+  const int iters = df_core(m, n, X, Cd, Jd, Vd, Bd, s, region, cap, wsb, true, own.p[5], mod_bytes);
   if (!on_device) {
     HIPCHECK(hipMemcpyAsync(B, Bd, bB, hipMemcpyDeviceToHost, s));
     HIPCHECK(hipStreamSynchronize(s));
@@ -377,7 +392,7 @@ int df_factors_noalloc_impl(int m, int n, int X, const double* C, const double* 
                   ", nspinor = " + std::to_string(n) + " need " + std::to_string(need) +
                   " bytes of scratch, above the static " + std::to_string((size_t)EXACC_DF_SCRATCH_BYTES));
   char* base = scratch_address();
-  return df_core(m, n, X, C, J, V, B, s, base, (size_t)EXACC_DF_SCRATCH_BYTES, (size_t)64 << 20, nullptr, 0);
+  return df_core(m, n, X, C, J, V, B, s, base, (size_t)EXACC_DF_SCRATCH_BYTES, (size_t)64 << 20, false, nullptr, 0);
 }
 
 }  // namespace exacc
