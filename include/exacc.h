@@ -114,7 +114,9 @@ void exacc_ccsd_default_opts(exacc_ccsd_opts* o);
  * modes the estimate includes the reference arrays of the ring correction
  * (ladder_defect_correction) when they fit in hbm_budget_bytes (or no budget is
  * set); create drops them when the plan with them exceeds the device memory, and
- * the estimate then overstates the footprint by that part. */
+ * the estimate then overstates the footprint by that part.  A workspace for large
+ * FP64 products is included (at most 10 GiB); hbm_budget_bytes shrinks or drops it
+ * before anything is refused, and so does create on a nearly full device. */
 size_t exacc_ccsd_memory_estimate(int nocc, int nvir, int naux, const exacc_ccsd_opts* opts);
 
 /* Validate the inputs, copy them to the device, build the stored integral

@@ -1,9 +1,11 @@
 // Complex GEMM-like tensor contraction (GETT) on CDNA4 matrix cores.
 //
-// One workgroup (4 waves of 64 lanes) owns a BM x BN tile of C; two
-// workgroups per CU (two waves per SIMD) hide LDS and barrier latency.
-// Operand tiles of BK complex columns (16 in production) are staged through
-// LDS as two real planes, k-major (re, im), so each 16x16x4 MFMA fragment is
+// Large FP64 products go to the integer residues of modgemm.hip; the rest, and
+// FP32, run here.  One workgroup (4 waves of 64 lanes) owns a BM x BN tile of C,
+// 64 x 64 or, where those are too few to fill the chip, 32 x 32; still smaller
+// products take 16 x 16 tiles without LDS (gett_tiny_kernel).  Two or more
+// workgroups per CU hide LDS and barrier latency.  Operand tiles of BK complex
+// columns (16 or 32) are staged through LDS as two real planes, k-major (re, im), so each 16x16x4 MFMA fragment is
 // read with unit stride; the re+im operand of the Gauss product is formed in
 // registers.  Complex products use the three-multiplication (Gauss) form:
 // T1 = re*re, T2 = im*im, T3 = (re+im)(re+im) accumulate in three MFMA

@@ -49,6 +49,7 @@ class Request:
     mem_wait: bool = False   # was at the head of the queue with a slot free but not the memory
     error: str = ""
     inputs: object = field(default=None, repr=False)
+    opts: dict = field(default_factory=dict)   # on top of the server's
 
 
 def _make_inputs(shape):
@@ -93,8 +94,17 @@ class Server:
         return time.perf_counter() - self.t0
 
     def submit(self, req: Request):
-        req.mem = exacc.memory_estimate(req.nocc, req.nvir, req.naux,
-                                        precision=self.opts.get("precision", exacc.FP64))
+        def plan(**kw):
+            return exacc.memory_estimate(req.nocc, req.nvir, req.naux,
+                                         precision=self.opts.get("precision", exacc.FP64), **kw)
+        req.mem = plan()
+        if req.mem > self.budget:
+            # the residue workspace is optional (its size is that of a plan without the mixed
+            # modes' correction arrays, which a budget drops first): without it, the request may fit
+            optional = plan(ladder_defect_correction=0) - plan(ladder_defect_correction=0, hbm_budget_bytes=1)
+            if req.mem - optional <= self.budget:
+                req.mem = plan(hbm_budget_bytes=self.budget)
+                req.opts = {"hbm_budget_bytes": self.budget}
         if req.mem > self.budget:
             req.status, req.error = exacc.ERR_NOMEM, "request exceeds the whole HBM budget"
             req.finished = self.now()
@@ -118,7 +128,7 @@ class Server:
 
     def _run(self, req: Request):
         try:
-            solve_one(req, self.opts)
+            solve_one(req, {**req.opts, **self.opts})
         except Exception as e:  # recorded, not raised: the loop keeps serving
             req.error = str(e)
             req.status = getattr(e, "status", exacc.ERR_DEVICE)
