@@ -47,3 +47,18 @@ def test_df_factors_in_chunks(lib):
     B, _ = exacc.df_factors(C, J, V)
     # the bar of the parity tests
     assert np.abs(B - want).max() <= 1e-12 * max(1.0, np.abs(want).max())
+
+
+# split sums are added in a fixed order: every repeat is the same
+@pytest.mark.parametrize("precision", ["FP64", "MIXED_FP32"])
+def test_split_sums_repeat(lib, precision):
+    from paper_2103_08473_amd import exacc
+    o, v, X = 4, 21, 900
+    eps, B = make_system(o, v, X, seed=3, sigma=0.2)
+    t = make_amplitudes(o, v, seed=5, scale=0.1)
+    with exacc.CCSD(eps, B, o, precision=getattr(exacc, precision)) as cc:
+        cc.set_amplitudes(*t)
+        first = [x.copy() for x in cc.residual()]
+        for _ in range(40):
+            for a, b in zip(first, cc.residual()):
+                assert np.array_equal(a, b)
