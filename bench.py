@@ -9,8 +9,8 @@ timed steps are iterations of a solve that then runs on to convergence.
 Prints one JSON line:
   value         ladder algorithmic TFLOP per iteration (Hermitian tile build plus
                 contraction, exacc_ladder_flops) / wall time of a whole FP64 iteration;
-  roofline      the ladder tile-build kernel (the dominant kernel), timed with HIP
-                events on the library's stream during the timed steps;
+  roofline      the ladder tile build (the dominant stage, INT8 residue planes), timed with
+                HIP events on the library's stream during the timed steps;
   solves        time to solution at ||Delta|| <= 1e-9 of the FP64, mixed FP32 and mixed
                 BF16x3 schedules, their iterations (low precision + FP64), |dE| and
                 max |dT| against the FP64 solve;
@@ -35,44 +35,9 @@ sys.path.insert(0, ROOT)
 PEAK_FP64_MFMA = 78.6  # TFLOP/s, MI355X dense FP64 matrix
 PEAK_FP32_MFMA = 157.3  # TFLOP/s, MI355X dense FP32 matrix
 PEAK_BF16_MFMA = 2516.6  # TFLOP/s, MI355X dense BF16 matrix
+PEAK_INT8_MFMA = 5033.2  # TOP/s, MI355X dense INT8 matrix
+INT8_OPS_PER_CMAC = 60  # 15 moduli, two real products of 2 operations each
 WORKLOAD = dict(nocc=40, nvir=360, naux=1200, seed=0)
-
-
-# HBM bytes per ladder-build launch (mean over the launches of one iteration), from one
-# rocprofv3 pass each of FETCH_SIZE and WRITE_SIZE, scaled by what the counters read for
-# a plain 1 GiB device copy (fetch x2.000, write x1.000), and the kernel's MFMA-busy
-# fraction and clock from a third pass.  They hold for the sources they were taken with:
-# `source_sha256` hashes the FP64 part of gett.hip (up to the BF16x3 section) and the
-# Hermitian ladder driver in exacc.cpp; the figures are reported as null once either
-# text differs.
-TRAFFIC = {"source_sha256": "92d536ddafb423d9bc33633bce1fb9315fdabc8b68f499c7b85fb7e9431cb068",
-           "fetch_bytes": 4.5734e9, "write_bytes": 0.2123e9,
-           "mfma_busy": 0.703, "clock_ghz": 2.34}
-GETT_SRC = os.path.join(ROOT, "paper_2103_08473_amd", "csrc", "gett.hip")
-EXACC_SRC = os.path.join(ROOT, "paper_2103_08473_amd", "csrc", "exacc.cpp")
-BF16_MARK = b"// BF16x3 complex GETT"
-LADDER_MARKS = (b"static void ladder_apply_herm(Handle& h, const Work<R>& w, const R* F, int64_t row_stride,\n"
-                b"                              const TV<R>& Lp, R* Znp, bool bf, bool use_bvs) {",
-                b"// The ring term of the FP64 iterations after a mixed-precision switch")
-
-
-def kernel_source_sha256():
-    import hashlib
-    with open(GETT_SRC, "rb") as f:
-        g = f.read()
-    cut = g.find(BF16_MARK)
-    with open(EXACC_SRC, "rb") as f:
-        e = f.read()
-    i, j = e.find(LADDER_MARKS[0]), e.find(LADDER_MARKS[1])
-    return hashlib.sha256((g[:cut] if cut >= 0 else g) + (e[i:j] if 0 <= i < j else e)).hexdigest()
-
-
-def measured_counters():
-    """Counter-derived HBM bytes per launch and MFMA-busy figures, or None if the kernel or
-    the ladder driver changed since they were taken."""
-    if TRAFFIC["source_sha256"] is None or kernel_source_sha256() != TRAFFIC["source_sha256"]:
-        return None
-    return TRAFFIC
 
 
 def ladder_build_flops(o, v, X):
@@ -529,8 +494,8 @@ def main():
     build_ms = stages.get("ladder_build", float("nan")) / args.steps
     contract_ms = stages.get("ladder_contract", float("nan")) / args.steps
     achieved = ladder_build_flops(o, v, X) / (build_ms * 1e-3) / 1e12
+    int8 = achieved / 8 * INT8_OPS_PER_CMAC
     ladder_ms = build_ms + contract_ms + stages.get("ladder_antisym", 0.0) / args.steps
-    ctr = measured_counters()
     out = {
         "metric": "ladder TFLOP/s + s/CCSD iter, FP64 vs mixed at |dE|<=1e-7 Eh; p99 solve latency",
         "value": round(value, 3),
@@ -553,18 +518,17 @@ def main():
         "residual_last_timed": res,
         "energy": [E.real, E.imag],
         "stage_ms_per_iter": {k: round(t / args.steps, 2) for k, t in stages.items()},
-        "roofline": {"bound": "mfma", "kernel": "ladder tile build (GETT kind 1)",
-                     "achieved": round(achieved, 3), "peak": PEAK_FP64_MFMA, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_FP64_MFMA, 4),
-                     "traffic": (ctr["fetch_bytes"] + ctr["write_bytes"]) if ctr else None,
-                     "traffic_unit": "bytes per launch (HBM, counter-derived)",
+        "roofline": {"bound": "mfma", "kernel": "ladder tile build (INT8 residue planes)",
+                     "achieved": round(int8, 3), "peak": PEAK_INT8_MFMA, "unit": "TOP/s",
+                     "frac": round(int8 / PEAK_INT8_MFMA, 4),
+                     "fp64_equivalent_tflops": round(achieved, 3),
+                     "fp64_equivalent_over_fp64_peak": round(achieved / PEAK_FP64_MFMA, 4),
+                     "traffic": None,
                      "algorithmic_bytes_per_launch": round(ladder_build_bytes(o, v, X)),
-                     "flops_counted": "8 real flops per complex multiply-add of the Hermitian build "
-                                      "(blocks on and above the pair diagonal); the kernel's "
-                                      "3-multiplication complex product issues 6",
-                     "hw_frac": round(0.75 * achieved / PEAK_FP64_MFMA, 4),
-                     "counters": ({"mfma_busy": ctr["mfma_busy"], "clock_ghz": ctr["clock_ghz"]}
-                                  if ctr else None)},
+                     "flops_counted": "INT8 operations of the Hermitian build (blocks on and above "
+                                      "the pair diagonal), 60 per complex multiply-add, over the "
+                                      "stage's time, splitting and reconstruction included; "
+                                      "fp64_equivalent: 8 flops per complex multiply-add"},
         "solves": solves,
     }
     out.update(extra)

@@ -145,8 +145,8 @@ __global__ void copy_rows_kernel(double* __restrict__ dst, const double* __restr
 
 // Intermediates: the first half transform runs over chunks of Q (rows p too where one Q does not
 // fit) and is finished into B itself, and the metric product runs over column chunks of B
-// copied out first, so neither is held whole (7.7 GB at 600/400/1200, cleared by the driver
-// on each call; the extra copy is 1.5 ms).
+// copied out first, so neither is held whole (7.7 GB at 600/400/1200, cleared when it is
+// allocated on each call; the extra copy is 1.5 ms).
 constexpr size_t kChunk = (size_t)128 << 20;
 size_t chunk_bytes(int m, int n, int X) {
   return std::min(kChunk, up256((size_t)X * n * m * 16)) + std::min(kChunk, up256((size_t)X * n * n * 16));
