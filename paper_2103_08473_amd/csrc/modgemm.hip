@@ -921,10 +921,11 @@ void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_
 }
 
 // ---------------------------------------------------------------- triples
-// nvir 126 per triple: FP64 products 49 us; here 22.9 (1.0 POP/s: 6 stages of K per tile, 70 MB
-// of planes and residues moved) and 11.5 for the reconstruction.  With the products of a batch
-// one after the other instead of side by side along n the planes of V_j and V_k are read from
-// memory for each: 24.6 us.
+// nvir 126 per triple: FP64 products 49 us; here 20 (1.2 POP/s: 6 stages of K per tile, 70 MB
+// of planes and residues moved) and 11.5 for the reconstruction.  Tiles of 8 x 4 blocks, two
+// workgroups per CU, which load 1.2 times the operand bytes, took 22.9, of 4 x 4 blocks 28;
+// with the products of a batch one after the other instead of side by side along n, the planes
+// of V_j and V_k are read from memory for each, 1.7 more.
 // Per triple the FP64 tiles take TFP us at 62 TFLOP/s (K = nvir in three passes over the
 // output), the residues their plane products and one reconstruction (the estimates of
 // mod_gemm_pays; splitting is amortised over nocc^2 / 6 triples per operand).
@@ -1017,7 +1018,7 @@ void ModTriples::rows(int i0, int ni, int j, int k, double* We, hipStream_t s) c
     }
     g.c_bat = cb;
     if (nb_ <= 4)
-      launch_planes<2, 2, 4, 2, 2, 2, true>(g, s);
+      launch_planes<4, 2, 4, 2, 1, 1, true>(g, s);
     else
       launch_planes<2, 4, 4, 2, 1, 1, true>(g, s);
     Gett<double> c{};
