@@ -281,8 +281,7 @@ struct Handle {
     set_gett_workspace(ws, ws_bytes);
     set_mod_workspace(mod_ws, mod_ws ? P.bytes_mod : 0);
   }
-  // Give the residue workspace back (memory is short); recorded graphs address it, and so may
-  // the calling thread's setting, made by use() earlier in the same call.
+  // Give the residue workspace back (memory is short); recorded graphs address it.
   bool release_mod() {
     if (!mod_ws) return false;
     HIPCHECK(hipStreamSynchronize(s));
@@ -291,7 +290,6 @@ struct Handle {
         (void)hipGraphExecDestroy(g);
         g = nullptr;
       }
-    set_mod_workspace(nullptr, 0);
     dfree(mod_ws);
     return true;
   }
