@@ -54,6 +54,8 @@ struct Gett {
   R* ws;       // split-K partial sums [z][batch][m][n] (unscaled)
   FastDiv m_div, n_div, k_div;  // of m_in, n_in, k_in (filled at launch)
   int tri;  // if not 0: only outputs with n / tri > m / tri are wanted (others may be left unset)
+  // if not null: the product is formed only where *when (on the device) is above 1, see mod_gemm
+  const int* when;
 };
 
 // Scratch the calling thread's GETT launches may use for split-K partials.
@@ -72,23 +74,29 @@ enum GettKind {
 template <typename R>
 void launch_gett(const Gett<R>& g, int kind, hipStream_t s);
 
-// FP64 products on the INT8 matrix cores (modgemm.hip): true when the product was launched,
-// false when it is not worth it or has no room in the thread's workspace.
+// FP64 products on the INT8 matrix cores (modgemm.hip), for one product without a batch: null
+// when it is not worth it or has no room in the thread's workspace, else a device int that is 0 or
+// 1 where the product was formed and 2 where its operands are too uneven for it (C untouched): the
+// caller launches the FP64 kernel behind it with Gett::when set to that.
 void set_mod_workspace(void* p, size_t bytes);
 bool mod_gemm_pays(int64_t M, int64_t N, int64_t K);
-int64_t mod_plane_bytes(int64_t rows, int64_t K);  // residues of a rows x K operand
-int64_t mod_out_bytes(int64_t M, int64_t N);       // residues of an M x N product
-bool mod_gemm(const Gett<double>& g, hipStream_t s);
+int64_t mod_operand_bytes(int64_t rows, int64_t K);  // residues and scales of a rows x K operand
+int64_t mod_out_bytes(int64_t M, int64_t N);         // residues of an M x N product
+bool mod_gemm_wanted(const Gett<double>& g);
+const int* mod_gemm(const Gett<double>& g, hipStream_t s);
 
 // Antisymmetrised ladder tiles from factor rows F[a][c][P] (row a at F + a row_stride complex
 // elements, [c][P] contiguous) whose residues are formed once and kept at the front of the
 // thread's workspace while the object lives.  ok() is false where that does not fit or pay.
 // Per-row FP64 products of small nvir fill the chip badly, so the line lies low: nvir 87,
-// naux 259: builds and antisymmetrise passes 3.4 ms on FP64 tiles, see exacc.cpp.
+// naux 259: builds and antisymmetrise passes 3.4 ms on FP64 tiles, see exacc.cpp.  level: how the
+// rows of F bear residues (0, 1: 16, 17 moduli; 2: not, FP64 tiles), from level(), which waits
+// for the device: once for factors that stay.
 constexpr int kModLadderNvir = 64, kModLadderNaux = 128;
 class ModLadder {
  public:
-  ModLadder(const double* F, int64_t row_stride, int v, int X, hipStream_t s);
+  ModLadder(const double* F, int64_t row_stride, int v, int X, int level, hipStream_t s);
+  static int level(const double* F, int64_t row_stride, int v, int X, hipStream_t s);
   ~ModLadder();
   ModLadder(const ModLadder&) = delete;
   ModLadder& operator=(const ModLadder&) = delete;
@@ -97,11 +105,13 @@ class ModLadder {
   void rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_t ldw, hipStream_t s) const;
 
  private:
-  int v_ = 0, X_ = 0;
+  int v_ = 0, X_ = 0, level_ = 2;
   int* exps_ = nullptr;
   signed char* planes_ = nullptr;
   size_t held_ = 0;
 };
+
+struct PlaneGemm;
 
 // The e-sums of the triples' W by exact residues: <ab||ie> of all i and t2 are split once, and
 // per triple We[(a<b)][c] = - sum_e (V_i t_jk + V_j t_ki + V_k t_ij) is one plane product over
@@ -117,7 +127,8 @@ class ModTriples {
   void rows(int i0, int ni, int j, int k, double* We, hipStream_t s) const;
 
  private:
-  int o_, v_, ni_, mb_, nb_;
+  PlaneGemm segments(int i, int j, int k, int64_t unit) const;
+  int o_, v_, ni_, mb_, nb_, level_ = 0;
   int *ea_, *eb_;
   signed char *pa_, *pb_, *out_;
 };

@@ -232,7 +232,6 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
   const size_t left = cap > cv.used ? (cap - cv.used) / 256 * 256 : 0;
   const size_t wsb = std::min(left, ws_cap);
   set_gett_workspace(wsb >= (1u << 20) ? cv.take(wsb) : nullptr, wsb >= (1u << 20) ? wsb : 0);
-  set_mod_workspace(mod, mod_bytes);
   Readback rb(s, lag);
   // scale: c = max_i sum_j |V_ij| bounds the spectrum of the symmetric V from above
   hipLaunchKernelGGL(row_abs_sum_kernel, dim3(nblk(X, 1024)), dim3(kTB), 0, s, Vd, X, part);
@@ -278,6 +277,10 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
     raise(-1, "DF factors: the inverse square root iteration did not converge (metric not positive "
               "definite or too ill-conditioned)");
 
+  // Residues for the transforms and the fit only.  Z and Y are nearly diagonal up to the norms of
+  // the functions, so that the products above fail the residues' test as a rule (naux 1200: 32 of
+  // 36, at 40 us each for nothing).
+  set_mod_workspace(mod, mod_bytes);
   // (pq|Q) = sum_mu nu conj(C_mu p) (mu nu|Q) C_nu q into B, chunks of Q (and p); then
   // B[P][p][q] = sum_Q [V^-1/2]_PQ (pq|Q), chunks of pq
   for (int q0 = 0; q0 < X; q0 += qc)

@@ -79,13 +79,13 @@ static size_t mod_workspace_bytes(const Plan& p) {
   constexpr int64_t kModCap = 10ll << 30, kOut = 512ll << 20;
   const int64_t v32 = (p.v + 31) / 32 * 32;
   int64_t want = 0;
-  if (mod_gemm_pays(ov, ov, ov)) want = 2 * mod_plane_bytes(ov, ov) + std::min(kOut, mod_out_bytes(ov, ov));
+  if (mod_gemm_pays(ov, ov, ov)) want = 2 * mod_operand_bytes(ov, ov) + std::min(kOut, mod_out_bytes(ov, ov));
   if (p.v > kModLadderNvir && p.X >= kModLadderNaux && p.Po > 0) {
     // the factor rows, and tiles or the operands of the products with W in turn
     const int64_t tiles = std::min(kOut, mod_out_bytes(8 * v32, (int64_t)p.v * v32));
-    const int64_t prod = mod_plane_bytes(p.Po, p.Pv) + std::min(2 * kOut, mod_plane_bytes(p.chunk_pairs, p.Pv)) +
+    const int64_t prod = mod_operand_bytes(p.Po, p.Pv) + std::min(2 * kOut, mod_operand_bytes(p.chunk_pairs, p.Pv)) +
                          std::min(kOut, mod_out_bytes(p.Po, p.chunk_pairs));
-    want = std::max(want, mod_plane_bytes((int64_t)p.v * v32, p.X) + std::max(tiles, prod) + 4 * p.v * v32);
+    want = std::max(want, mod_operand_bytes((int64_t)p.v * v32, p.X) + std::max(tiles, prod) + 4 * p.v * v32);
   }
   return want ? (size_t)std::min(want + (16 << 20), kModCap) : 0;
 }
@@ -242,6 +242,7 @@ struct Handle {
   // built from the current amplitudes and no other call has reused those buffers since.
   struct Lam {
     bool prepared = false;
+    int lad_level = 2;       // see ModLadder, of Bd
     double *lam = nullptr;   // [l1 (o v), l2 (i<j, a<b)], L complex
     double *l1w, *Lq, *Z1, *Bd, *Wooov, *O3a, *O3b, *LTp, *Q1, *gP, *gt, *s1, *gam;
   } lam;
@@ -250,6 +251,7 @@ struct Handle {
   double* redout = nullptr;   // reduced values (device)
   double* host = nullptr;     // pinned readback
   int* rowmap_o = nullptr;    // k*o+l for pairs k<l
+  int lad_level = 2;          // see ModLadder, of the factors B_vv
   // DIIS state
   std::vector<int> order;     // slot ids, oldest first
   std::vector<std::vector<zc>> G;
@@ -574,7 +576,7 @@ static void ladder_apply(Handle& h, const Work<R>& w, const R* F, int64_t row_st
   std::optional<ModLadder> mod;  // FP64: tiles from residues of the factor rows, formed once
   if constexpr (sizeof(R) == sizeof(double)) {
     Scope sc(h, "ladder_build");
-    mod.emplace(F, row_stride, v, X, s);
+    mod.emplace(F, row_stride, v, X, h.lam.lad_level, s);
   }
   for (int a = 0; a + 1 < v; ++a) {
     const int nb = v - a - 1;
@@ -665,7 +667,7 @@ static void ladder_apply_herm(Handle& h, const Work<R>& w, const R* F, int64_t r
   std::optional<ModLadder> mod;  // FP64: tiles from residues of the factor rows, formed once
   if constexpr (sizeof(R) == sizeof(double)) {
     Scope sc(h, "ladder_build");
-    mod.emplace(F, row_stride, v, X, s);
+    mod.emplace(F, row_stride, v, X, h.lad_level, s);
   }
   for (const LadderChunk& ch : ladder_chunks(v, cap, tail_t)) {
     const int a0 = ch.a0, wv = v - a0;
@@ -1851,6 +1853,7 @@ static void lambda_prepare(Handle& h) {
   // dressed factor Bd[a][e][P] = B^P_ea - sum_m t_m^e B^P_ma (B^P_qp = conj(B^P_pq))
   k_conj_rows(L.Bd, b.Bvv.p, v, (int64_t)n * X, (int64_t)v * X, s);
   contract(s, "amP,me->aeP", MONE, conj(b.Bvo), t1, true, view(L.Bd, {v, v, X}));
+  if (Po > 0 && !h.P.ladder_grouped) L.lad_level = ModLadder::level(L.Bd, (int64_t)v * X, v, X, s);
   L.prepared = true;
 }
 
@@ -2216,6 +2219,8 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     h->Ta = h->dalloc(h->P.ladder_grouped ? h->P.vv * h->P.vv : (int64_t)v * std::max(1, v - 1) * v);
     h->W = h->dalloc(P.chunk_pairs * std::max<int64_t>(1, P.Pv));
     h->use();
+    if (P.Po > 0 && !P.ladder_grouped && !op.cc2)
+      h->lad_level = ModLadder::level(bviews(*h, h->Bt).Bvv.p, (int64_t)n * X, v, X, h->s);
     HIPCHECK(hipMemsetAsync(h->x, 0, P.L * 16, h->s));
     HIPCHECK(hipStreamSynchronize(h->s));
     timer_collect(*h);

@@ -97,6 +97,7 @@ __device__ __forceinline__ C2<R> ldc(const R* p, int64_t off) {
 
 template <typename R, int BM, int BN, int BK, bool DB, bool AKF, bool BKF, int KIND>
 __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
+  if (g.when && *g.when <= 1) return;
   constexpr int NBUF = DB ? 2 : 1;  // DB: double-buffered LDS, one barrier per k-tile
   constexpr int RS = 256 / BK;      // tile rows per loader pass (k-fast operands)
   constexpr int LA = BM + 1;  // odd row pitch: conflict-free k-major stores
@@ -399,6 +400,7 @@ __global__ __launch_bounds__(256, 2) void gett_kernel(Gett<R> g) {
 // and MFMA rounds of a 32 x 32 tile.
 template <typename R, int W>
 __global__ __launch_bounds__(64 * W, 4) void gett_tiny_kernel(Gett<R> g) {
+  if (g.when && *g.when <= 1) return;
   typedef typename MF<R>::acc_t acc_t;
   constexpr int U = 4;
   __shared__ R red[W - 1][12][64];
@@ -500,6 +502,7 @@ __global__ __launch_bounds__(64 * W, 4) void gett_tiny_kernel(Gett<R> g) {
 // C[b](m, n) = alpha * sum_z ws[z][b][m][n] (+ C), fixed summation order.
 template <typename R>
 __global__ __launch_bounds__(256) void gett_splitk_reduce(Gett<R> g, int nz, int nb) {
+  if (g.when && *g.when <= 1) return;
   const int64_t MN = (int64_t)g.M * g.N, tot = MN * nb;
   for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < tot; t += (int64_t)gridDim.x * 256) {
     const int64_t b = t / MN, mn = t - b * MN;
@@ -1186,8 +1189,26 @@ void launch_gett(const Gett<R>& g, int kind_in, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nbatch <= 0) return;
   if ((int64_t)((g.M + 63) / 64) * ((g.N + 63) / 64) > 0x7fffffffLL)
     raise(-1, "contraction too large for one launch");
-  if constexpr (sizeof(R) == sizeof(double))
-    if (mod_gemm(g, s)) return;
+  // large FP64 products: residues, and behind them, for operands that residues are not for, the
+  // kernel of this file, each product of a batch by itself
+  if constexpr (sizeof(R) == sizeof(double)) {
+    if (!g.when && mod_gemm_wanted(g)) {
+      for (int q = 0; q < g.nbatch; ++q) {
+        Gett<R> h = g;
+        h.nbatch = 1;
+        h.A = g.A + 2 * (int64_t)q * g.a_b;
+        h.B = g.B + 2 * (int64_t)q * g.b_b;
+        h.C = g.C + 2 * (int64_t)q * g.c_b;
+        h.when = mod_gemm(h, s);
+        if (!h.when) {  // no room: sizes and workspace are the same for every product of the batch
+          if (q > 0) raise(-3, "residue products of one batch took different routes");
+          break;
+        }
+        launch_gett(h, kind_in, s);
+        if (q + 1 == g.nbatch) return;
+      }
+    }
+  }
   // BF16x3 kinds: only for FP32 operands that are K-contiguous in both A and B; 16-byte
   // loads of two complex values where row strides are even and bases 16-byte aligned
   const bool kcontig = g.k_in == g.K && g.a_ki == 1 && g.b_ki == 1;

@@ -4,11 +4,11 @@
 // 0.8 to 0.95 of it on large products.  The INT8 rate is about 64 times higher, so a large
 // product is formed exactly on integers instead, in a residue number system:
 //   * every operand row a_m is scaled by a power of two to the 2-norm range (2^(S-1), 2^S]
-//     and rounded to integers (S = 55 or 58 bits, more than the 53 of a double);
+//     and rounded to integers (S = 58 or 61 bits, more than the 53 of a double);
 //   * modulo a prime (or product of primes) p = 1 mod 4 there is j with j^2 = -1, and a
 //     complex integer x + iy is held as the pair (x + jy, x - jy) mod p: in this form a
 //     complex product is two real products (the quadratic residue number system of
-//     Leung and of Jenkins and Krogmeier), so 15 or 16 moduli give 30 or 32 INT8 planes;
+//     Leung and of Jenkins and Krogmeier), so 16 or 17 moduli give 32 or 34 INT8 planes;
 //   * per plane one INT8 GEMM with INT32 accumulation (exact: |sum| <= K (p/2)^2 < 2^31 for
 //     K <= kMaxK), reduced mod p to one byte per output;
 //   * the Chinese remainder theorem gives the exact integer product back: by the
@@ -17,7 +17,21 @@
 //     exact high part (multiples of 2^-42) and an FP64 remainder.
 // The only rounding is that of the scaled operands to integers (relative to the row's norm)
 // and of the result to FP64; sums over k are exact, so results do not depend on tiling.
-// A row with a non-finite element gives NaN outputs.
+//
+// That rounding is relative to |a_m| |b_n|, an FP64 sum's to sum_k |a_mk| |b_nk|, which is far
+// smaller where the entries of a row differ in size and the large ones of a_m meet the small
+// ones of b_n.  So each product is tested before it is formed: one further INT8 plane holds the
+// rows' magnitudes in units of 1/32 of the row's rms, rounded down and cut at 127, and its product
+// bounds sum_k |a_mk| |b_nk| from below for every output.  The largest ratio F of |a_m| |b_n| to that
+// bound picks 16 moduli (F <= kFlat), 17 (F <= 8 kFlat) or the FP64 kernel, which is launched
+// behind every residue product and returns at once unless it is wanted: no host decision, so
+// a recorded graph decides anew on each replay.  Rows that are not finite, or whose squares leave
+// the range of a double, take the FP64 kernel too.
+// rms error over sum |a||b| in units of 2^-53, K 1131, the sums in the FP64 kernel's form against
+// 58 and 61 bits (80-bit reference): Gaussian entries, F 1.7, 0.28 (re) | 0.023, 0.011; scales
+// along k opposed by 1 decade, F 4.0, 0.28 | 0.049, 0.012; lognormal sizes, F 10, 0.70 | 0.071,
+// 0.030; scales opposed by 2 decades, F 29, 0.27 | 0.24, 0.033; by 4, F 64000, 0.26 | 12, 1.5.
+// An FP64 sum split over K in eight has a third of these errors, which is where kFlat lies.
 #include <algorithm>
 #include <cmath>
 #include <cstdint>
@@ -25,14 +39,42 @@
 #include "common.h"
 
 namespace exacc {
+
+constexpr int kNP = 17;           // most moduli
+
+// Which moduli a launch takes: 0, 1 (see Tabs), or 2, none at all; read from the device where
+// the product's test has left it, or known.
+struct Level {
+  const int* flag;
+  int known;
+};
+struct PlaneGemm {
+  const signed char *A, *B;
+  signed char* C;              // [mblk][nblk][z][lane][q][r]: row 8 q + 4 (lane / 32) + r, column lane % 32
+  int mb, nb, kb;              // kb even
+  int a_in, a_outer;           // A block of m-block x: (x / a_in) * a_outer + x % a_in
+  int b_in, b_outer;           // likewise B
+  int tiles_m, tiles_n;
+  Level lv;                    // 2 (16 + level) of the kPlanes that the layouts have room for
+  int p[kNP];
+  // TEST kernels: one plane, of magnitudes; rows' and columns' flatness and where the level goes
+  const float *fa, *fb;
+  float flat;                  // kFlat, less where a product's rounding is more
+  int* out;
+  // SEG kernels: k in three segments of kb / 3 blocks, segment q of product y of a batch at
+  // 16-byte units a_seg[q] + y a_bat[q] of A (B likewise), C of product y c_bat bytes further
+  int batch;
+  int64_t a_seg[3], b_seg[3], a_bat[3], b_bat[3], c_bat;
+};
+
 namespace {
 
-constexpr int kNP = 16;           // most moduli; see moduli_for
 constexpr int kPlanes = 2 * kNP;
 constexpr int kMaxK = 131072;     // K (p / 2)^2 < 2^31 with p <= 241
 constexpr int kShortK = 1152;     // K (p / 2)^2 + 128 < 2^24
-constexpr int kNaN = 0x40000000;  // exponent of a row that holds a non-finite element
-constexpr int kZero = 4096;       // of a row of zeros: above that of any other finite row
+constexpr int kZero = 4096;       // exponent of a row of zeros: above that of any other
+constexpr double kUnit = 32.0;    // units of a magnitude in its row's rms
+constexpr float kFlat = 6.0f;     // largest F (see the top) that 16 moduli are taken for
 
 typedef int i4v __attribute__((ext_vector_type(4)));
 typedef int i16v __attribute__((ext_vector_type(16)));
@@ -40,7 +82,7 @@ typedef double d2v __attribute__((ext_vector_type(2)));
 typedef unsigned __int128 u128;
 
 // Pairwise coprime products of primes = 1 mod 4 (so that -1 has a square root), largest first.
-constexpr int kMods[16] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97};
+constexpr int kMods[kNP] = {241, 233, 229, 221, 205, 197, 193, 181, 173, 157, 149, 137, 113, 109, 101, 97, 89};
 
 struct ModTab {
   int np;  // moduli in use
@@ -102,20 +144,22 @@ ModTab make_tab(int np) {
   return t;
 }
 
-// 15 moduli (S = 55) or 16 (S = 58).  The operands' rounding grows with sqrt(K) like the FP64
-// GETT's sums do, and 15 moduli stay below those (relative rms error of re / im against
-// 80-bit sums, FP64 GETT | 15 moduli: K 504 7.0e-16 / 1.2e-15 | 5.4e-16, 1131 6.4e-16 / 1.1e-15 |
-// 7.2e-16, 4032 2.1e-15 / 3.8e-15 | 1.5e-15, 8000 1.7e-15 / 3.0e-15 | 1.5e-15) but where the
-// FP64 GETT splits a long K into short chains (600 x 700 x 40000 1.7e-15 / 2.9e-15 | 5.9e-15):
-// there 16 are taken (7.2e-16).
-const ModTab& tab(int np) {
-  static const ModTab t15 = make_tab(15), t16 = make_tab(16);
-  return np == 15 ? t15 : t16;
+// Both choices of moduli: t[0] 16 of them (S = 58), t[1] 17 (S = 61).  Scale exponents are
+// those of t[1]; t[0] takes kShift less.
+struct Tabs {
+  ModTab t[2];
+};
+constexpr int kShift = 3;
+const Tabs& tabs() {
+  static const Tabs t = [] {
+    Tabs x{{make_tab(16), make_tab(17)}};
+    if (x.t[1].S - x.t[0].S != kShift) raise(-3, "residue tables");
+    return x;
+  }();
+  return t;
 }
-int moduli_for(int64_t M, int64_t N, int64_t K) {
-  const bool split = ((M + 63) / 64) * ((N + 63) / 64) < 1024;
-  return K <= 8192 || !split ? 15 : 16;
-}
+
+__device__ __forceinline__ int level_of(const Level& l) { return l.flag ? *l.flag : l.known; }
 
 __device__ __forceinline__ int64_t cmap(int x, int in, int64_t so, int64_t si) {
   const int q = x / in;
@@ -136,79 +180,127 @@ struct Src {
   // zero past rows and K.  All planes of 32 rows x 64 k are together, so that splitting writes
   // whole 64 KiB runs (a plane-major order: 2.3 TB/s at 12363^2, this one: see mod_split_kernel)
   signed char* planes;
-  int* exps;        // power of two each row was scaled by
+  int* exps;        // power of two each row was scaled by (of t[1], see Tabs)
+  // magnitudes, max(|re|, |im|) in units of the row's rms / kUnit, rounded down and at most 127, in
+  // the order of the planes without z, and per row its norm in that unit: 0 for a row of zeros,
+  // infinite for a row that residues are not for
+  signed char* mags;
+  float* flat;
+  double* norm;     // if not null: per row its norm (0 where it is not in range)
   int rb, kb;       // 32-row and 32-k blocks (kb even)
 };
 
-// Scale exponents: per row the largest |component| and the sum of squares (fixed order).
-// kfast: tpr threads per row; else 32 rows x 32 k phases per workgroup.  Bound by reading
-// the operand once.
-__global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src b, int tpr_a, int tpr_b, int S) {
+// Scale exponents, magnitudes and flatness of all rows of an operand, padding included: per row
+// the largest |component| and the sum of squares (fixed order), then the magnitudes, of which each
+// thread has kept its first kKeep entries' (the upper words, below the entries themselves); a
+// longer row is read again.  kfast: tpr threads per row; else 32 rows x 32 k phases per workgroup.
+// what: 1 the scales, 2 the magnitudes (with the norms of an earlier launch where 1 is left
+// out), 3 both.  Bound by reading the operand.
+__global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src b, int tpr_a, int tpr_b, int S,
+                                                        int what, int* flag) {
   const bool first = (int)blockIdx.x < blocks_a;
   const Src s = first ? a : b;
   const int blk = first ? blockIdx.x : blockIdx.x - blocks_a;
   const int tid = threadIdx.x;
   __shared__ double ssum[1024], smax[1024];
-  int row, k0, kstep, stride, width;
+  if (flag && blockIdx.x == 0 && tid == 0) *flag = 0;
+  int row, k0, width, stride;
   if (s.kfast) {
-    const int tpr = first ? tpr_a : tpr_b;
-    row = s.row0 + blk * (1024 / tpr) + tid / tpr;
-    k0 = tid % tpr;
-    kstep = width = tpr;
+    width = first ? tpr_a : tpr_b;
+    row = blk * (1024 / width) + tid / width;
+    k0 = tid % width;
     stride = 1;
   } else {
-    row = s.row0 + blk * 32 + (tid & 31);
+    width = 32;
+    row = blk * 32 + (tid & 31);
     k0 = tid >> 5;
-    kstep = width = 32;
     stride = 32;
   }
-  double sum = 0.0, mx = 0.0;
-  if (row < s.rows && (s.r_valid == 0 || row % s.r_in < s.r_valid)) {
-    const double* p = s.p + 2 * cmap(row, s.r_in, s.r_so, s.r_si);
-    if (s.k_in == s.K) {
-#pragma unroll 4
-      for (int k = k0; k < s.K; k += kstep) {
-        const d2v x = *reinterpret_cast<const d2v*>(p + 2 * (int64_t)k * s.k_si);
-        sum += x.x * x.x + x.y * x.y;
-        mx = fmax(mx, fmax(fabs(x.x), fabs(x.y)));
+  const bool has = row < s.rows && (s.r_valid == 0 || row % s.r_in < s.r_valid);
+  const bool plain = s.k_in == s.K;
+  const double* p = has ? s.p + 2 * cmap(row, s.r_in, s.r_so, s.r_si) : nullptr;
+  auto at = [&](int k) {
+    return *reinterpret_cast<const d2v*>(p + 2 * (plain ? (int64_t)k * s.k_si : cmap(k, s.k_in, s.k_so, s.k_si)));
+  };
+  constexpr int kKeep = 32, kG = 8;
+  unsigned keep[kKeep] = {};
+  double sum = 0.0, mx = 0.0, norm = 0.0;
+  if (what & 1) {
+    if (has) {
+#pragma unroll
+      for (int j = 0; j < kKeep; j += kG) {
+        if (j * width >= s.K) break;
+        d2v x[kG];
+#pragma unroll
+        for (int i = 0; i < kG; ++i) x[i] = at(min(k0 + (j + i) * width, s.K - 1));
+#pragma unroll
+        for (int i = 0; i < kG; ++i) {
+          if (k0 + (j + i) * width >= s.K) x[i] = d2v{0.0, 0.0};
+          const double m = fmax(fabs(x[i].x), fabs(x[i].y));
+          sum += x[i].x * x[i].x + x[i].y * x[i].y;
+          mx = fmax(mx, m);
+          keep[j + i] = (unsigned)__double2hiint(m);
+        }
       }
-    } else {
 #pragma unroll 4
-      for (int k = k0; k < s.K; k += kstep) {
-        const d2v x = *reinterpret_cast<const d2v*>(p + 2 * cmap(k, s.k_in, s.k_so, s.k_si));
+      for (int k = k0 + kKeep * width; k < s.K; k += width) {
+        const d2v x = at(k);
         sum += x.x * x.x + x.y * x.y;
         mx = fmax(mx, fmax(fabs(x.x), fabs(x.y)));
       }
     }
-  }
-  ssum[tid] = sum;
-  smax[tid] = mx;
-  __syncthreads();
-  for (int w = width / 2; w > 0; w >>= 1) {
-    if (k0 < w) {
-      ssum[tid] += ssum[tid + w * stride];
-      smax[tid] = fmax(smax[tid], smax[tid + w * stride]);
-    }
+    ssum[tid] = sum;
+    smax[tid] = mx;
     __syncthreads();
-  }
-  if (k0 == 0 && row < s.rows) {
-    sum = ssum[tid];
-    mx = smax[tid];
-    int e = kZero;
-    if (sum != sum || mx > 1.7976931348623157e308) {
-      e = kNaN;
-    } else if (mx > 0.0) {
-      int ex;
-      if (sum > 1e-280 && sum < 1e300) {  // norm < 2^(ex / 2)
-        (void)frexp(sum, &ex);
-        ex = (ex + 1) >> 1;
-      } else {  // squares out of range: norm <= max sqrt(2 K)
-        (void)frexp(mx, &ex);
-        ex += (33 - __clz(2 * s.K)) >> 1;
+    for (int w = width / 2; w > 0; w >>= 1) {
+      if (k0 < w) {
+        ssum[tid] += ssum[tid + w * stride];
+        smax[tid] = fmax(smax[tid], smax[tid + w * stride]);
       }
-      e = S - ex;
+      __syncthreads();
     }
-    s.exps[row] = e;
+    sum = ssum[tid - k0 * stride];
+    mx = smax[tid - k0 * stride];
+    // (a sum that is not finite fails the second comparison)
+    const bool ok = sum > 1e-280 && sum < 1e300;
+    if (k0 == 0 && row < 32 * s.rb) {
+      int ex = 0;
+      if (ok) {
+        (void)frexp(sum, &ex);  // norm < 2^(ex / 2)
+        ex = (ex + 1) >> 1;
+      }
+      s.exps[row] = ok ? S - ex : kZero;
+      const bool zero = sum == 0.0 && mx == 0.0;
+      s.flat[row] = zero ? 0.0f : ok ? (float)(kUnit * sqrt((double)s.K)) : __builtin_huge_valf();
+      if (s.norm) s.norm[row] = ok ? sqrt(sum) : 0.0;
+    }
+    if (ok) norm = sqrt(sum);
+  } else if (row < s.rows) {
+    norm = s.norm[row];
+  }
+  if (!(what & 2) || row >= 32 * s.rb) return;
+  const double inv = norm > 0.0 ? kUnit * sqrt((double)s.K) / norm : 0.0;
+  signed char* out = s.mags + (int64_t)(row >> 5) * (s.kb / 2) * 2048 + (row & 31) * 16;
+  auto put = [&](int k, double m) {
+    out[(int64_t)(k >> 6) * 2048 + ((k >> 5) & 1) * 1024 + ((k >> 4) & 1) * 512 + (k & 15)] =
+        (signed char)(int)fmin(m * inv, 127.0);
+  };
+  if (what & 1) {
+#pragma unroll
+    for (int j = 0; j < kKeep; ++j) {
+      const int k = k0 + j * width;
+      if (j * width >= 32 * s.kb) break;
+      if (k < 32 * s.kb) put(k, __hiloint2double((int)keep[j], 0));
+    }
+  }
+#pragma unroll 4
+  for (int k = k0 + (what & 1 ? kKeep * width : 0); k < 32 * s.kb; k += width) {
+    double m = 0.0;
+    if (has && k < s.K && inv > 0.0) {
+      const d2v x = at(k);
+      m = fmax(fabs(x.x), fabs(x.y));
+    }
+    put(k, m);
   }
 }
 
@@ -217,7 +309,11 @@ __global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src
 // 32 x 32 block, 16 k per lane: x mod p is a dot product of the digits with 256^d mod p (two
 // 4-byte dot instructions) and one rounding step, 16 instructions per element and modulus
 // against 16 bytes read and 4 written.
-__global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src b, ModTab t) {
+__global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src b, Level lv, Tabs tt) {
+  const int level = level_of(lv);
+  if (level > 1) return;
+  const ModTab& t = tt.t[level];
+  const int shift = level ? 0 : kShift;
   const bool first = (int)blockIdx.x < blocks_a;
   const Src s = first ? a : b;
   const int blk = first ? blockIdx.x : blockIdx.x - blocks_a;
@@ -249,9 +345,9 @@ __global__ __launch_bounds__(256) void mod_split_kernel(Src a, int blocks_a, Src
     const int r = r0 + rstep * q, kk = kk0 + kstep * q;
     d2v x = {0.0, 0.0};
     const bool pad = s.r_valid && (rowb + r) % s.r_in >= s.r_valid;
-    if (rowb + r < s.rows && kgrp * 64 + kk < s.K && es[q] != kNaN && !pad) {
-      x.x = rint(ldexp(xs[q].x, es[q]));
-      x.y = rint(ldexp(s.conj ? -xs[q].y : xs[q].y, es[q]));
+    if (rowb + r < s.rows && kgrp * 64 + kk < s.K && !pad) {
+      x.x = rint(ldexp(xs[q].x, es[q] - shift));
+      x.y = rint(ldexp(s.conj ? -xs[q].y : xs[q].y, es[q] - shift));
     }
     // digits: the bytes of x + 0x80..80, each less 128 (flipping the top bit does that)
     constexpr uint64_t kBias = 0x8080808080808080ull;
@@ -307,20 +403,6 @@ __device__ __forceinline__ void tile_of(int id, int n, int tiles_m, int tiles_n,
 typedef __attribute__((address_space(3))) void lds_void;
 typedef const __attribute__((address_space(1))) void global_void;
 
-struct PlaneGemm {
-  const signed char *A, *B;
-  signed char* C;              // [mblk][nblk][z][lane][q][r]: row 8 q + 4 (lane / 32) + r, column lane % 32
-  int mb, nb, kb;              // kb even
-  int a_in, a_outer;           // A block of m-block x: (x / a_in) * a_outer + x % a_in
-  int b_in, b_outer;           // likewise B
-  int tiles_m, tiles_n;
-  int planes;                  // 2 np of the kPlanes that the layouts have room for
-  int p[kNP];
-  // SEG kernels: k in three segments of kb / 3 blocks, segment q of product y of a batch at
-  // 16-byte units a_seg[q] + y a_bat[q] of A (B likewise), C of product y c_bat bytes further
-  int batch;
-  int64_t a_seg[3], b_seg[3], a_bat[3], b_bat[3], c_bat;
-};
 
 // C[z] = A[z] B[z]^T mod p: WM x WN waves of TM x TN 32 x 32 blocks, stages of 64 k in three
 // LDS buffers filled by direct global-to-LDS loads, two stages ahead.  Operands lie in
@@ -330,9 +412,15 @@ struct PlaneGemm {
 // Bound by the power the INT8 matrix cores draw: 4032^3 x 32 planes 2380 TOP/s, the same
 // launch on zeros and ones about 3000; one tile per workgroup 2250 there and 1426 instead of
 // 1895 at 1268 x 25000 x 951, where filling the pipeline is a larger part.
-template <int WM, int WN, int TM, int TN, int OCC, bool LONG, bool SEG>
+// TEST: the product of the magnitudes, which is not stored: the outputs' largest
+// fa fb / sum gives the level (see the top).
+template <int WM, int WN, int TM, int TN, int OCC, bool LONG, bool SEG, bool TEST>
 __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g) {
   constexpr int KB = 2, S = 3;
+  constexpr int kStage = TEST ? 128 : kPlanes * 128;  // 16-byte units of a stage of one row block
+  const int level = TEST ? 0 : level_of(g.lv);
+  if (!TEST && level > 1) return;
+  const int planes = TEST ? 1 : 2 * (16 + level);
   constexpr int T = 64 * WM * WN, RA = WM * TM, RB = WN * TN;
   constexpr int NA = RA * KB * 64 / T, NB = RB * KB * 64 / T;
   static_assert(NA * T == RA * KB * 64 && NB * T == RB * KB * 64, "whole copies per thread");
@@ -341,9 +429,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
   const int wm = w % WM, wn = w / WM;
   // a batch's products are further tiles along n, so that what they share of A is read together
   const int tiles_n = SEG ? g.tiles_n * g.batch : g.tiles_n;
-  const int tiles = g.tiles_m * tiles_n, total = tiles * g.planes;
+  const int tiles = g.tiles_m * tiles_n, total = tiles * planes;
   const int nk = g.kb / KB, nseg = SEG ? nk / 3 : nk;
-  const int64_t rs = (int64_t)nseg * kPlanes * 128;  // 16-byte units per row block
+  const int64_t rs = (int64_t)nseg * kStage;  // 16-byte units per row block
   const i4v* pa[NA];
   const i4v* pb[NB];
   int m0, n0, z, bat = 0;
@@ -378,10 +466,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
     }
   };
   auto load = [&](int kt, int buf) {
-    int64_t ka = (int64_t)kt * (kPlanes * 128), kb = ka;
+    int64_t ka = (int64_t)kt * kStage, kb = ka;
     if (SEG) {
       const int sg = kt >= 2 * nseg ? 2 : kt >= nseg ? 1 : 0;
-      ka -= (int64_t)sg * nseg * (kPlanes * 128);
+      ka -= (int64_t)sg * nseg * kStage;
       kb = ka + (sg == 2 ? sb[2] : sg == 1 ? sb[1] : sb[0]);
       ka += sg == 2 ? sa[2] : sg == 1 ? sa[1] : sa[0];
     }
@@ -398,7 +486,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
   start(job);
 #pragma unroll
   for (int s = 0; s < S - 1; ++s) load(min(s, nk - 1), s);
-  constexpr int kBias = LONG ? 0 : 128;  // see the reduction below
+  constexpr int kBias = LONG || TEST ? 0 : 128;  // see the reduction below
   int cur = 0;
   while (true) {
     const int cm0 = m0, cn0 = n0, cz = z, cbat = bat, next = job + (int)gridDim.x;
@@ -446,6 +534,28 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void mod_gemm_kernel(PlaneGemm g
             acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][i], b[s][j], acc[i][j], 0, 0, 0);
       cur = cur + 1 == S ? 0 : cur + 1;
     }
+    if constexpr (TEST) {
+      int worst = 0;
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int bm = cm0 + wm * TM + i, bn = cn0 + wn * TN + j;
+          if (bm >= g.mb || bn >= g.nb) continue;
+          const float fb = g.fb[32 * bn + (lane & 31)];
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float x = g.fa[32 * bm + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)] * fb;
+            const float y = g.flat * (float)acc[i][j][r];
+            worst = max(worst, y >= x ? 0 : 8.0f * y >= x ? 1 : 2);  // 2 where x is no number
+          }
+        }
+      const bool any2 = __ballot(worst == 2) != 0, any1 = __ballot(worst == 1) != 0;
+      if (lane == 0 && (any1 || any2)) atomicMax(g.out, any2 ? 2 : 1);
+      job = next;
+      if (job >= total) break;
+      continue;
+    }
     // Residues in [-p/2, p/2], kept 128 higher as unsigned bytes.  Up to kShortK the sums are
     // exact in FP32 and one rounded quotient suffices; beyond, a first step on the integers
     // (quotients below 2^23, off by at most 2) brings them there.
@@ -487,7 +597,7 @@ __device__ __forceinline__ Frac4 crt4(const int* c, const ModTab& t) {
   double hr[4] = {0, 0, 0, 0}, lr[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0}, li[4] = {0, 0, 0, 0};
 #pragma unroll
   for (int i = 0; i < kNP; ++i) {
-    if (i >= 15 && i >= t.np) break;
+    if (i >= 16 && i >= t.np) break;
     const int u = c[(2 * i) * 256], v = c[(2 * i + 1) * 256];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
@@ -515,7 +625,11 @@ __device__ __forceinline__ Frac4 crt4(const int* c, const ModTab& t) {
 // Bound by reading 2 kNP bytes and writing 16 per output.
 __global__ __launch_bounds__(256) void mod_crt_kernel(const int* Cp, int mb, int nb, int m0, int n0,
                                                       const int* ea, const int* eb, Gett<double> g, int64_t cp_bat,
-                                                      int64_t c_bat, ModTab t) {
+                                                      int64_t c_bat, Level lv, Tabs tt) {
+  const int level = level_of(lv);
+  if (level > 1) return;
+  const ModTab& t = tt.t[level];
+  const int shift = level ? 0 : 2 * kShift;
   Cp += blockIdx.y * cp_bat;
   g.C += 2 * (int64_t)blockIdx.y * c_bat;
   const int64_t tot = (int64_t)mb * nb * 4;
@@ -528,16 +642,14 @@ __global__ __launch_bounds__(256) void mod_crt_kernel(const int* Cp, int mb, int
     const int n = n0 + 32 * bn + col, mr = m0 + 32 * bm + row;
     const Frac4 f = crt4(Cp + tile * (kPlanes * 256) + q * 64 + lane, t);
     if (n >= g.N) continue;
-    const int en = eb[n];
+    const int en = eb[n] - shift;
     const int64_t co = cmap(n, g.n_in, g.c_no, g.c_ni);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = mr + r;
       if (m >= g.M) continue;
       const int em = ea[m];
-      const bool bad = em == kNaN || en == kNaN;
-      const double xr = bad ? __builtin_nan("") : ldexp(f.re[r], -(em + en));
-      const double xi = bad ? __builtin_nan("") : ldexp(f.im[r], -(em + en));
+      const double xr = ldexp(f.re[r], -(em + en)), xi = ldexp(f.im[r], -(em + en));
       d2v* c = reinterpret_cast<d2v*>(g.C + 2 * (co + cmap(m, g.m_in, g.c_mo, g.c_mi)));
       d2v y = {g.alpha_re * xr - g.alpha_im * xi, g.alpha_re * xi + g.alpha_im * xr};
       if (g.accumulate) y += *c;
@@ -560,7 +672,9 @@ struct LadderTiles {
   double* W;
   int64_t ldw;
 };
-__global__ __launch_bounds__(256) void mod_ladder_antisym_kernel(LadderTiles g, ModTab t) {
+__global__ __launch_bounds__(256) void mod_ladder_antisym_kernel(LadderTiles g, int level, Tabs tt) {
+  const ModTab& t = tt.t[level];
+  const int shift = level ? 0 : 2 * kShift;
   const int a = g.a_first + blockIdx.z, b = g.b_first + blockIdx.y;
   if (b <= a) return;
   int p = 0, q = blockIdx.x;
@@ -576,13 +690,12 @@ __global__ __launch_bounds__(256) void mod_ladder_antisym_kernel(LadderTiles g, 
         ((int64_t)blockIdx.z * g.wvb + rb) * ld + (int64_t)blockIdx.y * g.wvb + cb;
     const Frac4 f = crt4(g.C + tile * (kPlanes * 256) + w * 64 + lane, t);
     const int r0 = 32 * (g.blk0 + rb) + row, c0 = 32 * (g.blk0 + cb) + col;
-    const int en = c0 < g.v ? g.exps[b * 32 * g.vb + c0] : 0;
+    const int en = c0 < g.v ? g.exps[b * 32 * g.vb + c0] - shift : 0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int em = r0 + r < g.v ? g.exps[a * 32 * g.vb + r0 + r] : 0;
-      const bool bad = em == kNaN || en == kNaN;
-      y[r].x = bad ? __builtin_nan("") : ldexp(f.re[r], -(em + en));
-      y[r].y = bad ? __builtin_nan("") : ldexp(f.im[r], -(em + en));
+      y[r].x = ldexp(f.re[r], -(em + en));
+      y[r].y = ldexp(f.im[r], -(em + en));
     }
   };
   d2v x[4], y[4];
@@ -610,65 +723,76 @@ __global__ __launch_bounds__(256) void mod_ladder_antisym_kernel(LadderTiles g, 
 }
 
 // Rows whose products are summed get one scale: exps[g n + r], g < groups, becomes the least
-// of them less 1, room for three rows in one Cauchy-Schwarz bound (sqrt(3) < 2).  One thread
-// per r; nothing beside what it prepares (groups n dwords).
-__global__ __launch_bounds__(256) void mod_joint_exps_kernel(int* exps, int groups, int n) {
+// of them less 1, room for three rows in one Cauchy-Schwarz bound (sqrt(3) < 2); the norm
+// becomes the group's largest, and so does the flatness.  One thread per r; nothing beside what it prepares (groups n rows).
+__global__ __launch_bounds__(256) void mod_joint_exps_kernel(int* exps, double* norm, float* flat, int groups, int n) {
   const int r = blockIdx.x * 256 + threadIdx.x;
   if (r >= n) return;
   int e = kZero;
-  bool bad = false;
+  double top = 0.0;
+  float f = 0.0f;
 #pragma unroll 8
   for (int g = 0; g < groups; ++g) {
-    const int x = exps[(int64_t)g * n + r];
-    bad |= x == kNaN;
-    e = min(e, x);
+    const int64_t q = (int64_t)g * n + r;
+    e = min(e, exps[q]);
+    top = fmax(top, norm[q]);
+    f = fmaxf(f, flat[q]);
   }
-  e = bad ? kNaN : e - 1;
-  for (int g = 0; g < groups; ++g) exps[(int64_t)g * n + r] = e;
+  for (int g = 0; g < groups; ++g) {
+    const int64_t q = (int64_t)g * n + r;
+    exps[q] = e - 1;
+    norm[q] = top;
+    flat[q] = f;
+  }
 }
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
 int tpr_of(const Src& s) { return s.K >= 4096 ? 256 : 64; }
-int norm_blocks(const Src& s) {
-  return cdiv(std::min(s.rows - s.row0, 32 * s.rb), s.kfast ? 1024 / tpr_of(s) : 32);
-}
+int norm_blocks(const Src& s) { return cdiv(32 * s.rb, s.kfast ? 1024 / tpr_of(s) : 32); }
 
-// Scale and split one or two operands (b may have rows == 0).
-void split_scaled(const Src& a, const Src& b, const ModTab& t, hipStream_t s) {
+// Residue planes of one or two operands (b may have rows == 0).
+void split(const Src& a, const Src& b, Level lv, hipStream_t s) {
   const int sa = a.rb * (a.kb / 2), sb = b.rows ? b.rb * (b.kb / 2) : 0;
-  hipLaunchKernelGGL(mod_split_kernel, dim3(sa + sb), dim3(256), 0, s, a, sa, b, t);
+  hipLaunchKernelGGL(mod_split_kernel, dim3(sa + sb), dim3(256), 0, s, a, sa, b, lv, tabs());
   HIPCHECK(hipGetLastError());
 }
-void split(const Src& a, const Src& b, const ModTab& t, hipStream_t s) {
+// Their scales (what & 1) and magnitudes (what & 2); flag: set to 0 (may be null).
+void norms(const Src& a, const Src& b, int what, int* flag, hipStream_t s) {
   const int na = norm_blocks(a), nb = b.rows ? norm_blocks(b) : 0;
-  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), t.S);
+  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nb), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), tabs().t[1].S,
+                     what, flag);
   HIPCHECK(hipGetLastError());
-  split_scaled(a, b, t, s);
 }
 
 // RES: workgroups one CU holds (of 160 KiB LDS).  256 CUs.
-template <int WM, int WN, int TM, int TN, int OCC, int RES, bool SEG = false>
+template <int WM, int WN, int TM, int TN, int OCC, int RES, bool SEG = false, bool TEST = false>
 void launch_planes(PlaneGemm g, hipStream_t s) {
+  // the grid is laid out for 17 moduli or one plane of magnitudes; fewer leave workgroups without a tile
+  const int planes = TEST ? 1 : kPlanes;
   g.tiles_m = cdiv(g.mb, WM * TM);
   g.tiles_n = cdiv(g.nb, WN * TN);
-  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * g.planes * (SEG ? g.batch : 1);
+  const int64_t jobs = (int64_t)g.tiles_m * g.tiles_n * planes * (SEG ? g.batch : 1);
   if (jobs > 0x7fffffffLL) raise(-1, "contraction too large for one launch");
   const dim3 grid((unsigned)std::min<int64_t>(jobs, 256 * RES)), block(64 * WM * WN);
-  if (32 * g.kb <= kShortK)
-    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, false, SEG>), grid, block, 0, s, g);
+  if constexpr (TEST)
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, true, SEG, true>), grid, block, 0, s, g);
+  else if (32 * g.kb <= kShortK)
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, false, SEG, false>), grid, block, 0, s, g);
   else
-    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, true, SEG>), grid, block, 0, s, g);
+    hipLaunchKernelGGL((mod_gemm_kernel<WM, WN, TM, TN, OCC, true, SEG, false>), grid, block, 0, s, g);
   HIPCHECK(hipGetLastError());
 }
 
 // Tile choice: the padded block count of each tile shape over its measured rate (TOP/s at
 // full tiles, see mod_gemm_kernel), in whole rounds of the workgroups the chip holds.
+template <bool TEST = false>
 void gemm_planes(PlaneGemm g, hipStream_t s) {
+  const int planes = TEST ? 1 : kPlanes - 2;  // 16 moduli as a rule
   if (g.kb < 4) raise(-1, "residue product: K too short for its pipeline");  // two stages at least
   for (int i = 0; i < kNP; ++i) g.p[i] = kMods[i];
   auto cost = [&](int ra, int rb, int resident, double rate) {
-    const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * g.planes;
+    const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * planes;
     const double rounds = wgs >= 8 * resident ? (double)wgs / resident : (double)((wgs + resident - 1) / resident);
     return rounds * resident * ra * rb / rate;
   };
@@ -676,13 +800,13 @@ void gemm_planes(PlaneGemm g, hipStream_t s) {
                c3 = cost(4, 4, 768, 1720);
   const double best = std::min(std::min(c0, c1), std::min(c2, c3));
   if (best == c0)
-    launch_planes<2, 4, 4, 2, 1, 1>(g, s);
+    launch_planes<2, 4, 4, 2, 1, 1, false, TEST>(g, s);
   else if (best == c1)
-    launch_planes<2, 2, 2, 4, 2, 2>(g, s);
+    launch_planes<2, 2, 2, 4, 2, 2, false, TEST>(g, s);
   else if (best == c2)
-    launch_planes<2, 2, 4, 2, 2, 2>(g, s);
+    launch_planes<2, 2, 4, 2, 2, 2, false, TEST>(g, s);
   else
-    launch_planes<2, 2, 2, 2, 3, 3>(g, s);
+    launch_planes<2, 2, 2, 2, 3, 3, false, TEST>(g, s);
 }
 
 thread_local char* t_ws = nullptr;
@@ -693,8 +817,8 @@ inline int kblocks(int K) { return 2 * cdiv(K, 64); }
 
 }  // namespace
 
-// Estimated times (us).  FP64 GETT: 64 x 64 tiles at 62 TFLOP/s (55 to 72 reached).  Here: four
-// launches, splitting 15 ps per element, reconstruction 15 ps per output, the plane products at
+// Estimated times (us).  FP64 GETT: 64 x 64 tiles at 62 TFLOP/s (55 to 72 reached).  Here: six
+// launches, one of them the FP64 kernel that returns, splitting 15 ps per element, reconstruction 15 ps per output, the plane products at
 // 1.7 POP/s on 32 x 32 blocks.  Measured at the line (us, FP64 GETT / this): 900^3 138 / 107,
 // 400 x 19800 x 600 687 / 540, 4032 x 576 x 504 176 / 155, 190 x 9730 x 9730 2266 / 2215; under
 // it 640^3 59 / 66, 28224 x 168 x 504 391 / 440, 1131 x 1131 x 259 67 / 82.
@@ -702,13 +826,17 @@ bool mod_gemm_pays(int64_t M, int64_t N, int64_t K) {
   if (M < 128 || N < 128 || K < 128) return false;
   auto up = [](int64_t x, int64_t m) { return (double)((x + m - 1) / m * m); };
   const double t64 = 8.0 * up(M, 64) * up(N, 64) * (double)K / 62e6;
-  const double tm = 25.0 + (double)(M + N) * K * 15e-6 + (double)M * N * 15e-6 +
-                    2.0 * kPlanes * up(M, 32) * up(N, 32) * up(K, 64) / 1.7e9;
+  const double tm = 40.0 + (double)(M + N) * K * 15e-6 + (double)M * N * 15e-6 +
+                    2.0 * (kPlanes - 1) * up(M, 32) * up(N, 32) * up(K, 64) / 1.7e9;
   return tm < 0.95 * t64;
 }
 
-int64_t mod_plane_bytes(int64_t rows, int64_t K) {
+static int64_t plane_bytes(int64_t rows, int64_t K) {
   return kPlanes * ((rows + 31) / 32) * ((K + 63) / 64) * 2048;
+}
+static int64_t mag_bytes(int64_t rows, int64_t K) { return ((rows + 31) / 32) * ((K + 63) / 64) * 2048; }
+int64_t mod_operand_bytes(int64_t rows, int64_t K) {
+  return plane_bytes(rows, K) + mag_bytes(rows, K) + ((rows + 31) / 32) * 256;
 }
 int64_t mod_out_bytes(int64_t M, int64_t N) { return kPlanes * ((M + 31) / 32) * ((N + 31) / 32) * 1024; }
 
@@ -717,23 +845,11 @@ void set_mod_workspace(void* p, size_t bytes) {
   t_ws_bytes = p ? bytes : 0;
 }
 
-bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
+bool mod_gemm_wanted(const Gett<double>& g) { return t_ws && g.K >= 1 && mod_gemm_pays(g.M, g.N, g.K); }
+
+const int* mod_gemm(const Gett<double>& g0, hipStream_t s) {
   Gett<double> g = g0;
-  if (!t_ws || g.K < 1 || !mod_gemm_pays(g.M, g.N, g.K)) return false;
-  if (g.nbatch > 1) {
-    for (int q = 0; q < g0.nbatch; ++q) {
-      Gett<double> h = g0;
-      h.nbatch = 1;
-      h.A = g0.A + 2 * (int64_t)q * g0.a_b;
-      h.B = g0.B + 2 * (int64_t)q * g0.b_b;
-      h.C = g0.C + 2 * (int64_t)q * g0.c_b;
-      if (!mod_gemm(h, s)) {  // the first refuses or none does: sizes and workspace are the same
-        if (q > 0) raise(-1, "residue products of one batch took different routes");
-        return false;
-      }
-    }
-    return true;
-  }
+  if (!mod_gemm_wanted(g) || g.nbatch != 1) return nullptr;
   // columns of C (n) are the nearer neighbours in memory
   if (g.c_ni != 1 && g.c_mi == 1) {
     std::swap(g.A, g.B);
@@ -748,16 +864,20 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     std::swap(g.conj_a, g.conj_b);
   }
   const int mb = cdiv(g.M, 32), nb = cdiv(g.N, 32);
-  const int kc_max = std::min(g.K, kMaxK);
-  const size_t rbytes = (size_t)kPlanes * kblocks(kc_max) * 1024, tbytes = (size_t)kPlanes * 1024;
-  const size_t ebytes = up256((size_t)g.M * 4) + up256((size_t)g.N * 4);
+  // K in near-equal slices of whole 64-k groups, so that no slice is short
+  const int nsl = cdiv(g.K, kMaxK), ks = nsl == 1 ? g.K : 64 * cdiv(cdiv(g.K, nsl), 64);
+  if (nsl > 1 && g.k_in != g.K) return nullptr;  // a k slice needs a shifted base
+  const size_t rbytes = (size_t)kPlanes * kblocks(ks) * 1024, tbytes = (size_t)kPlanes * 1024;
+  // ahead of the planes: the level, scale exponents and flatness of every row, magnitudes
+  const size_t ra = up256((size_t)mb * 128), rb = up256((size_t)nb * 128);
+  const size_t ebytes = 256 + 2 * (ra + rb) + (size_t)mag_bytes(g.M, ks) + (size_t)mag_bytes(g.N, ks);
   // A and B blocks resident at a time (ma, nbr) and C blocks per product (mc x nc): C is kept
   // to what the last-level cache holds, since the reconstruction reads it right away
   constexpr size_t kC = (size_t)512 << 20;
-  if (ebytes + 64 * tbytes > t_ws_bytes) return false;
+  if (ebytes + 64 * tbytes > t_ws_bytes) return nullptr;
   const size_t room = t_ws_bytes - ebytes;
   size_t cbytes = std::min(std::min(kC, room / 4), (size_t)mb * nb * tbytes);
-  if (cbytes < (size_t)std::min(mb, 8) * std::min(nb, 8) * tbytes) return false;
+  if (cbytes < (size_t)std::min(mb, 8) * std::min(nb, 8) * tbytes) return nullptr;
   const size_t rows_room = (room - cbytes) / rbytes;  // row blocks of A and B together
   int ma = mb, nr = nb;
   if ((size_t)mb + nb > rows_room) {
@@ -769,7 +889,7 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     } else {
       ma = nr = (int)(rows_room / 2);
     }
-    if (ma < std::min(mb, 16) || nr < std::min(nb, 16)) return false;
+    if (ma < std::min(mb, 16) || nr < std::min(nb, 16)) return nullptr;
     if (ma < mb) ma = ma / 8 * 8;
     if (nr < nb) nr = nr / 8 * 8;
   }
@@ -778,13 +898,21 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
   int nc = std::min(nr, std::max(1, cb / mc));
   if (nc < nr && nc >= 8) nc = nc / 8 * 8;
   char* w = t_ws;
-  int* ea = reinterpret_cast<int*>(w);
-  int* eb = reinterpret_cast<int*>(w + up256((size_t)g.M * 4));
-  w += ebytes;
+  auto take = [&](size_t bytes) {
+    char* p = w;
+    w += bytes;
+    return p;
+  };
+  int* const flag = reinterpret_cast<int*>(take(256));
+  int* const ea = reinterpret_cast<int*>(take(ra));
+  int* const eb = reinterpret_cast<int*>(take(rb));
+  float* const fa = reinterpret_cast<float*>(take(ra));
+  float* const fb = reinterpret_cast<float*>(take(rb));
+  signed char* const ga = reinterpret_cast<signed char*>(take((size_t)mag_bytes(g.M, ks)));
+  signed char* const gb = reinterpret_cast<signed char*>(take((size_t)mag_bytes(g.N, ks)));
   signed char* Cp = reinterpret_cast<signed char*>(w);
   signed char* Ap = Cp + cbytes / 1024 * 1024;
   signed char* Bp = Ap + (size_t)ma * rbytes;
-  if (g.K > kMaxK && g.k_in != g.K) return false;  // a k slice needs a shifted base
   auto src = [&](bool is_a, signed char* planes, int blk0, int rb, int k0, int kc) {
     Src x{};
     x.p = (is_a ? g.A : g.B) + 2 * (int64_t)k0 * (is_a ? g.a_ki : g.b_ki);
@@ -803,14 +931,37 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
     x.rb = rb;
     x.kb = kblocks(kc);
     x.exps = is_a ? ea : eb;
+    x.flat = is_a ? fa : fb;
+    x.mags = is_a ? ga : gb;
     return x;
   };
-  const ModTab& t = tab(moduli_for(g.M, g.N, g.K));
   // a product of an operand with itself (the same element map) needs its residues once
   const bool same = g.A == g.B && g.M == g.N && g.m_in == g.n_in && g.a_mo == g.b_no && g.a_mi == g.b_ni &&
                     g.a_ko == g.b_ko && g.a_ki == g.b_ki && g.conj_a == g.conj_b && ma == mb && nr == nb;
-  for (int k0 = 0; k0 < g.K; k0 += kMaxK) {
-    const int kc = std::min(g.K - k0, kMaxK);
+  // scales and magnitudes of the slice from k0 on
+  auto scale = [&](int k0, int kc, int* level) {
+    norms(src(true, nullptr, 0, mb, k0, kc), same ? Src{} : src(false, nullptr, 0, nb, k0, kc), 3, level, s);
+  };
+  // the level of the whole product comes first: C may be accumulated into
+  for (int k0 = 0; k0 < g.K; k0 += ks) {
+    const int kc = std::min(g.K - k0, ks);
+    scale(k0, kc, k0 == 0 ? flag : nullptr);
+    PlaneGemm pg{};
+    pg.A = ga;
+    pg.B = same ? ga : gb;
+    pg.mb = pg.a_in = pg.a_outer = mb;
+    pg.nb = pg.b_in = pg.b_outer = nb;
+    pg.kb = kblocks(kc);
+    pg.fa = fa;
+    pg.fb = same ? fa : fb;
+    pg.flat = kFlat;
+    pg.out = flag;
+    gemm_planes<true>(pg, s);
+  }
+  const Level lv{flag, 0};
+  for (int k0 = 0; k0 < g.K; k0 += ks) {
+    const int kc = std::min(g.K - k0, ks);
+    if (nsl > 1) scale(k0, kc, nullptr);
     Gett<double> h = g;
     if (k0 > 0) h.accumulate = 1;
     for (int m0 = 0; m0 < mb; m0 += ma) {
@@ -820,16 +971,16 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
         const bool do_a = n0 == 0, do_b = m0 == 0 || nr < nb;
         const Src a = src(true, Ap, m0, am, k0, kc), b = src(false, Bp, n0, bn, k0, kc);
         if (do_a)
-          split(a, do_b && !same ? b : Src{}, t, s);
+          split(a, do_b && !same ? b : Src{}, lv, s);
         else
-          split(b, Src{}, t, s);
+          split(b, Src{}, lv, s);
         for (int m1 = 0; m1 < am; m1 += mc)
           for (int n1 = 0; n1 < bn; n1 += nc) {
             PlaneGemm pg{};
             pg.mb = std::min(mc, am - m1);
             pg.nb = std::min(nc, bn - n1);
             pg.kb = a.kb;
-            pg.planes = 2 * t.np;
+            pg.lv = lv;
             pg.A = Ap + (int64_t)m1 * (a.kb / 2) * kPlanes * 2048;
             pg.B = (same ? Ap : Bp) + (int64_t)n1 * (b.kb / 2) * kPlanes * 2048;
             pg.C = Cp;
@@ -839,28 +990,19 @@ bool mod_gemm(const Gett<double>& g0, hipStream_t s) {
             const int64_t units = (int64_t)pg.mb * pg.nb;
             hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>(units, 65535)), dim3(256), 0, s,
                                reinterpret_cast<const int*>(Cp), pg.mb, pg.nb, 32 * (m0 + m1),
-                               32 * (n0 + n1), ea, same ? ea : eb, h, (int64_t)0, (int64_t)0, t);
+                               32 * (n0 + n1), ea, same ? ea : eb, h, (int64_t)0, (int64_t)0, lv, tabs());
             HIPCHECK(hipGetLastError());
           }
       }
     }
   }
-  return true;
+  return flag;
 }
 
 // ---------------------------------------------------------------- particle ladder
-ModLadder::ModLadder(const double* F, int64_t row_stride, int v, int X, hipStream_t s) {
-  const int vb = cdiv(v, 32), kb = kblocks(X);
-  const size_t eb = up256((size_t)v * vb * 32 * 4), pb = (size_t)mod_plane_bytes((int64_t)v * vb * 32, X);
-  const size_t least = (size_t)vb * vb * std::min(v, 8) * kPlanes * 1024;  // tiles of one a and 8 b
-  if (!t_ws || v <= kModLadderNvir || X < kModLadderNaux || (int64_t)v * vb * 32 > 0x7fffffffLL ||
-      eb + pb + least > t_ws_bytes)
-    return;
-  v_ = v;
-  X_ = X;
-  exps_ = reinterpret_cast<int*>(t_ws);
-  planes_ = reinterpret_cast<signed char*>(t_ws + eb);
-  held_ = eb + pb;
+// Rows (a, c) of the factors as one operand, each a padded to whole blocks.
+static Src ladder_rows(const double* F, int64_t row_stride, int v, int X) {
+  const int vb = cdiv(v, 32);
   Src a{};
   a.p = F;
   a.rows = v * vb * 32;
@@ -872,11 +1014,52 @@ ModLadder::ModLadder(const double* F, int64_t row_stride, int v, int X, hipStrea
   a.r_si = X;
   a.k_so = a.k_si = 1;
   a.kfast = 1;
-  a.planes = planes_;
-  a.exps = exps_;
   a.rb = v * vb;
-  a.kb = kb;
-  split(a, Src{}, tab(15), s);  // K = naux: below the line of moduli_for, or no split
+  a.kb = kblocks(X);
+  return a;
+}
+static bool ladder_wanted(int v, int X) {
+  return t_ws && v > kModLadderNvir && X >= kModLadderNaux && (int64_t)v * cdiv(v, 32) * 32 <= 0x7fffffffLL;
+}
+
+int ModLadder::level(const double* F, int64_t row_stride, int v, int X, hipStream_t s) {
+  if (!ladder_wanted(v, X)) return 2;
+  Src a = ladder_rows(F, row_stride, v, X);
+  const size_t rows = up256((size_t)a.rows * 4), mags = (size_t)mag_bytes(a.rows, X);
+  if (256 + 2 * rows + mags > t_ws_bytes) return 2;
+  int* flag = reinterpret_cast<int*>(t_ws);
+  a.exps = reinterpret_cast<int*>(t_ws + 256);
+  a.flat = reinterpret_cast<float*>(t_ws + 256 + rows);
+  a.mags = reinterpret_cast<signed char*>(t_ws + 256 + 2 * rows);
+  norms(a, Src{}, 3, flag, s);
+  PlaneGemm g{};
+  g.A = g.B = a.mags;
+  g.mb = g.a_in = g.a_outer = g.nb = g.b_in = g.b_outer = a.rb;
+  g.kb = a.kb;
+  g.fa = g.fb = a.flat;
+  g.flat = kFlat;
+  g.out = flag;
+  gemm_planes<true>(g, s);
+  int lv = 2;
+  HIPCHECK(hipMemcpyAsync(&lv, flag, sizeof lv, hipMemcpyDeviceToHost, s));
+  HIPCHECK(hipStreamSynchronize(s));
+  return lv;
+}
+
+ModLadder::ModLadder(const double* F, int64_t row_stride, int v, int X, int level, hipStream_t s) : level_(level) {
+  const int vb = cdiv(v, 32);
+  const size_t eb = up256((size_t)v * vb * 32 * 4), pb = (size_t)plane_bytes((int64_t)v * vb * 32, X);
+  const size_t least = (size_t)vb * vb * std::min(v, 8) * kPlanes * 1024;  // tiles of one a and 8 b
+  if (level > 1 || !ladder_wanted(v, X) || 2 * eb + pb + least > t_ws_bytes) return;
+  v_ = v;
+  X_ = X;
+  Src a = ladder_rows(F, row_stride, v, X);
+  a.exps = exps_ = reinterpret_cast<int*>(t_ws);
+  a.flat = reinterpret_cast<float*>(t_ws + eb);
+  a.planes = planes_ = reinterpret_cast<signed char*>(t_ws + 2 * eb);
+  held_ = 2 * eb + pb;
+  norms(a, Src{}, 1, nullptr, s);
+  split(a, Src{}, Level{nullptr, level_}, s);
   t_ws += held_;  // the rest serves this ladder's tiles and, in turn, other products
   t_ws_bytes -= held_;
 }
@@ -908,12 +1091,13 @@ void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_
         pg.mb = g1 * wvb;
         pg.nb = nbn * wvb;
         pg.kb = kblocks(X_);
-        pg.planes = 2 * 15;
+        pg.lv = Level{nullptr, level_};
         pg.a_in = pg.b_in = wvb;
         pg.a_outer = pg.b_outer = vb;
         gemm_planes(pg, s);
         LadderTiles lt{reinterpret_cast<const int*>(t_ws), exps_, v, vb, wvb, blk0, a0, a1, b, nbn, row0, W, ldw};
-        hipLaunchKernelGGL(mod_ladder_antisym_kernel, dim3(wvb * (wvb + 1) / 2, nbn, g1), dim3(256), 0, s, lt, tab(15));
+        hipLaunchKernelGGL(mod_ladder_antisym_kernel, dim3(wvb * (wvb + 1) / 2, nbn, g1), dim3(256), 0, s, lt, level_,
+                           tabs());
         HIPCHECK(hipGetLastError());
       }
     }
@@ -935,7 +1119,7 @@ bool ModTriples::pays(int o, int v) {
   if ((int64_t)o * ((int64_t)v * v + 32) > 0x3fffffffLL || (int64_t)o * o * (v + 32) > 0x3fffffffLL) return false;
   const double P = 0.5 * v * (v - 1.0), n = o * (o - 1.0) * (o - 2.0) / 6.0;
   const double t64 = 3 * 8.0 * up(P, 64) * up(v, 64) * v / 62e6;
-  const double tm = P * v * 15e-6 + 2.0 * kPlanes * up(P, 32) * up(v, 32) * 3 * up(v, 64) / 1.7e9;
+  const double tm = P * v * 15e-6 + 2.0 * (kPlanes - 1) * up(P, 32) * up(v, 32) * 3 * up(v, 64) / 1.7e9;
   const double once = 50.0 + ((double)o * P * v + (double)o * o * v * v) * 15e-6;
   return tm + once / n < 0.9 * t64;
 }
@@ -943,7 +1127,9 @@ bool ModTriples::pays(int o, int v) {
 size_t ModTriples::bytes(int o, int v, int ni) {
   const int64_t P = (int64_t)v * (v - 1) / 2;
   const size_t mb = (size_t)cdiv(P, 32), nb = (size_t)cdiv(v, 32), rows = 32 * (o * mb + (size_t)o * o * nb);
-  return up256(rows * 4) + (size_t)mod_plane_bytes(rows, v) + (size_t)ni * mb * nb * kPlanes * 1024;
+  // per row norm, flatness and scale
+  return 256 + rows * 16 + (size_t)mag_bytes(rows, v) + (size_t)plane_bytes(rows, v) +
+         (size_t)ni * mb * nb * kPlanes * 1024;
 }
 
 ModTriples::ModTriples(void* ws, const double* V, const double* T2, int o, int v, int ni, hipStream_t s)
@@ -952,14 +1138,20 @@ ModTriples::ModTriples(void* ws, const double* V, const double* T2, int o, int v
   mb_ = cdiv(P, 32);
   nb_ = cdiv(v, 32);
   const int kb = kblocks(v);
-  ea_ = static_cast<int*>(ws);
-  eb_ = ea_ + (size_t)32 * o * mb_;
-  pa_ = static_cast<signed char*>(ws) + up256((size_t)32 * ((size_t)o * mb_ + (size_t)o * o * nb_) * 4);
-  pb_ = pa_ + mod_plane_bytes(32LL * o * mb_, v);
-  out_ = pb_ + mod_plane_bytes(32LL * o * o * nb_, v);
+  const int64_t rows_a = 32LL * o * mb_, rows_b = 32LL * o * o * nb_, rows = rows_a + rows_b;
+  char* w = static_cast<char*>(ws);
+  int* flag = reinterpret_cast<int*>(w);
+  double* norm = reinterpret_cast<double*>(w + 256);
+  float* flat = reinterpret_cast<float*>(norm + rows);
+  ea_ = reinterpret_cast<int*>(flat + rows);
+  eb_ = ea_ + rows_a;
+  signed char* mags = reinterpret_cast<signed char*>(ea_ + rows);
+  pa_ = mags + mag_bytes(rows, v);
+  pb_ = pa_ + plane_bytes(rows_a, v);
+  out_ = pb_ + plane_bytes(rows_b, v);
   Src a{};
   a.p = V;
-  a.rows = 32 * o * mb_;
+  a.rows = (int)rows_a;
   a.K = a.k_in = v;
   a.r_in = 32 * mb_;
   a.r_valid = (int)P;
@@ -968,54 +1160,66 @@ ModTriples::ModTriples(void* ws, const double* V, const double* T2, int o, int v
   a.k_so = a.k_si = 1;
   a.kfast = 1;
   a.planes = pa_;
+  a.mags = mags;
   a.exps = ea_;
+  a.norm = norm;
+  a.flat = flat;
   a.rb = o * mb_;
   a.kb = kb;
   Src b = a;
   b.p = T2;
-  b.rows = 32 * o * o * nb_;
+  b.rows = (int)rows_b;
   b.r_in = 32 * nb_;
   b.r_valid = v;
   b.r_so = (int64_t)v * v;
   b.planes = pb_;
+  b.mags = mags + mag_bytes(rows_a, v);
   b.exps = eb_;
+  b.norm = norm + rows_a;
+  b.flat = flat + rows_a;
   b.rb = o * o * nb_;
-  const ModTab& t = tab(15);  // K = 3 nvir: short chains in the FP64 products too
-  const int na = norm_blocks(a), nbk = norm_blocks(b);
-  hipLaunchKernelGGL(mod_norm_kernel, dim3(na + nbk), dim3(1024), 0, s, a, na, b, tpr_of(a), tpr_of(b), t.S);
+  norms(a, b, 1, flag, s);
+  hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * mb_, 256)), dim3(256), 0, s, ea_, a.norm, a.flat, o,
+                     32 * mb_);
   HIPCHECK(hipGetLastError());
-  hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * mb_, 256)), dim3(256), 0, s, ea_, o, 32 * mb_);
+  hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * nb_, 256)), dim3(256), 0, s, eb_, b.norm, b.flat, o * o,
+                     32 * nb_);
   HIPCHECK(hipGetLastError());
-  hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * nb_, 256)), dim3(256), 0, s, eb_, o * o, 32 * nb_);
-  HIPCHECK(hipGetLastError());
-  split_scaled(a, b, t, s);
+  split(a, b, Level{nullptr, level_}, s);
+}
+
+// The products of (i, j, k) and of the i after it; unit: 16-byte units of 64 k of one row block.
+PlaneGemm ModTriples::segments(int i, int j, int k, int64_t unit) const {
+  const int64_t seg = (int64_t)kblocks(v_) / 2 * unit;  // per row block
+  const int64_t ta = mb_ * seg, tb = nb_ * seg;          // per tile and per pair
+  PlaneGemm g{};
+  g.mb = g.a_in = g.a_outer = mb_;
+  g.nb = g.b_in = g.b_outer = nb_;
+  g.kb = 3 * kblocks(v_);
+  for (int q = 0; q < kNP; ++q) g.p[q] = kMods[q];
+  const int64_t at[3] = {i, j, k}, bt[3] = {(int64_t)j * o_ + k, (int64_t)k * o_ + i, (int64_t)i * o_ + j};
+  const int abat[3] = {1, 0, 0}, bbat[3] = {0, 1, o_};
+  for (int q = 0; q < 3; ++q) {
+    g.a_seg[q] = at[q] * ta;
+    g.b_seg[q] = bt[q] * tb;
+    g.a_bat[q] = abat[q] * ta;
+    g.b_bat[q] = bbat[q] * tb;
+  }
+  return g;
 }
 
 void ModTriples::rows(int i0, int ni, int j, int k, double* We, hipStream_t s) const {
   const int64_t P = (int64_t)v_ * (v_ - 1) / 2;
-  const int64_t seg = (int64_t)kblocks(v_) / 2 * kPlanes * 128;  // 16-byte units per row block
-  const int64_t ta = mb_ * seg, tb = nb_ * seg;                  // per tile and per pair
   const int64_t cb = (int64_t)mb_ * nb_ * kPlanes * 1024;
+  const Level lv{nullptr, level_};
   for (int y = 0; y < ni; y += ni_) {
-    const int i = i0 + y, n = std::min(ni_, ni - y);
-    PlaneGemm g{};
+    const int n = std::min(ni_, ni - y);
+    PlaneGemm g = segments(i0 + y, j, k, kPlanes * 128);
     g.A = pa_;
     g.B = pb_;
     g.C = out_;
-    g.mb = g.a_in = g.a_outer = mb_;
-    g.nb = g.b_in = g.b_outer = nb_;
-    g.kb = 3 * kblocks(v_);
-    g.planes = 2 * 15;
-    for (int q = 0; q < kNP; ++q) g.p[q] = kMods[q];
+    g.lv = lv;
     g.batch = n;
-    const int64_t at[3] = {i, j, k}, bt[3] = {(int64_t)j * o_ + k, (int64_t)k * o_ + i, (int64_t)i * o_ + j};
-    const int abat[3] = {1, 0, 0}, bbat[3] = {0, 1, o_};
-    for (int q = 0; q < 3; ++q) {
-      g.a_seg[q] = at[q] * ta;
-      g.b_seg[q] = bt[q] * tb;
-      g.a_bat[q] = abat[q] * ta;
-      g.b_bat[q] = bbat[q] * tb;
-    }
     g.c_bat = cb;
     if (nb_ <= 4)
       launch_planes<4, 2, 4, 2, 1, 1, true>(g, s);
@@ -1029,7 +1233,8 @@ void ModTriples::rows(int i0, int ni, int j, int k, double* We, hipStream_t s) c
     c.alpha_re = -1.0;
     c.C = We + 2 * y * P * v_;
     hipLaunchKernelGGL(mod_crt_kernel, dim3((unsigned)std::min<int64_t>((int64_t)mb_ * nb_, 65535), n), dim3(256), 0, s,
-                       reinterpret_cast<const int*>(out_), mb_, nb_, 0, 0, ea_, eb_, c, cb / 4, P * v_, tab(15));
+                       reinterpret_cast<const int*>(out_), mb_, nb_, 0, 0, ea_, eb_, c, cb / 4, P * v_, lv,
+                       tabs());
     HIPCHECK(hipGetLastError());
   }
 }

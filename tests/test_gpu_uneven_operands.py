@@ -1,0 +1,157 @@
+"""Large FP64 products whose operands are uneven: the large entries of a row of one operand
+meet the small ones of the other's rows.  An FP64 sum's error is relative to the sum of the
+absolute products; integer residues, whose error is relative to the rows' norms, must not be
+taken where that is larger."""
+import numpy as np
+import pytest
+
+from paper_2103_08473_amd.synth import make_system
+
+pytestmark = pytest.mark.gpu
+U = 2.0 ** -53
+
+
+def gauss(rng, *shape):
+    return rng.normal(size=shape) + 1j * rng.normal(size=shape)
+
+
+# decades by which the rows of C rise and those of J fall along the AOs (0: even operands); the
+# transforms of these sizes are large enough for residues
+@pytest.mark.parametrize("decades", [0, 1, 2, 8])
+def test_df_transforms_of_opposed_scales(lib, decades):
+    from paper_2103_08473_amd import exacc
+    m, n, X = 600, 400, 20
+    rng = np.random.default_rng(decades)
+    g = 10.0 ** np.linspace(0, decades, m)
+    C = gauss(rng, m, n) * g[:, None]
+    J = gauss(rng, X, m, m) / (g[:, None] * g[None, :])
+    J = 0.5 * (J + J.conj().transpose(0, 2, 1))
+    B, _ = exacc.df_factors(np.ascontiguousarray(C), np.ascontiguousarray(J), np.eye(X))
+    aC = np.abs(C)
+    # two sums of m terms, here and in the reference, each with three real products per term,
+    # and the sum over the metric's row; at most one rounding of the running sum per term
+    tol = 2 * (2 * (m + 4) + X) * U
+    worst = 0.0
+    for q in range(0, X, 7):
+        ref = C.conj().T @ J[q] @ C
+        worst = max(worst, (np.abs(B[q] - ref) / (aC.T @ np.abs(J[q]) @ aC)).max())
+    print("worst %.2e of the absolute sums (tolerance %.2e)" % (worst, tol), flush=True)
+    assert worst <= tol
+
+
+# V = D W D: auxiliary functions whose norms differ by 6 and 7 decades (condition number about
+# 1e12 and 1e14), and by none; the Newton-Schulz products' operands are then opposed in scale
+@pytest.mark.parametrize("decades", [0, 6, 7])
+def test_df_metric_of_functions_of_different_norm(lib, decades):
+    from paper_2103_08473_amd import exacc
+    m, n, X = 36, 32, 1000  # (n^2 columns: large enough a fit for the residue workspace to be taken)
+    rng = np.random.default_rng(decades)
+    d = 10.0 ** -rng.uniform(0, decades, size=X)
+    L = np.tril(rng.normal(size=(X, X)) * 0.3 / np.sqrt(X), -1) + np.eye(X)
+    K = gauss(rng, X, m, m)
+    K = 0.5 * (K + K.conj().transpose(0, 2, 1))
+    J = d[:, None, None] * np.einsum("PQ,Qmn->Pmn", L, K)
+    C = np.linalg.qr(gauss(rng, m, m))[0][:, :n]
+    V = (d[:, None] * d[None, :]) * (L @ L.T)
+    B, iters = exacc.df_factors(np.ascontiguousarray(C), J, 0.5 * (V + V.T))
+    # the fitted integrals sum_P B_pq B_rs are sum_P K~_pq K~_rs whatever D is
+    Kt = np.einsum("mp,Pmn,nq->Ppq", np.conj(C), K, C, optimize=True).reshape(X, -1)
+    Bf = B.reshape(X, -1)
+    got, ref, scale = Bf.T @ Bf, Kt.T @ Kt, np.abs(Kt).T @ np.abs(Kt)
+    worst = (np.abs(got - ref) / scale).max()
+    # sums of X terms in the metric, its inverse root and the fit, 16 of them at their bound
+    tol = 16 * X * U
+    print("%d steps, worst %.2e (tolerance %.2e)" % (iters, worst, tol), flush=True)
+    assert worst <= tol
+
+
+def residual(o, v, X, eps, B, t, **opts):
+    from paper_2103_08473_amd import exacc
+    with exacc.CCSD(eps, B, o, **opts) as cc:
+        cc.set_amplitudes(*t)
+        s1, s2 = cc.residual()
+    return np.asarray(s1), np.asarray(s2)
+
+
+# integrals that grow with the virtual indices as the amplitudes fall: every contraction over
+# them has opposed operands, and the residual divided by the growth of its own indices is even
+@pytest.mark.parametrize("decades", [0, 2, 8])
+@pytest.mark.parametrize("opts", [{}, {"cc2": 1}, {"ladder_chunk_pairs": 1500}])
+def test_residual_of_opposed_scales(lib, decades, opts):
+    from paper_2103_08473_amd import exacc
+    o, v, X = (24, 96, 300) if opts.get("cc2") else (13, 87, 259)
+    eps, B = make_system(o, v, X, seed=11)
+    rng = np.random.default_rng(7)
+    s = 10.0 ** rng.permutation(np.linspace(0, decades, v))
+    f = np.concatenate([np.ones(o), s])
+    B = np.ascontiguousarray(B * (f[:, None] * f[None, :]))
+    t1 = 0.01 * gauss(rng, o, v) / s
+    t2 = 0.01 * gauss(rng, o, o, v, v)
+    t2 = t2 - t2.transpose(1, 0, 2, 3)
+    t2 = np.ascontiguousarray((t2 - t2.transpose(0, 1, 3, 2)) / (s[:, None] * s[None, :]))
+    base = exacc.memory_estimate(o, v, X, hbm_budget_bytes=1, **opts)
+    plain = residual(o, v, X, eps, B, (t1, t2), hbm_budget_bytes=base, **opts)
+    mod = residual(o, v, X, eps, B, (t1, t2), **opts)
+    # either route rounds a sum of K products to within K 2^-53 of the absolute products
+    tol = max(v * (v - 1) // 2, o * v) * U
+    for a, b, g in zip(plain, mod, (s, s[:, None] * s[None, :])):
+        a, b = a / g, b / g
+        print("max |d| / max %.2e (tolerance %.2e)" % (np.abs(a - b).max() / np.abs(a).max(), tol), flush=True)
+        assert np.abs(a - b).max() <= tol * np.abs(a).max()
+
+
+def test_lambda_of_opposed_scales(lib):
+    """The Lambda residual, with the ladder on T1-dressed factors."""
+    from paper_2103_08473_amd import exacc
+    o, v, X = 13, 87, 259
+    eps, B = make_system(o, v, X, seed=12)
+    rng = np.random.default_rng(8)
+    s = 10.0 ** rng.permutation(np.linspace(0, 8, v))
+    f = np.concatenate([np.ones(o), s])
+    B = np.ascontiguousarray(B * (f[:, None] * f[None, :]))
+
+    def amps():
+        t1 = 0.01 * gauss(rng, o, v) / s
+        t2 = 0.01 * gauss(rng, o, o, v, v)
+        t2 = t2 - t2.transpose(1, 0, 2, 3)
+        return t1, np.ascontiguousarray((t2 - t2.transpose(0, 1, 3, 2)) / (s[:, None] * s[None, :]))
+
+    t, l = amps(), amps()
+    base = exacc.memory_estimate(o, v, X, hbm_budget_bytes=1)
+    out = []
+    for budget in (base + (63 << 20), 0):
+        with exacc.CCSD(eps, B, o, hbm_budget_bytes=budget) as cc:
+            cc.set_amplitudes(*t)
+            cc.set_lambda(*l)
+            out.append([np.asarray(x) for x in cc.lambda_residual()])
+    tol = v * (v - 1) // 2 * U
+    for a, b, g in zip(*out, (s, s[:, None] * s[None, :])):
+        a, b = a / g, b / g
+        print("max |d| / max %.2e (tolerance %.2e)" % (np.abs(a - b).max() / np.abs(a).max(), tol), flush=True)
+        assert np.abs(a - b).max() <= tol * np.abs(a).max()
+
+
+def test_ladder_of_factors_in_separate_fit_blocks(lib):
+    """Virtuals in four classes, each with its factors in its own blocks of the fit index and 1e-6
+    of that elsewhere; amplitudes in class 0 only.  The residual between classes 1 and 2 is then
+    the driver and the ladder, both from products of large and small entries."""
+    from paper_2103_08473_amd import exacc
+    o, v, X = 4, 96, 256
+    eps, B = make_system(o, v, X, seed=13)
+    cls = np.concatenate([np.zeros(o, int), np.arange(v) % 4])
+    own = (np.arange(X)[:, None, None] // 32 + cls[:, None] + cls[None, :]) % 4 == 0
+    B = np.ascontiguousarray(np.where(own, B, 1e-6 * B))
+    rng = np.random.default_rng(9)
+    t2 = gauss(rng, o, o, v, v)
+    t2 = t2 - t2.transpose(1, 0, 2, 3)
+    t2 = t2 - t2.transpose(0, 1, 3, 2)
+    zero = np.arange(v) % 4 != 0
+    t2[:, :, zero] = 0
+    t2[:, :, :, zero] = 0
+    t = np.zeros((o, v), complex), np.ascontiguousarray(t2)
+    base = exacc.memory_estimate(o, v, X, hbm_budget_bytes=1)
+    plain = residual(o, v, X, eps, B, t, hbm_budget_bytes=base)[1][:, :, 1::4, 2::4]
+    mod = residual(o, v, X, eps, B, t)[1][:, :, 1::4, 2::4]
+    tol = v * (v - 1) // 2 * U
+    print("max |d| / max %.2e (tolerance %.2e)" % (np.abs(plain - mod).max() / np.abs(plain).max(), tol), flush=True)
+    assert np.abs(plain - mod).max() <= tol * np.abs(plain).max()
