@@ -116,7 +116,8 @@ struct PlaneGemm;
 // The e-sums of the triples' W by exact residues: <ab||ie> of all i and t2 are split once, and
 // per triple We[(a<b)][c] = - sum_e (V_i t_jk + V_j t_ki + V_k t_ij) is one plane product over
 // K = 3 nvir and one reconstruction.  A row (a, b) has one scale for all i and a row c of t2
-// one for all pairs, so that the three terms add as integers.
+// one for all pairs, so that the three terms add as integers; level() above 1: these scales are
+// too far apart for that, and rows() must not be called.  The constructor waits for the device.
 class ModTriples {
  public:
   static bool pays(int o, int v);
@@ -125,10 +126,11 @@ class ModTriples {
   ModTriples(void* ws, const double* V, const double* T2, int o, int v, int ni, hipStream_t s);
   // We of (i, j, k), i0 <= i < i0 + ni, one after the other
   void rows(int i0, int ni, int j, int k, double* We, hipStream_t s) const;
+  int level() const { return level_; }
 
  private:
   PlaneGemm segments(int i, int j, int k, int64_t unit) const;
-  int o_, v_, ni_, mb_, nb_, level_ = 0;
+  int o_, v_, ni_, mb_, nb_, level_ = 2;
   int *ea_, *eb_;
   signed char *pa_, *pb_, *out_;
 };

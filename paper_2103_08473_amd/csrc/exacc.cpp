@@ -1600,6 +1600,7 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   if (mod) {
     build(0, 0);
     mt.emplace(mod, Ve, T2, o, v, mod_ni, s);
+    if (mt->level() > 1) mt.reset();
   }
   // three nested loops over occupied blocks, unique block triples bi <= bj <= bk
   for (int bk = 0; bk < nb_occ; ++bk)

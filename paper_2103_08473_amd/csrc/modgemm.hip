@@ -1185,7 +1185,28 @@ ModTriples::ModTriples(void* ws, const double* V, const double* T2, int o, int v
   hipLaunchKernelGGL(mod_joint_exps_kernel, dim3(cdiv(32LL * nb_, 256)), dim3(256), 0, s, eb_, b.norm, b.flat, o * o,
                      32 * nb_);
   HIPCHECK(hipGetLastError());
-  split(a, b, Level{nullptr, level_}, s);
+  norms(a, b, 2, nullptr, s);
+  // the level, from all triples: the scales are the largest of any i and any pair, so a triple
+  // whose own integrals or amplitudes are far smaller takes the FP64 products with all others
+  for (int k = 2; k < o; ++k)
+    for (int j = 1; j < k; ++j) {
+      PlaneGemm g = segments(0, j, k, 128);
+      g.A = a.mags;
+      g.B = b.mags;
+      g.batch = j;
+      g.fa = a.flat;
+      g.fb = b.flat;
+      // one bit less and three sums: 2 sqrt(3) times the rounding of one product
+      g.flat = kFlat / 3.5f;
+      g.out = flag;
+      if (nb_ <= 4)
+        launch_planes<4, 2, 4, 2, 1, 1, true, true>(g, s);
+      else
+        launch_planes<2, 4, 4, 2, 1, 1, true, true>(g, s);
+    }
+  HIPCHECK(hipMemcpyAsync(&level_, flag, sizeof level_, hipMemcpyDeviceToHost, s));
+  HIPCHECK(hipStreamSynchronize(s));
+  if (level_ <= 1) split(a, b, Level{nullptr, level_}, s);
 }
 
 // The products of (i, j, k) and of the i after it; unit: 16-byte units of 64 k of one row block.

@@ -155,3 +155,33 @@ def test_ladder_of_factors_in_separate_fit_blocks(lib):
     tol = v * (v - 1) // 2 * U
     print("max |d| / max %.2e (tolerance %.2e)" % (np.abs(plain - mod).max() / np.abs(plain).max(), tol), flush=True)
     assert np.abs(plain - mod).max() <= tol * np.abs(plain).max()
+
+
+# a pair of occupied orbitals with amplitudes 1e12 of the others', its own triples' energies
+# nothing for their denominators; without it (1) the amplitudes are even
+@pytest.mark.parametrize("strong", [1e12, 1.0])
+def test_triples_beside_a_far_stronger_pair(lib, strong):
+    from paper_2103_08473_amd import exacc
+    o, v, X = 8, 120, 40
+    eps, B = make_system(o, v, X, seed=14)
+    rng = np.random.default_rng(10)
+    t1 = 0.01 * gauss(rng, o, v)
+    t2 = 0.01 * gauss(rng, o, o, v, v)
+    t2 = t2 - t2.transpose(1, 0, 2, 3)
+    t2 = t2 - t2.transpose(0, 1, 3, 2)
+    if strong > 1:
+        t2[6, 7] *= strong
+        t2[7, 6] *= strong
+        eps = eps.copy()
+        eps[6] = eps[7] = -1e60
+    out = []
+    for block in (2, 0):
+        with exacc.CCSD(eps, B, o, triples_occ_block=block) as cc:
+            cc.set_amplitudes(t1, np.ascontiguousarray(t2))
+            # E_-T has a term without denominators, of the strong pair
+            out.append(np.array(cc.triples())[:2 if strong > 1 else 3])
+    plain, mod = out
+    # W is off by at most 3 nvir + 3 nocc roundings of its own norm, the energies quadratic in it
+    tol = 6 * (v + o) * U
+    print("max |d| / max %.2e (tolerance %.2e)" % ((np.abs(mod - plain) / np.abs(plain)).max(), tol), flush=True)
+    assert (np.abs(mod - plain) <= tol * np.abs(plain)).all()
