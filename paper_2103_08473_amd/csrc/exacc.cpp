@@ -251,7 +251,7 @@ struct Handle {
   double* redout = nullptr;   // reduced values (device)
   double* host = nullptr;     // pinned readback
   int* rowmap_o = nullptr;    // k*o+l for pairs k<l
-  int lad_level = 2;          // see ModLadder, of the factors B_vv
+  int lad_level = -1;         // see ModLadder, of the factors B_vv; -1: not known yet
   // DIIS state
   std::vector<int> order;     // slot ids, oldest first
   std::vector<std::vector<zc>> G;
@@ -283,48 +283,92 @@ struct Handle {
     set_gett_workspace(ws, ws_bytes);
     set_mod_workspace(mod_ws, mod_ws ? P.bytes_mod : 0);
   }
-  // Give the residue workspace back (memory is short); recorded graphs address it.
-  bool release_mod() {
-    if (!mod_ws) return false;
-    HIPCHECK(hipStreamSynchronize(s));
+  void forget(const void* p) {
+    for (size_t i = 0; i < allocs.size(); ++i)
+      if (allocs[i] == p) {
+        allocs.erase(allocs.begin() + i);
+        break;
+      }
+    for (size_t i = 0; i < ranges.size(); ++i)
+      if (ranges[i].base == p) {
+        ranges.erase(ranges.begin() + i);
+        break;
+      }
+  }
+  void drop_graphs() {
     for (auto& g : gexec)
       if (g) {
         (void)hipGraphExecDestroy(g);
         g = nullptr;
       }
-    dfree(mod_ws);
+  }
+  // Give the residue workspace back (memory is short); recorded graphs address it.  Leaves the
+  // calling thread's registry and workspaces as they are.
+  bool drop_mod() {
+    if (!mod_ws) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      return false;
+    }
+    HIPCHECK(hipStreamSynchronize(s));
+    drop_graphs();
+    void* p = mod_ws;
+    mod_ws = nullptr;
+    forget(p);
+    HIPCHECK(hipFree(p));
     return true;
+  }
+  bool release_mod() {
+    if (!drop_mod()) return false;
+    use();
+    return true;
+  }
+  size_t held() const {
+    size_t b = 0;
+    for (const AllocRange& r : ranges) b += r.bytes;
+    return b;
+  }
+  // Take the planned residue workspace where the handle is without it and 1 GiB beside it is free.
+  void regain_mod() {
+    if (mod_ws || !P.bytes_mod) return;
+    if (op.hbm_budget_bytes && held() + P.bytes_mod > op.hbm_budget_bytes) return;
+    size_t fr = 0, tot = 0;
+    HIPCHECK(hipMemGetInfo(&fr, &tot));
+    if (P.bytes_mod + ((size_t)1 << 30) > fr) return;
+    mod_ws = try_alloc(P.bytes_mod);
+    if (!mod_ws) return;
+    HIPCHECK(hipStreamSynchronize(s));
+    drop_graphs();  // recorded without it
+    use();
   }
   template <typename T>
   void dfree(T*& p) {
     if (!p) return;
-    for (size_t i = 0; i < allocs.size(); ++i)
-      if (allocs[i] == (void*)p) {
-        allocs.erase(allocs.begin() + i);
-        break;
-      }
-    for (size_t i = 0; i < ranges.size(); ++i)
-      if (ranges[i].base == (const void*)p) {
-        ranges.erase(ranges.begin() + i);
-        break;
-      }
+    forget(p);
     HIPCHECK(hipFree(p));
     p = nullptr;
     use();
   }
-  double* dalloc(int64_t complex_elems) {
+  // null where the device has no block of that size
+  void* try_alloc(size_t bytes) {
     void* p = nullptr;
-    const size_t b = (size_t)std::max<int64_t>(complex_elems, 1) * 16;
-    hipError_t e = hipMalloc(&p, b);
-    if (e == hipErrorOutOfMemory && mod_ws) {
+    const hipError_t e = hipMalloc(&p, bytes);
+    if (e == hipErrorOutOfMemory) {
       (void)hipGetLastError();
-      release_mod();
-      e = hipMalloc(&p, b);
+      return nullptr;
     }
     HIPCHECK(e);
     allocs.push_back(p);
-    ranges.push_back({p, b});
+    ranges.push_back({p, bytes});
     set_alloc_registry(ranges.data(), (int)ranges.size());
+    return p;
+  }
+  double* dalloc(int64_t complex_elems) {
+    const size_t b = (size_t)std::max<int64_t>(complex_elems, 1) * 16;
+    void* p = try_alloc(b);
+    if (!p && release_mod()) p = try_alloc(b);
+    if (!p) raise(EXACC_ERR_NOMEM, "device allocation of " + std::to_string(b) + " bytes failed");
     return (double*)p;
   }
 };
@@ -333,13 +377,8 @@ struct Handle {
 // temporaries) stay within opts.hbm_budget_bytes together with what the handle holds.
 static void check_budget(Handle& h, size_t extra, const char* what) {
   if (!h.op.hbm_budget_bytes) return;
-  auto held = [&] {
-    size_t b = 0;
-    for (const AllocRange& r : h.ranges) b += r.bytes;
-    return b;
-  };
-  if (held() + extra > h.op.hbm_budget_bytes) h.release_mod();
-  if (held() + extra > h.op.hbm_budget_bytes)
+  if (h.held() + extra > h.op.hbm_budget_bytes) h.release_mod();
+  if (h.held() + extra > h.op.hbm_budget_bytes)
     raise(EXACC_ERR_NOMEM, std::string(what) + " would exceed hbm_budget_bytes");
 }
 
@@ -1514,8 +1553,7 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   // the products of several i together while those stay within 512 MB
   int mod_ni = 0;
   size_t mod_bytes = 0;
-  size_t in_use = 0;
-  for (const AllocRange& r : h.ranges) in_use += r.bytes;
+  const size_t in_use = h.held();
   // what the optional buffers come on top of (Acat at its larger size)
   size_t rest = small + tiles + (size_t)cap * wrow + (size_t)cap * v * 3 * o * 16;
   auto fits = [&](size_t more) {
@@ -1549,16 +1587,8 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   part = h.dalloc(2 * cap * nblk);  // 4 doubles per block
   tri = h.dalloc(2 * ooo);          // (e4, e5, ey, -) at [i][j][k]
   Acat = h.dalloc(cap * v * (one_m ? 3 : 2) * o);
-  auto optional = [&](size_t bytes) -> double* {
-    try {
-      return h.dalloc((int64_t)(bytes / 16));
-    } catch (...) {  // no block of that size: done without
-      (void)hipGetLastError();
-      return nullptr;
-    }
-  };
-  if (one_m) Bcat = optional(bcat_bytes);
-  if (mod_ni) mod = optional(mod_bytes);
+  if (one_m) Bcat = (double*)h.try_alloc(bcat_bytes);  // null: done without
+  if (mod_ni) mod = (double*)h.try_alloc(mod_bytes);
   int b_k = -1, b_i0 = -1, b_filled = 0;  // slots of Bcat that hold their k and i parts
   // full t2 [i][j][a][b] into H4 and t2 packed over the virtual pair [k][m][(b<c)] into
   // TAU (FP64 work arrays rebuilt every iteration)
@@ -1758,6 +1788,19 @@ static void lambda_alloc(Handle& h) {
   h.lam = L;
 }
 
+// How the factors B_vv bear residues, once, when there is a workspace to find out in.
+static void find_lad_level(Handle& h) {
+  const Plan& P = h.P;
+  if (h.lad_level >= 0 || !h.mod_ws || P.Po == 0 || P.ladder_grouped || h.op.cc2) return;
+  h.lad_level = ModLadder::level(bviews(h, h.Bt).Bvv.p, (int64_t)P.n * P.X, P.v, P.X, h.s);
+}
+
+// A handle that gave its residue workspace back, or found no room for it, takes it when there is.
+static void regain_workspace(Handle& h) {
+  h.regain_mod();
+  find_lad_level(h);
+}
+
 static void lambda_check(Handle& h) {
   if (h.phase32)
     raise(EXACC_ERR_INVALID_ARG, "Lambda equations need the FP64 integrals: iterate into the FP64 phase first");
@@ -1765,6 +1808,7 @@ static void lambda_check(Handle& h) {
     raise(EXACC_ERR_INVALID_ARG, "Lambda equations are those of CCSD; not for CCD or CC2 handles");
   h.use();
   lambda_alloc(h);
+  regain_workspace(h);
 }
 
 static void lambda_prepare(Handle& h) {
@@ -2102,7 +2146,7 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     if (P.bytes_mod) {  // optional: only where it leaves room for the whole plan
       size_t fr = 0, tot = 0;
       HIPCHECK(hipMemGetInfo(&fr, &tot));
-      if (P.bytes_peak + P.bytes_mod + ((size_t)1 << 30) <= fr) h->mod_ws = h->dalloc((int64_t)(P.bytes_mod / 16));
+      if (P.bytes_peak + P.bytes_mod + ((size_t)1 << 30) <= fr) h->mod_ws = h->try_alloc(P.bytes_mod);
     }
     // B: stage raw, check Hermiticity and finiteness on the device, transpose to [p][q][P]
     const double* Braw = B;
@@ -2220,8 +2264,7 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     h->Ta = h->dalloc(h->P.ladder_grouped ? h->P.vv * h->P.vv : (int64_t)v * std::max(1, v - 1) * v);
     h->W = h->dalloc(P.chunk_pairs * std::max<int64_t>(1, P.Pv));
     h->use();
-    if (P.Po > 0 && !P.ladder_grouped && !op.cc2)
-      h->lad_level = ModLadder::level(bviews(*h, h->Bt).Bvv.p, (int64_t)n * X, v, X, h->s);
+    find_lad_level(*h);
     HIPCHECK(hipMemsetAsync(h->x, 0, P.L * 16, h->s));
     HIPCHECK(hipStreamSynchronize(h->s));
     timer_collect(*h);
@@ -2306,6 +2349,7 @@ int exacc_ccsd_iterate(exacc_ccsd_t hh, int max_steps, int* steps_done, double* 
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
     Handle& h = *reinterpret_cast<Handle*>(hh);
     h.use();
+    regain_workspace(h);
     lambda_invalidate(h);
     if (h.diis_owner != 0) {
       reset_diis(h);
@@ -2390,6 +2434,7 @@ int exacc_ccsd_residual(exacc_ccsd_t hh, double* s1, double* s2, int on_device) 
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
     Handle& h = *reinterpret_cast<Handle*>(hh);
     h.use();
+    regain_workspace(h);
     lambda_invalidate(h);
     const int o = h.P.o, v = h.P.v;
     compute_residual_phase(h);

@@ -1050,7 +1050,7 @@ ModLadder::ModLadder(const double* F, int64_t row_stride, int v, int X, int leve
   const int vb = cdiv(v, 32);
   const size_t eb = up256((size_t)v * vb * 32 * 4), pb = (size_t)plane_bytes((int64_t)v * vb * 32, X);
   const size_t least = (size_t)vb * vb * std::min(v, 8) * kPlanes * 1024;  // tiles of one a and 8 b
-  if (level > 1 || !ladder_wanted(v, X) || 2 * eb + pb + least > t_ws_bytes) return;
+  if (level < 0 || level > 1 || !ladder_wanted(v, X) || 2 * eb + pb + least > t_ws_bytes) return;
   v_ = v;
   X_ = X;
   Src a = ladder_rows(F, row_stride, v, X);
