@@ -79,6 +79,7 @@ void launch_gett(const Gett<R>& g, int kind, hipStream_t s);
 // 1 where the product was formed and 2 where its operands are too uneven for it (C untouched): the
 // caller launches the FP64 kernel behind it with Gett::when set to that.
 void set_mod_workspace(void* p, size_t bytes);
+bool reclaim_workspaces(const void* self);  // of idle handles (not self), when memory is short; see exacc.cpp
 bool mod_gemm_pays(int64_t M, int64_t N, int64_t K);
 int64_t mod_operand_bytes(int64_t rows, int64_t K);  // residues and scales of a rows x K operand
 int64_t mod_out_bytes(int64_t M, int64_t N);         // residues of an M x N product

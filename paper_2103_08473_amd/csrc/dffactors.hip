@@ -311,7 +311,12 @@ struct Owned {
       if (q) (void)hipFree(q);
   }
   char* alloc(int k, size_t bytes) {
-    if (hipMalloc(&p[k], std::max<size_t>(bytes, 16)) != hipSuccess) {
+    hipError_t e = hipMalloc(&p[k], std::max<size_t>(bytes, 16));
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      if (reclaim_workspaces(nullptr)) e = hipMalloc(&p[k], std::max<size_t>(bytes, 16));
+    }
+    if (e != hipSuccess) {
       (void)hipGetLastError();
       p[k] = nullptr;
       raise(-2, "DF factors: device allocation of " + std::to_string(bytes) + " bytes failed");

@@ -15,6 +15,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <optional>
 #include <string>
 #include <vector>
@@ -283,6 +284,8 @@ struct Handle {
     set_gett_workspace(ws, ws_bytes);
     set_mod_workspace(mod_ws, mod_ws ? P.bytes_mod : 0);
   }
+  std::mutex busy;  // held by every call on the handle, see reclaim_workspaces
+  int dev = 0;
   void forget(const void* p) {
     for (size_t i = 0; i < allocs.size(); ++i)
       if (allocs[i] == p) {
@@ -368,9 +371,42 @@ struct Handle {
     const size_t b = (size_t)std::max<int64_t>(complex_elems, 1) * 16;
     void* p = try_alloc(b);
     if (!p && release_mod()) p = try_alloc(b);
+    if (!p && reclaim_workspaces(this)) p = try_alloc(b);
     if (!p) raise(EXACC_ERR_NOMEM, "device allocation of " + std::to_string(b) + " bytes failed");
     return (double*)p;
   }
+};
+
+// All handles, for what one of them may ask of the others.
+struct Live {
+  std::mutex mu;
+  std::vector<Handle*> handles;
+};
+static Live& live() {
+  static Live* l = new Live;  // outlives every handle and thread
+  return *l;
+}
+
+// The residue workspaces are extra: an allocation on the device that finds no room takes those of
+// the handles no call is running on (they take them again when there is room).  True if any was.
+bool reclaim_workspaces(const void* self) {
+  int dev = 0;
+  HIPCHECK(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lk(live().mu);
+  bool any = false;
+  for (Handle* h : live().handles) {
+    if (h == self || h->dev != dev) continue;
+    std::unique_lock<std::mutex> idle(h->busy, std::try_to_lock);
+    if (idle) any = h->drop_mod() || any;
+  }
+  return any;
+}
+
+// The handle of a call, until it returns.
+struct Entered {
+  Handle& h;
+  std::lock_guard<std::mutex> lk;
+  explicit Entered(exacc_ccsd_t hh) : h(*reinterpret_cast<Handle*>(hh)), lk(h.busy) {}
 };
 
 // Calls after create that allocate on top of the handle (the Lambda buffers, the triples
@@ -1531,6 +1567,7 @@ static void triples_impl(Handle& h, double* e4_out, double* e5_out, double* ey_o
   int red = o;
   HIPCHECK(hipMemGetInfo(&free_b, &total_b));
   if (small + (size_t)o * (trow + wrow) > free_b && h.release_mod()) HIPCHECK(hipMemGetInfo(&free_b, &total_b));
+  if (small + (size_t)o * (trow + wrow) > free_b && reclaim_workspaces(&h)) HIPCHECK(hipMemGetInfo(&free_b, &total_b));
   if (small + (size_t)o * trow + wrow > free_b) {
     if (small + 3 * trow + wrow > free_b)
       raise(EXACC_ERR_NOMEM, "triples: three <ab||ie> tile rows and one W row do not fit in free device memory");
@@ -1750,6 +1787,7 @@ static void lambda_alloc(Handle& h) {
   size_t fr = 0, tot = 0;
   HIPCHECK(hipMemGetInfo(&fr, &tot));
   if ((size_t)need * 16 + (256u << 20) > fr && h.release_mod()) HIPCHECK(hipMemGetInfo(&fr, &tot));
+  if ((size_t)need * 16 + (256u << 20) > fr && reclaim_workspaces(&h)) HIPCHECK(hipMemGetInfo(&fr, &tot));
   if ((size_t)need * 16 + (256u << 20) > fr) raise(EXACC_ERR_NOMEM, "Lambda buffers do not fit");
   check_budget(h, (size_t)need * 16, "Lambda buffers");
   // into a local set first: the handle records them only once every allocation succeeded;
@@ -2121,6 +2159,7 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     h->P = P;
     h->op = opx;
     h->tm.on = op.timing != 0;
+    HIPCHECK(hipGetDevice(&h->dev));
     if (op.stream) {
       h->s = (hipStream_t)op.stream;
     } else {
@@ -2152,7 +2191,12 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     const double* Braw = B;
     double* Bstage = nullptr;
     if (!op.inputs_on_device) {
-      HIPCHECK(hipMalloc((void**)&Bstage, nnX * 16));
+      hipError_t e = hipMalloc((void**)&Bstage, nnX * 16);
+      if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        if (h->release_mod() | reclaim_workspaces(h)) e = hipMalloc((void**)&Bstage, nnX * 16);
+      }
+      HIPCHECK(e);
       HIPCHECK(hipMemcpyAsync(Bstage, B, nnX * 16, hipMemcpyHostToDevice, h->s));
       Braw = Bstage;
     }
@@ -2268,6 +2312,8 @@ static Handle* create_impl(int o, int v, int X, const double* eps, const double*
     HIPCHECK(hipMemsetAsync(h->x, 0, P.L * 16, h->s));
     HIPCHECK(hipStreamSynchronize(h->s));
     timer_collect(*h);
+    std::lock_guard<std::mutex> lk(live().mu);
+    live().handles.push_back(h);
     return h;
   } catch (...) {
     if (h->s) (void)hipStreamSynchronize(h->s);
@@ -2347,7 +2393,8 @@ int exacc_ccsd_iterate(exacc_ccsd_t hh, int max_steps, int* steps_done, double* 
   if (converged) *converged = 0;
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     h.use();
     regain_workspace(h);
     lambda_invalidate(h);
@@ -2376,7 +2423,8 @@ int exacc_ccsd_iterate(exacc_ccsd_t hh, int max_steps, int* steps_done, double* 
 int exacc_ccsd_energy(exacc_ccsd_t hh, double* e_re, double* e_im) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     h.use();
     const zc e = device_energy(h);
     timer_collect(h);
@@ -2389,7 +2437,8 @@ int exacc_ccsd_energy(exacc_ccsd_t hh, double* e_re, double* e_im) {
 int exacc_ccsd_get_amplitudes(exacc_ccsd_t hh, double* t1, double* t2, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     h.use();
     lambda_invalidate(h);
     const int o = h.P.o, v = h.P.v;
@@ -2407,7 +2456,8 @@ int exacc_ccsd_get_amplitudes(exacc_ccsd_t hh, double* t1, double* t2, int on_de
 int exacc_ccsd_set_amplitudes(exacc_ccsd_t hh, const double* t1, const double* t2, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     h.use();
     lambda_invalidate(h);
     const int o = h.P.o, v = h.P.v;
@@ -2432,7 +2482,8 @@ int exacc_ccsd_set_amplitudes(exacc_ccsd_t hh, const double* t1, const double* t
 int exacc_ccsd_residual(exacc_ccsd_t hh, double* s1, double* s2, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     h.use();
     regain_workspace(h);
     lambda_invalidate(h);
@@ -2457,7 +2508,8 @@ int exacc_ccsd_residual(exacc_ccsd_t hh, double* s1, double* s2, int on_device) 
 int exacc_ccsd_triples(exacc_ccsd_t hh, double* e_plus_t, double* e_paren_t, double* e_minus_t) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     h.use();
     lambda_invalidate(h);
     double e4 = 0, e5 = 0, ey = 0;
@@ -2475,7 +2527,8 @@ int exacc_ccsd_lambda_iterate(exacc_ccsd_t hh, int max_steps, int* steps_done, d
   if (converged) *converged = 0;
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     lambda_check(h);
     double first = -1.0;
     for (int k = 0; k < max_steps; ++k) {
@@ -2496,7 +2549,8 @@ int exacc_ccsd_lambda_iterate(exacc_ccsd_t hh, int max_steps, int* steps_done, d
 int exacc_ccsd_lambda_residual(exacc_ccsd_t hh, double* r1, double* r2, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     lambda_check(h);
     const int o = h.P.o, v = h.P.v;
     lambda_compute(h);
@@ -2515,7 +2569,8 @@ int exacc_ccsd_lambda_residual(exacc_ccsd_t hh, double* r1, double* r2, int on_d
 int exacc_ccsd_get_lambda(exacc_ccsd_t hh, double* l1, double* l2, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     lambda_check(h);
     const int o = h.P.o, v = h.P.v;
     const hipMemcpyKind k = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
@@ -2532,7 +2587,8 @@ int exacc_ccsd_get_lambda(exacc_ccsd_t hh, double* l1, double* l2, int on_device
 int exacc_ccsd_set_lambda(exacc_ccsd_t hh, const double* l1, const double* l2, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     lambda_check(h);
     const int o = h.P.o, v = h.P.v;
     const hipMemcpyKind k = on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
@@ -2556,7 +2612,8 @@ int exacc_ccsd_density(exacc_ccsd_t hh, double* gamma, int on_device) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
     if (!gamma) raise(EXACC_ERR_INVALID_ARG, "null output");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     lambda_check(h);
     const int64_t n = h.P.n;
     double* g = on_device ? gamma : h.lam.gam;
@@ -2615,7 +2672,8 @@ int exacc_df_factors_noalloc(int nao, int nspinor, int naux, const double* C, co
 int exacc_ccsd_stage_times(exacc_ccsd_t hh, const char** names, double* ms, int* count, int reset) {
   return guarded([&] {
     if (!hh || !count) raise(EXACC_ERR_INVALID_ARG, "null argument");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     const int cap = *count;
     const int nn = (int)h.tm.names.size();
     for (int i = 0; i < nn && i < cap; ++i) {
@@ -2632,7 +2690,8 @@ int exacc_ccsd_stage_times(exacc_ccsd_t hh, const char** names, double* ms, int*
 int exacc_ccsd_phase(exacc_ccsd_t hh, int* fp32, int* fp64_iters) {
   return guarded([&] {
     if (!hh) raise(EXACC_ERR_INVALID_ARG, "null handle");
-    Handle& h = *reinterpret_cast<Handle*>(hh);
+    Entered in(hh);
+    Handle& h = in.h;
     if (fp32) *fp32 = h.phase32 ? 1 : (h.dc == 2 ? 2 : 0);
     if (fp64_iters) *fp64_iters = h.fp64_iters;
     return (int)EXACC_OK;
@@ -2650,6 +2709,11 @@ int exacc_ccsd_destroy(exacc_ccsd_t hh) {
   if (!hh) return EXACC_OK;
   return guarded([&] {
     Handle* h = reinterpret_cast<Handle*>(hh);
+    {
+      std::lock_guard<std::mutex> lk(live().mu);
+      auto& all = live().handles;
+      all.erase(std::remove(all.begin(), all.end(), h), all.end());
+    }
     if (h->s) (void)hipStreamSynchronize(h->s);
     set_alloc_registry(nullptr, 0);
     set_gett_workspace(nullptr, 0);

@@ -1,5 +1,5 @@
-"""The residue workspace is extra memory: what needs its place takes it, and the handle
-takes it again when there is room."""
+"""The residue workspace is extra memory: what needs its place takes it, another handle's too,
+and the handle takes it again when there is room."""
 import numpy as np
 import pytest
 
@@ -35,3 +35,32 @@ def test_workspace_comes_back_after_the_triples(lib):
     assert any((a != b).any() for a, b in zip(first, plain[0]))     # which is another route
     roomy = run(0, True)
     assert roomy[3] == 0 and np.abs(e - roomy[2]).max() <= 1e-12 * np.abs(e).max()
+
+
+def test_second_handle_takes_an_idle_ones_workspace(lib):
+    import torch
+    from paper_2103_08473_amd import exacc
+    o, v, X = 24, 168, 504
+    base = exacc.memory_estimate(o, v, X, hbm_budget_bytes=1)
+    extra = exacc.memory_estimate(o, v, X) - base
+    assert extra > 1 << 30
+    eps, B = make_system(o, v, X, seed=3)
+    t = make_amplitudes(o, v, seed=4)
+    with exacc.CCSD(eps, B, o) as cc:
+        cc.set_amplitudes(*t)
+        first = cc.residual()
+        free = torch.cuda.mem_get_info()[0]
+        with exacc.CCSD(eps, B, o, hbm_budget_bytes=base):
+            need = free - torch.cuda.mem_get_info()[0]
+        # leave half a workspace less than a second handle holds
+        fill = torch.empty(torch.cuda.mem_get_info()[0] - need + extra // 2, dtype=torch.uint8, device="cuda")
+        with exacc.CCSD(eps, B, o) as other:
+            other.set_amplitudes(*t)
+            second, again = other.residual(), cc.residual()
+        del fill
+        torch.cuda.empty_cache()
+        last = cc.residual()
+    for r in (second, again):                                       # without the workspace
+        for a, b in zip(first, r):
+            assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
+    assert all((a == b).all() for a, b in zip(first, last))         # with it
