@@ -193,7 +193,8 @@ struct Src {
 // Scale exponents, magnitudes and flatness of all rows of an operand, padding included: per row
 // the largest |component| and the sum of squares (fixed order), then the magnitudes, of which each
 // thread has kept its first kKeep entries' (the upper words, below the entries themselves); a
-// longer row is read again.  kfast: tpr threads per row; else 32 rows x 32 k phases per workgroup.
+// longer row is read again.  kfast: tpr threads per row; else 1024 / tpr rows of a
+// workgroup side by side, 32, or 8 where 32 would give too few workgroups.
 // what: 1 the scales, 2 the magnitudes (with the norms of an earlier launch where 1 is left
 // out), 3 both.  Bound by reading the operand.
 __global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src b, int tpr_a, int tpr_b, int S,
@@ -204,18 +205,9 @@ __global__ __launch_bounds__(1024) void mod_norm_kernel(Src a, int blocks_a, Src
   const int tid = threadIdx.x;
   __shared__ double ssum[1024], smax[1024];
   if (flag && blockIdx.x == 0 && tid == 0) *flag = 0;
-  int row, k0, width, stride;
-  if (s.kfast) {
-    width = first ? tpr_a : tpr_b;
-    row = blk * (1024 / width) + tid / width;
-    k0 = tid % width;
-    stride = 1;
-  } else {
-    width = 32;
-    row = blk * 32 + (tid & 31);
-    k0 = tid >> 5;
-    stride = 32;
-  }
+  const int width = first ? tpr_a : tpr_b, rows = 1024 / width;
+  const int row = blk * rows + (s.kfast ? tid / width : tid % rows);
+  const int k0 = s.kfast ? tid % width : tid / rows, stride = s.kfast ? 1 : rows;
   const bool has = row < s.rows && (s.r_valid == 0 || row % s.r_in < s.r_valid);
   const bool plain = s.k_in == s.K;
   const double* p = has ? s.p + 2 * cmap(row, s.r_in, s.r_so, s.r_si) : nullptr;
@@ -748,8 +740,8 @@ __global__ __launch_bounds__(256) void mod_joint_exps_kernel(int* exps, double* 
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-int tpr_of(const Src& s) { return s.K >= 4096 ? 256 : 64; }
-int norm_blocks(const Src& s) { return cdiv(32 * s.rb, s.kfast ? 1024 / tpr_of(s) : 32); }
+int tpr_of(const Src& s) { return s.kfast ? (s.K >= 4096 ? 256 : 64) : s.rb < 256 ? 128 : 32; }
+int norm_blocks(const Src& s) { return cdiv(32 * s.rb, 1024 / tpr_of(s)); }
 
 // Residue planes of one or two operands (b may have rows == 0).
 void split(const Src& a, const Src& b, Level lv, hipStream_t s) {
@@ -786,27 +778,34 @@ void launch_planes(PlaneGemm g, hipStream_t s) {
 
 // Tile choice: the padded block count of each tile shape over its measured rate (TOP/s at
 // full tiles, see mod_gemm_kernel), in whole rounds of the workgroups the chip holds.
+struct Tile {
+  int pick;     // 0: 8 x 8 blocks, 1: 4 x 8, 2: 8 x 4, 3: 4 x 4
+  double cost;  // padded blocks / (TOP/s)
+};
+Tile tile_for(int mb, int nb, int planes) {
+  static const struct {
+    int ra, rb, resident;
+    double rate;
+  } c[4] = {{8, 8, 256, 2200}, {4, 8, 512, 1900}, {8, 4, 512, 1940}, {4, 4, 768, 1720}};
+  Tile best{0, 1e300};
+  for (int q = 0; q < 4; ++q) {
+    const int64_t wgs = (int64_t)cdiv(mb, c[q].ra) * cdiv(nb, c[q].rb) * planes, r = c[q].resident;
+    const double rounds = wgs >= 8 * r ? (double)wgs / r : (double)((wgs + r - 1) / r);
+    const double cost = rounds * r * c[q].ra * c[q].rb / c[q].rate;
+    if (cost < best.cost) best = {q, cost};
+  }
+  return best;
+}
 template <bool TEST = false>
 void gemm_planes(PlaneGemm g, hipStream_t s) {
-  const int planes = TEST ? 1 : kPlanes - 2;  // 16 moduli as a rule
   if (g.kb < 4) raise(-1, "residue product: K too short for its pipeline");  // two stages at least
   for (int i = 0; i < kNP; ++i) g.p[i] = kMods[i];
-  auto cost = [&](int ra, int rb, int resident, double rate) {
-    const int64_t wgs = (int64_t)cdiv(g.mb, ra) * cdiv(g.nb, rb) * planes;
-    const double rounds = wgs >= 8 * resident ? (double)wgs / resident : (double)((wgs + resident - 1) / resident);
-    return rounds * resident * ra * rb / rate;
-  };
-  const double c0 = cost(8, 8, 256, 2200), c1 = cost(4, 8, 512, 1900), c2 = cost(8, 4, 512, 1940),
-               c3 = cost(4, 4, 768, 1720);
-  const double best = std::min(std::min(c0, c1), std::min(c2, c3));
-  if (best == c0)
-    launch_planes<2, 4, 4, 2, 1, 1, false, TEST>(g, s);
-  else if (best == c1)
-    launch_planes<2, 2, 2, 4, 2, 2, false, TEST>(g, s);
-  else if (best == c2)
-    launch_planes<2, 2, 4, 2, 2, 2, false, TEST>(g, s);
-  else
-    launch_planes<2, 2, 2, 2, 3, 3, false, TEST>(g, s);
+  switch (tile_for(g.mb, g.nb, TEST ? 1 : kPlanes - 2).pick) {  // 16 moduli as a rule
+    case 0: return launch_planes<2, 4, 4, 2, 1, 1, false, TEST>(g, s);
+    case 1: return launch_planes<2, 2, 2, 4, 2, 2, false, TEST>(g, s);
+    case 2: return launch_planes<2, 2, 4, 2, 2, 2, false, TEST>(g, s);
+    default: return launch_planes<2, 2, 2, 2, 3, 3, false, TEST>(g, s);
+  }
 }
 
 thread_local char* t_ws = nullptr;
@@ -817,17 +816,21 @@ inline int kblocks(int K) { return 2 * cdiv(K, 64); }
 
 }  // namespace
 
-// Estimated times (us).  FP64 GETT: 64 x 64 tiles at 62 TFLOP/s (55 to 72 reached).  Here: six
-// launches, one of them the FP64 kernel that returns, splitting 15 ps per element, reconstruction 15 ps per output, the plane products at
-// 1.7 POP/s on 32 x 32 blocks.  Measured at the line (us, FP64 GETT / this): 900^3 138 / 107,
-// 400 x 19800 x 600 687 / 540, 4032 x 576 x 504 176 / 155, 190 x 9730 x 9730 2266 / 2215; under
-// it 640^3 59 / 66, 28224 x 168 x 504 391 / 440, 1131 x 1131 x 259 67 / 82.
+// Estimated times (us).  FP64 GETT: 64 x 64 tiles at 58 TFLOP/s (43 to 67 reached).  Here: seven
+// launches, two of them the FP64 kernel's that return; scales, magnitudes and splitting 18 ps per
+// element; reconstruction 15 ps per output; the plane products as tile_for has them; the test
+// 0.36 per stage of a tile alone on its CU, or the whole at 1.7 POP/s.  Measured (us, FP64 GETT /
+// this): 900^3 135 / 103, 1131^3 213 / 146, 400 x 19800 x 600 696 / 643, 700 x 900 x 5000 461 / 351,
+// 600 x 700 x 40000 2056 / 1813; under the line 640^3 57 / 65, 28224 x 168 x 504 396 / 508,
+// 1131 x 1131 x 259 64 / 80, 190 x 9730 x 9730 2129 / 2355, 400 x 400 x 19600 579 / 613.  Operands
+// that fail the test cost the FP64 GETT and the test: 1131^3 257, 1200 x 1200 x 4096 776 / 838.
 bool mod_gemm_pays(int64_t M, int64_t N, int64_t K) {
-  if (M < 128 || N < 128 || K < 128) return false;
+  if (M < 128 || N < 128 || K < 128 || M > 0x7fffffffLL || N > 0x7fffffffLL) return false;
   auto up = [](int64_t x, int64_t m) { return (double)((x + m - 1) / m * m); };
-  const double t64 = 8.0 * up(M, 64) * up(N, 64) * (double)K / 62e6;
-  const double tm = 40.0 + (double)(M + N) * K * 15e-6 + (double)M * N * 15e-6 +
-                    2.0 * (kPlanes - 1) * up(M, 32) * up(N, 32) * up(K, 64) / 1.7e9;
+  const double t64 = 8.0 * up(M, 64) * up(N, 64) * (double)K / 58e6;
+  const double test = std::max(0.36 * up(K, 64) / 64, 2.0 * up(M, 32) * up(N, 32) * up(K, 64) / 1.7e9);
+  const double tm = 30.0 + (double)(M + N) * K * (K > kMaxK ? 23e-6 : 18e-6) + (double)M * N * 15e-6 +
+                    tile_for(cdiv(M, 32), cdiv(N, 32), kPlanes - 2).cost * 2048e-6 * up(K, 64) + test;
   return tm < 0.95 * t64;
 }
 
@@ -894,9 +897,12 @@ const int* mod_gemm(const Gett<double>& g0, hipStream_t s) {
     if (nr < nb) nr = nr / 8 * 8;
   }
   const int cb = (int)(cbytes / tbytes);  // C blocks
-  int mc = std::min(ma, std::max(8, cb / std::min(nr, 64) / 8 * 8));
-  int nc = std::min(nr, std::max(1, cb / mc));
-  if (nc < nr && nc >= 8) nc = nc / 8 * 8;
+  int mc = ma, nc = nr;
+  if ((int64_t)ma * nr > cb) {
+    mc = std::min(ma, std::max(8, cb / std::min(nr, 64) / 8 * 8));
+    nc = std::min(nr, std::max(1, cb / mc));
+    if (nc < nr && nc >= 8) nc = nc / 8 * 8;
+  }
   char* w = t_ws;
   auto take = [&](size_t bytes) {
     char* p = w;
