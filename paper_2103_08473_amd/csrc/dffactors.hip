@@ -151,6 +151,19 @@ constexpr size_t kChunk = (size_t)128 << 20;
 size_t chunk_bytes(int m, int n, int X) {
   return std::min(kChunk, up256((size_t)X * n * m * 16)) + std::min(kChunk, up256((size_t)X * n * n * 16));
 }
+// B holds the half-transformed integrals, so it is written while C and J are still read.  An output
+// that overlaps C gets a copy of C; one that overlaps J, the whole first half transform ahead.
+struct Overlap {
+  size_t c, t1;  // bytes more of the region
+};
+Overlap overlap(int m, int n, int X, const void* C, const void* J, const void* B) {
+  auto hit = [&](const void* a, size_t bytes) {
+    const char *p = static_cast<const char*>(a), *b = static_cast<const char*>(B);
+    return p < b + (size_t)X * n * n * 16 && b < p + bytes;
+  };
+  return {hit(C, (size_t)m * n * 16) ? up256((size_t)m * n * 16) : 0,
+          hit(J, (size_t)X * m * m * 16) ? up256((size_t)X * n * m * 16) : 0};
+}
 size_t splitk_bytes(int X) { return std::min<size_t>((size_t)64 << 20, std::max<size_t>(1 << 20, (size_t)X * X * 256)); }
 
 // Host memory that one step's residual norm lands in: pinned, while the next step is on its way
@@ -205,9 +218,15 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
   const size_t fixed = fixed_bytes(X);
   if (fixed + slice_bytes(m, n, X, 1) > cap) raise(-2, "DF factors: scratch region too small");
   const int64_t nn = (int64_t)n * n;
-  const size_t room = (cap - fixed) / 2 / 256 * 256;
-  const size_t t1b = std::min(std::min(kChunk, up256((size_t)X * n * m * 16)), room);
-  const size_t mb = std::min(std::min(kChunk, up256((size_t)X * nn * 16)), room);
+  const Overlap ov = overlap(m, n, X, Cd, Jd, Bd);
+  // (a region too small for the whole half transform beside one column of M: in halves, as without
+  // an overlap)
+  const size_t all = cap - fixed - std::min(cap - fixed, ov.c);
+  const bool whole = ov.t1 && ov.t1 + up256((size_t)X * 16) <= all;
+  const size_t room = all / 2 / 256 * 256;
+  const size_t t1b = whole ? ov.t1 : std::min(std::min(kChunk, up256((size_t)X * n * m * 16)), room);
+  const size_t mb = std::min(std::min(kChunk, up256((size_t)X * nn * 16)), whole ? all - ov.t1 : room);
+  if (t1b < (size_t)m * 16 || mb < (size_t)X * 16) raise(-2, "DF factors: scratch region too small");
   const int qc = (int)std::max<int64_t>(1, std::min<int64_t>(X, (int64_t)(t1b / ((size_t)n * m * 16))));
   const int pc = (int)std::max<int64_t>(1, std::min<int64_t>(n, (int64_t)(t1b / ((size_t)qc * m * 16))));
   const int64_t xc = std::max<int64_t>(1, std::min<int64_t>(nn, (int64_t)(mb / ((size_t)X * 16))));
@@ -229,6 +248,11 @@ int df_core(int m, int n, int X, const double* Cd, const double* Jd, const doubl
   double* Z2 = cv.take((size_t)X * X * 16);
   double* T1 = cv.take((size_t)qc * pc * m * 16);
   double* M = cv.take((size_t)X * xc * 16);
+  if (ov.c) {
+    double* Cc = cv.take((size_t)m * n * 16);
+    k_copy_bytes(Cc, Cd, (int64_t)m * n * 16, s);
+    Cd = Cc;
+  }
   const size_t left = cap > cv.used ? (cap - cv.used) / 256 * 256 : 0;
   const size_t wsb = std::min(left, ws_cap);
   set_gett_workspace(wsb >= (1u << 20) ? cv.take(wsb) : nullptr, wsb >= (1u << 20) ? wsb : 0);
@@ -369,7 +393,8 @@ int df_factors_impl(int m, int n, int X, const double* C, const double* J, const
   // every temporary in one region, no larger than its sizes need: allocations up to 16 MB
   // take 0.02 ms here, larger ones 0.3 ms and more (0.04 to allocate, 0.27 to free 70 MB)
   const size_t wsb = splitk_bytes(X);
-  const size_t cap = fixed_bytes(X) + std::max(chunk_bytes(m, n, X), slice_bytes(m, n, X, 1)) + wsb;
+  const Overlap ov = overlap(m, n, X, Cd, Jd, Bd);
+  const size_t cap = fixed_bytes(X) + std::max(chunk_bytes(m, n, X), slice_bytes(m, n, X, 1)) + ov.c + ov.t1 + wsb;
   char* region = own.alloc(4, cap);
   // residues of the transforms' and the metric product's operands, where that gains and leaves
   // the device memory it takes to spare
