@@ -740,7 +740,8 @@ __global__ __launch_bounds__(256) void mod_joint_exps_kernel(int* exps, double* 
 
 inline int cdiv(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-int tpr_of(const Src& s) { return s.kfast ? (s.K >= 4096 ? 256 : 64) : s.rb < 256 ? 128 : 32; }
+// Threads per row of mod_norm_kernel: as many as keep a whole row, up to 32768 entries.
+int tpr_of(const Src& s) { return s.kfast ? (s.K <= 2048 ? 64 : s.K <= 8192 ? 256 : 1024) : s.rb < 256 ? 128 : 32; }
 int norm_blocks(const Src& s) { return cdiv(32 * s.rb, 1024 / tpr_of(s)); }
 
 // Residue planes of one or two operands (b may have rows == 0).
