@@ -36,8 +36,39 @@ PEAK_FP64_MFMA = 78.6  # TFLOP/s, MI355X dense FP64 matrix
 PEAK_FP32_MFMA = 157.3  # TFLOP/s, MI355X dense FP32 matrix
 PEAK_BF16_MFMA = 2516.6  # TFLOP/s, MI355X dense BF16 matrix
 PEAK_INT8_MFMA = 5033.2  # TOP/s, MI355X dense INT8 matrix
-INT8_OPS_PER_CMAC = 60  # 15 moduli, two real products of 2 operations each
+INT8_OPS_PER_CMAC = 64  # 16 moduli, two real products of 2 operations each
 WORKLOAD = dict(nocc=40, nvir=360, naux=1200, seed=0)
+
+
+# HBM bytes of the ladder tile build per iteration (scales and split of the factor rows, plane
+# products, reconstruction), from one rocprofv3 pass each of FETCH_SIZE and WRITE_SIZE, scaled by
+# what the counters read for a plain 1 GiB device copy (fetch x2.000, write x1.000), and the plane
+# kernels' MFMA-busy fraction and clock from a third pass.  They hold for the sources they were
+# taken with: `source_sha256` hashes modgemm.hip and the Hermitian ladder driver in exacc.cpp; the
+# figures are reported as null once either text differs.
+TRAFFIC = {"source_sha256": "e5af1838aa8c0f09bea589487f86cf33280000aa96d642ffa35c95329a82ef54",
+           "fetch_bytes": 7.222e11, "write_bytes": 2.318e11, "mfma_busy": 0.398, "clock_ghz": 2.25}
+MOD_SRC = os.path.join(ROOT, "paper_2103_08473_amd", "csrc", "modgemm.hip")
+EXACC_SRC = os.path.join(ROOT, "paper_2103_08473_amd", "csrc", "exacc.cpp")
+LADDER_MARKS = (b"static void ladder_apply_herm(Handle& h, const Work<R>& w, const R* F, int64_t row_stride,\n"
+                b"                              const TV<R>& Lp, R* Znp, bool bf, bool use_bvs) {",
+                b"// The ring term of the FP64 iterations after a mixed-precision switch")
+
+
+def kernel_source_sha256():
+    import hashlib
+    with open(MOD_SRC, "rb") as f:
+        g = f.read()
+    with open(EXACC_SRC, "rb") as f:
+        e = f.read()
+    i, j = e.find(LADDER_MARKS[0]), e.find(LADDER_MARKS[1])
+    return hashlib.sha256(g + (e[i:j] if 0 <= i < j else e)).hexdigest()
+
+
+def measured_counters():
+    """Counter-derived HBM bytes and MFMA-busy figures, or None if the kernels or the ladder
+    driver changed since they were taken."""
+    return TRAFFIC if kernel_source_sha256() == TRAFFIC["source_sha256"] else None
 
 
 def ladder_build_flops(o, v, X):
@@ -495,6 +526,7 @@ def main():
     contract_ms = stages.get("ladder_contract", float("nan")) / args.steps
     achieved = ladder_build_flops(o, v, X) / (build_ms * 1e-3) / 1e12
     int8 = achieved / 8 * INT8_OPS_PER_CMAC
+    ctr = measured_counters()
     ladder_ms = build_ms + contract_ms + stages.get("ladder_antisym", 0.0) / args.steps
     out = {
         "metric": "ladder TFLOP/s + s/CCSD iter, FP64 vs mixed at |dE|<=1e-7 Eh; p99 solve latency",
@@ -523,10 +555,13 @@ def main():
                      "frac": round(int8 / PEAK_INT8_MFMA, 4),
                      "fp64_equivalent_tflops": round(achieved, 3),
                      "fp64_equivalent_over_fp64_peak": round(achieved / PEAK_FP64_MFMA, 4),
-                     "traffic": None,
+                     "traffic": (ctr["fetch_bytes"] + ctr["write_bytes"]) if ctr else None,
+                     "traffic_unit": "bytes per iteration (HBM, counter-derived)",
+                     "counters": ({"mfma_busy": ctr["mfma_busy"], "clock_ghz": ctr["clock_ghz"]}
+                                  if ctr else None),
                      "algorithmic_bytes_per_launch": round(ladder_build_bytes(o, v, X)),
                      "flops_counted": "INT8 operations of the Hermitian build (blocks on and above "
-                                      "the pair diagonal), 60 per complex multiply-add, over the "
+                                      "the pair diagonal), 64 per complex multiply-add, over the "
                                       "stage's time, splitting and reconstruction included; "
                                       "fp64_equivalent: 8 flops per complex multiply-add"},
         "solves": solves,

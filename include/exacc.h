@@ -116,7 +116,11 @@ void exacc_ccsd_default_opts(exacc_ccsd_opts* o);
  * set); create drops them when the plan with them exceeds the device memory, and
  * the estimate then overstates the footprint by that part.  A workspace for large
  * FP64 products is included (at most 10 GiB); hbm_budget_bytes shrinks or drops it
- * before anything is refused, and so does create on a nearly full device. */
+ * before anything is refused, and so does create on a nearly full device.  An
+ * allocation of the library that finds no room takes the workspaces of handles on
+ * the device that no call is running on; they take them again when there is room.
+ * The products' errors are those of FP64 sums or less with and without it, their
+ * last bits are not the same. */
 size_t exacc_ccsd_memory_estimate(int nocc, int nvir, int naux, const exacc_ccsd_opts* opts);
 
 /* Validate the inputs, copy them to the device, build the stored integral
@@ -237,7 +241,8 @@ int exacc_ccsd_density(exacc_ccsd_t h, double* gamma, int ptr_on_device);
  * stream: hipStream_t or NULL (the call then uses a stream of its own).
  * Temporary device memory of 6 naux^2 + naux nspinor (nao + nspinor) complex
  * values at most, the second part never above 256 MB, and 768 MB for large
- * sizes where twice that is free (plus copies of the inputs for host pointers),
+ * sizes where twice that is free (plus copies of the inputs for host pointers, and
+ * of C or the half-transformed integrals where B overlaps C or J),
  * is allocated and freed inside the call (NOMEM if it does not fit).  INVALID_ARG for sizes outside
  * 1 <= nspinor <= nao, naux >= 1, null pointers, or a metric on which the
  * iteration does not converge (not positive definite, or condition number

@@ -1112,10 +1112,10 @@ void ModLadder::rows(int a_lo, int a_hi, int a0, int64_t row0, double* W, int64_
 }
 
 // ---------------------------------------------------------------- triples
-// nvir 126 per triple: FP64 products 49 us; here 20 (1.2 POP/s: 6 stages of K per tile, 70 MB
-// of planes and residues moved) and 11.5 for the reconstruction.  Tiles of 8 x 4 blocks, two
-// workgroups per CU, which load 1.2 times the operand bytes, took 22.9, of 4 x 4 blocks 28;
-// with the products of a batch one after the other instead of side by side along n, the planes
+// nvir 126 per triple: FP64 products 49 us; here 22 (1.2 POP/s: 6 stages of K per tile, 70 MB
+// of planes and residues moved), 10.6 for the reconstruction and 3 for the test.  Tiles of 8 x 4
+// blocks, two workgroups per CU, which load 1.2 times the operand bytes, took 2.9 more, of 4 x 4
+// blocks 8; with the products of a batch one after the other instead of side by side along n, the planes
 // of V_j and V_k are read from memory for each, 1.7 more.
 // Per triple the FP64 tiles take TFP us at 62 TFLOP/s (K = nvir in three passes over the
 // output), the residues their plane products and one reconstruction (the estimates of
