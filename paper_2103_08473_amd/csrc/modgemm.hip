@@ -1039,14 +1039,19 @@ int ModLadder::level(const double* F, int64_t row_stride, int v, int X, hipStrea
   a.flat = reinterpret_cast<float*>(t_ws + 256 + rows);
   a.mags = reinterpret_cast<signed char*>(t_ws + 256 + 2 * rows);
   norms(a, Src{}, 3, flag, s);
-  PlaneGemm g{};
-  g.A = g.B = a.mags;
-  g.mb = g.a_in = g.a_outer = g.nb = g.b_in = g.b_outer = a.rb;
-  g.kb = a.kb;
-  g.fa = g.fb = a.flat;
-  g.flat = kFlat;
-  g.out = flag;
-  gemm_planes<true>(g, s);
+  // the pairs of rows once each, up to the blocks of an eighth of them
+  const int step = std::max(64, 8 * cdiv(a.rb, 64));
+  for (int b0 = 0; b0 < a.rb; b0 += step) {
+    PlaneGemm g{};
+    g.A = g.B = a.mags + (int64_t)b0 * (a.kb / 2) * 2048;
+    g.mb = g.a_in = g.a_outer = std::min(step, a.rb - b0);
+    g.nb = g.b_in = g.b_outer = a.rb - b0;
+    g.kb = a.kb;
+    g.fa = g.fb = a.flat + 32 * b0;
+    g.flat = kFlat;
+    g.out = flag;
+    gemm_planes<true>(g, s);
+  }
   int lv = 2;
   HIPCHECK(hipMemcpyAsync(&lv, flag, sizeof lv, hipMemcpyDeviceToHost, s));
   HIPCHECK(hipStreamSynchronize(s));
