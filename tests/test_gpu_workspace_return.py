@@ -64,3 +64,25 @@ def test_second_handle_takes_an_idle_ones_workspace(lib):
         for a, b in zip(first, r):
             assert np.abs(a - b).max() <= 1e-12 * np.abs(a).max()
     assert all((a == b).all() for a, b in zip(first, last))         # with it
+
+
+def test_phase_answers_while_a_call_is_running(lib):
+    """A thread that watches a solve is not held until the solve returns."""
+    import threading
+    import time
+    from paper_2103_08473_amd import exacc
+    o, v, X = 8, 48, 144
+    eps, B = make_system(o, v, X, seed=5)
+    with exacc.CCSD(eps, B, o, tol=0.0) as cc:
+        cc.iterate(1)
+        t0 = time.perf_counter()
+        cc.iterate(20)
+        steps = max(40, int(20 * 2.0 / (time.perf_counter() - t0)))  # about two seconds
+        run = threading.Thread(target=cc.iterate, args=(steps,))
+        run.start()
+        time.sleep(0.2)
+        t0 = time.perf_counter()
+        cc.phase()
+        waited, running = time.perf_counter() - t0, run.is_alive()
+        run.join()
+    assert running and waited < 0.5
