@@ -178,7 +178,7 @@ struct Src {
   // planes[row / 32][k / 64][z][(k / 32) % 2][lane][16]: lane l holds row l % 32 and
   // k 16 (l / 32) .. + 15 of its 32 x 32 block, the fragment order of the 32x32x32 INT8 MFMA;
   // zero past rows and K.  All planes of 32 rows x 64 k are together, so that splitting writes
-  // whole 64 KiB runs (a plane-major order: 2.3 TB/s at 12363^2, this one: see mod_split_kernel)
+  // whole 68 KiB runs (a plane-major order: 2.3 TB/s at 12363^2, this one: see mod_split_kernel)
   signed char* planes;
   int* exps;        // power of two each row was scaled by (of t[1], see Tabs)
   // magnitudes, max(|re|, |im|) in units of the row's rms / kUnit, rounded down and at most 127, in
